@@ -88,21 +88,87 @@ template hipError_t pad_field<double, float>(const double *, const double *, flo
                                              hipStream_t);
 
 // ---------------------------------------------------------------------------
-// out[lambda_of[b]][v] = sum over slots of batch entry b of part[slot][v]
-// (double accumulation, fixed slot order)
+// Sum of a voxel's partial slots (double accumulation).  The slots are split
+// over G wavefronts of the block, each adding a contiguous run of them in
+// order with eight loads in flight, and the G sums are added in order: a fixed
+// order for a given grid.  A thread per voxel (G = 1) fills the chip only
+// from about a quarter million voxels on; below that one wavefront walked 256
+// slots on its own, which took 36-43 us on 33^3 voxels (37 MB of slots).
+// G depends on the number of voxels alone, so a wavelength's sum does not
+// depend on the batch it is in.  With G > 1 the result is valid in the first
+// wavefront (threads 0-63), one voxel a lane.
 // ---------------------------------------------------------------------------
-template <typename TP, typename TO>
-__global__ void reduce_kernel(const TP *__restrict__ part, const int32_t *__restrict__ slot_begin,
-                              const int32_t *__restrict__ slot_ids, const int32_t *__restrict__ lambda_of,
-                              TO *__restrict__ out, int64_t n_vox)
+constexpr int slot_groups(int64_t n_vox) { return n_vox >= 262144 ? 1 : n_vox >= 65536 ? 4 : 16; }
+
+template <typename TP>
+__device__ __forceinline__ double slot_run(const TP *__restrict__ part, const int32_t *__restrict__ slot_ids, int s,
+                                           int s1, int64_t n_vox, int64_t v)
+{
+    double acc = 0.0;
+    constexpr int U = 8;
+    for (; s + U <= s1; s += U) {
+        TP x[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) x[u] = part[(int64_t)slot_ids[s + u] * n_vox + v];
+#pragma unroll
+        for (int u = 0; u < U; ++u) acc += (double)x[u];
+    }
+    for (; s < s1; ++s) acc += (double)part[(int64_t)slot_ids[s] * n_vox + v];
+    return acc;
+}
+
+template <typename TP, int G>
+__device__ __forceinline__ double slot_sum(const TP *__restrict__ part, const int32_t *__restrict__ slot_begin,
+                                           const int32_t *__restrict__ slot_ids, int b, int64_t n_vox, int64_t v)
+{
+    const int s0 = slot_begin[b], s1 = slot_begin[b + 1];
+    if constexpr (G == 1) return v < n_vox ? slot_run(part, slot_ids, s0, s1, n_vox, v) : 0.0;
+    __shared__ double sums[G][64];
+    const int g = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), n = s1 - s0;
+    double acc = v < n_vox ? slot_run(part, slot_ids, s0 + n * g / G, s0 + n * (g + 1) / G, n_vox, v) : 0.0;
+    sums[g][threadIdx.x % 64] = acc;
+    __syncthreads();
+    if (g == 0)
+        for (int k = 1; k < G; ++k) acc += sums[k][threadIdx.x];
+    return acc;
+}
+
+// Voxel of this thread and whether it writes (blocks of 256 threads for
+// G = 1, of G wavefronts over 64 voxels otherwise).
+template <int G>
+__device__ __forceinline__ int64_t slot_voxel()
+{
+    return G == 1 ? (int64_t)blockIdx.x * 256 + threadIdx.x : (int64_t)blockIdx.x * 64 + threadIdx.x % 64;
+}
+
+template <int G>
+static dim3 slot_grid(int64_t n_vox, int n_batch)
+{
+    const int64_t per = G == 1 ? 256 : 64;
+    return dim3((unsigned)((n_vox + per - 1) / per), (unsigned)n_batch);
+}
+
+// out[lambda_of[b]][v] = sum of the slots of batch entry b
+template <typename TP, typename TO, int G>
+__global__ void __launch_bounds__(G == 1 ? 256 : 64 * G) reduce_kernel(const TP *__restrict__ part,
+                                                                       const int32_t *__restrict__ slot_begin,
+                                                                       const int32_t *__restrict__ slot_ids,
+                                                                       const int32_t *__restrict__ lambda_of,
+                                                                       TO *__restrict__ out, int64_t n_vox)
 {
     const int b = blockIdx.y;
-    const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (v >= n_vox) return;
-    double acc = 0.0;
-    const int s1 = slot_begin[b + 1];
-    for (int s = slot_begin[b]; s < s1; ++s) acc += (double)part[(int64_t)slot_ids[s] * n_vox + v];
-    out[(int64_t)lambda_of[b] * n_vox + v] = (TO)acc;
+    const int64_t v = slot_voxel<G>();
+    const double acc = slot_sum<TP, G>(part, slot_begin, slot_ids, b, n_vox, v);
+    if (v < n_vox && (G == 1 || threadIdx.x < 64)) out[(int64_t)lambda_of[b] * n_vox + v] = (TO)acc;
+}
+
+template <typename TP, typename TO, int G>
+static hipError_t reduce_t(const TP *part, const int32_t *slot_begin, const int32_t *slot_ids,
+                           const int32_t *lambda_of, int n_batch, TO *out, int64_t n_vox, hipStream_t st)
+{
+    hipLaunchKernelGGL((reduce_kernel<TP, TO, G>), slot_grid<G>(n_vox, n_batch), dim3(G == 1 ? 256 : 64 * G), 0, st,
+                       part, slot_begin, slot_ids, lambda_of, out, n_vox);
+    return hipGetLastError();
 }
 
 template <typename TP, typename TO>
@@ -110,11 +176,11 @@ hipError_t reduce_partials(const TP *part, const int32_t *slot_begin, const int3
                            const int32_t *lambda_of, int n_batch, TO *out, int64_t n_vox, hipStream_t st)
 {
     if (n_batch == 0 || n_vox == 0) return hipSuccess;
-    const int bs = 256;
-    dim3 grid((unsigned)((n_vox + bs - 1) / bs), (unsigned)n_batch);
-    hipLaunchKernelGGL((reduce_kernel<TP, TO>), grid, dim3(bs), 0, st, part, slot_begin, slot_ids, lambda_of, out,
-                       n_vox);
-    return hipGetLastError();
+    switch (slot_groups(n_vox)) {
+    case 1: return reduce_t<TP, TO, 1>(part, slot_begin, slot_ids, lambda_of, n_batch, out, n_vox, st);
+    case 4: return reduce_t<TP, TO, 4>(part, slot_begin, slot_ids, lambda_of, n_batch, out, n_vox, st);
+    default: return reduce_t<TP, TO, 16>(part, slot_begin, slot_ids, lambda_of, n_batch, out, n_vox, st);
+    }
 }
 
 template hipError_t reduce_partials<float, float>(const float *, const int32_t *, const int32_t *, const int32_t *,
@@ -247,40 +313,28 @@ template hipError_t source_update<float, double>(const double *, const float *, 
 // fused: J_fs = J_anchor + sum of partial slots; operator-splitting update;
 // S; next padded input; Ng history; per-wavelength max |dJ/J|
 // ---------------------------------------------------------------------------
-template <typename TP, typename G, typename TN>
-__global__ void __launch_bounds__(256) ali_update_kernel(AliUpdateArgs a)
+template <typename TP, typename G, typename TN, int NG>
+__global__ void __launch_bounds__(NG == 1 ? 256 : 64 * NG) ali_update_kernel(AliUpdateArgs a)
 {
+    constexpr int BS = NG == 1 ? 256 : 64 * NG;
     const int b = blockIdx.y;
     const int lam = a.lambda_of[b];
-    const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    double rel = 0.0, res = 0.0;
+    const int64_t v = slot_voxel<NG>();
+    const bool own = v < a.n_vox && (NG == 1 || threadIdx.x < 64);  // this thread's voxel is written by it
+    double rel = 0.0, res = 0.0, sum = 0.0;
+    if (a.part && !a.rfs_in)  // uniform over the launch
+        sum = slot_sum<TP, NG>(reinterpret_cast<const TP *>(a.part), a.slot_begin, a.slot_ids, b, a.n_vox, v);
     if (a.rfs_out) {  // uniform over the launch: no thread reaches the block reductions
-        if (v < a.n_vox) {
+        if (own) {
             const int64_t i = (int64_t)lam * a.n_vox + v;
-            double jfs = a.J_anchor ? a.J_anchor[i] : 0.0;
-            if (a.part) {
-                const TP *part = reinterpret_cast<const TP *>(a.part);
-                const int s1 = a.slot_begin[b + 1];
-                double acc = 0.0;
-                for (int s = a.slot_begin[b]; s < s1; ++s) acc += (double)part[(int64_t)a.slot_ids[s] * a.n_vox + v];
-                jfs += acc;
-            }
+            const double jfs = (a.J_anchor ? a.J_anchor[i] : 0.0) + sum;
             a.rfs_out[i] = jfs - a.J[i];
         }
         return;
     }
-    if (v < a.n_vox) {
+    if (own) {
         const int64_t i = (int64_t)lam * a.n_vox + v;
-        double jfs = a.J_anchor ? a.J_anchor[i] : 0.0;
-        if (a.rfs_in) {
-            jfs = a.J[i] + a.rfs_in[i];
-        } else if (a.part) {
-            const TP *part = reinterpret_cast<const TP *>(a.part);
-            const int s1 = a.slot_begin[b + 1];
-            double acc = 0.0;
-            for (int s = a.slot_begin[b]; s < s1; ++s) acc += (double)part[(int64_t)a.slot_ids[s] * a.n_vox + v];
-            jfs += acc;
-        }
+        const double jfs = a.rfs_in ? a.J[i] + a.rfs_in[i] : (a.J_anchor ? a.J_anchor[i] : 0.0) + sum;
         const double e = (double)reinterpret_cast<const G *>(a.eps)[i];
         const double L = (double)reinterpret_cast<const G *>(a.lstar)[i];
         const double Bv = (double)reinterpret_cast<const G *>(a.B)[i];
@@ -302,22 +356,32 @@ __global__ void __launch_bounds__(256) ali_update_kernel(AliUpdateArgs a)
         const TN out = (TN)(a.S_anchor ? s - a.S_anchor[i] : s);
         store_padded<TN>(reinterpret_cast<TN *>(a.next_pad), lam, a.n_vox, v, a.Nx, a.Ny, 1, out);
     }
-    rel = block_max<256>(rel);
+    rel = block_max<BS>(rel);
     if (threadIdx.x == 0) atomic_max_nonneg(&a.rel_change[lam], rel);
     if (a.resid) {
         __syncthreads();  // the reduction scratch of block_max is reused
-        res = block_max<256>(res);
+        res = block_max<BS>(res);
         if (threadIdx.x == 0) atomic_max_nonneg(&a.resid[lam], res);
     }
+}
+
+template <typename TP, typename G, typename TN, int NG>
+static hipError_t ali_update_g(const AliUpdateArgs &a, int n_batch, hipStream_t st)
+{
+    hipLaunchKernelGGL((ali_update_kernel<TP, G, TN, NG>), slot_grid<NG>(a.n_vox, n_batch),
+                       dim3(NG == 1 ? 256 : 64 * NG), 0, st, a);
+    return hipGetLastError();
 }
 
 template <typename TP, typename G, typename TN>
 static hipError_t ali_update_t(const AliUpdateArgs &a, int n_batch, hipStream_t st)
 {
-    const int bs = 256;
-    dim3 grid((unsigned)((a.n_vox + bs - 1) / bs), (unsigned)n_batch);
-    hipLaunchKernelGGL((ali_update_kernel<TP, G, TN>), grid, dim3(bs), 0, st, a);
-    return hipGetLastError();
+    // launches that sum no slots need no groups
+    switch (a.part && !a.rfs_in ? slot_groups(a.n_vox) : 1) {
+    case 1: return ali_update_g<TP, G, TN, 1>(a, n_batch, st);
+    case 4: return ali_update_g<TP, G, TN, 4>(a, n_batch, st);
+    default: return ali_update_g<TP, G, TN, 16>(a, n_batch, st);
+    }
 }
 
 hipError_t ali_update(const AliUpdateArgs &a, bool part_double, bool grid_double, bool next_double, int n_batch,
@@ -371,13 +435,18 @@ __global__ void __launch_bounds__(256) ng_dots_kernel(const double *__restrict__
     }
 }
 
-__global__ void ng_solve_kernel(const double *__restrict__ blk, int nblk, double *__restrict__ coef)
+// The block sums of the five dot products: lane l adds the blocks l, l + 64, ...
+// in order, then the lanes are added pairwise (a fixed order; one thread adding
+// all blocks in turn took 45 us).
+__global__ void __launch_bounds__(64) ng_solve_kernel(const double *__restrict__ blk, int nblk, double *__restrict__ coef)
 {
     const int b = blockIdx.x;
-    if (threadIdx.x != 0) return;
     double A[5] = {0, 0, 0, 0, 0};
-    for (int k = 0; k < nblk; ++k)
+    for (int k = threadIdx.x; k < nblk; k += 64)
         for (int c = 0; c < 5; ++c) A[c] += blk[((int64_t)b * nblk + k) * 5 + c];
+    for (int c = 0; c < 5; ++c)
+        for (int o = 32; o > 0; o >>= 1) A[c] += __shfl_xor(A[c], o, 64);
+    if (threadIdx.x != 0) return;
     const double det = A[0] * A[2] - A[1] * A[1];
     double ca = 0.0, cb = 0.0, ok = 0.0;
     if (det > 1e-10 * A[0] * A[2] && det == det && det < 1e300) {
