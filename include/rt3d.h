@@ -487,7 +487,10 @@ rt_status rt_autotune_dirs(rt_grid_t grid, int32_t n_lambda, const void *chi, co
  * Fixes the launch shape of the grid's single-output formal-solution kernel
  * to one of the compiled shapes (threads = workgroup size bound, rays = rays
  * per thread), e.g. one that rt_autotune chose in an earlier process, so that
- * runs are reproducible without re-tuning.  A launch may use fewer threads
+ * runs are reproducible without re-tuning.  The grid's default shape (as
+ * rt_launch_shape reports it on a fresh grid) keeps its own number of ray
+ * bundles; any other shape takes the number it is compiled for (layer tiles)
+ * or the fewest that fit (band tiles).  A launch may use fewer threads
  * than the bound when a direction has fewer rays.  RT_E_INVALID if no
  * compiled shape matches or the shape cannot hold one direction's rays in
  * the device's LDS; RT_E_UNSUPPORTED on spherical grids.  Does not launch

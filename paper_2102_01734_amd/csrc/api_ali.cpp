@@ -162,16 +162,16 @@ static rt_status plain_step_launches(rt_grid *g, rt_state *s, const std::vector<
 static rt_status graph_plain_step(rt_grid *g, rt_state *s, const std::vector<int32_t> &lams,
                                   const int32_t *lambda_of, hipStream_t st, int sweeps)
 {
-    const Variant &v = variant(g, g->dbl, true, false);
+    const Variant v = pick_variant(g, g->dbl, true, false, (int)lams.size());
     DevSchedule *sc = nullptr;
     rt_status rs = get_schedule(g, v.n_wg, lams, &sc, nullptr, &v);
     if (rs != RT_OK) return rs;
     DevBuf &pJ = g->dbl ? g->partJ64 : g->partJ;
     HIPCHK(pJ.ensure((size_t)sc->n_slots * g->n_vox * (g->dbl ? 8 : 4)));
     char buf[512];
-    snprintf(buf, sizeof buf, "%d|%p|%p|%p|%p|%p|%p|%p|%p|%p|%p|%d|%d|%d|%d:", g->hist_count % 4, (void *)s->J,
+    snprintf(buf, sizeof buf, "%d|%p|%p|%p|%p|%p|%p|%p|%p|%p|%p|%d|%d.%d|%d.%d|%d:", g->hist_count % 4, (void *)s->J,
              (void *)s->S, s->lstar, s->eps, s->B, (void *)s->rel_change, pJ.p, (void *)st,
-             g->net ? g->net_r.p : nullptr, g->resid.p, s->n_lambda, v.lb, v.R,
+             g->net ? g->net_r.p : nullptr, g->resid.p, s->n_lambda, v.lb, v.nb, v.R, v.band ? 1 : 0,
              g->nonlocal ? (g->os_gs ? 1000000 + sweeps : sweeps) : -1);
     std::string key(buf);
     for (int l : lams) key += std::to_string(l) + ",";

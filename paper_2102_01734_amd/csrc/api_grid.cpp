@@ -576,6 +576,10 @@ rt_status rt_create_grid(const rt_grid_desc *desc, rt_grid_t *out)
     HIPCHK(g->s.ensure(nvis * 8));
     HIPCHK(hipMemcpy(g->goff.p, g->geo.goff.data(), nvis * 4, hipMemcpyHostToDevice));
     HIPCHK(hipMemcpy(g->dxy.p, g->geo.dxy.data(), nvis * 4, hipMemcpyHostToDevice));
+    // the kernels take half path lengths (half the optical depth of a segment is
+    // what the steps between points are sums of); the host has no use for them
+    // beyond this point
+    for (double &v : g->geo.s) v *= 0.5;
     HIPCHK(hipMemcpy(g->s.p, g->geo.s.data(), nvis * 8, hipMemcpyHostToDevice));
     HIPCHK(g->brow.ensure(nvis * 4));
     HIPCHK(hipMemcpy(g->brow.p, g->geo.brow.data(), nvis * 4, hipMemcpyHostToDevice));
@@ -621,7 +625,7 @@ rt_status rt_grid_info(rt_grid_t g, int64_t *n_vox, int32_t *n_dir, int64_t *n_v
     if (n_vox) *n_vox = g->n_vox;
     if (n_dir) *n_dir = g->n_dir;
     if (n_visits_total) *n_visits_total = g->n_visits;
-    if (n_wg) *n_wg = g->sphere ? (int32_t)g->sph_chunks.size() : variant(g, g->dbl, true, false).n_wg;
+    if (n_wg) *n_wg = g->sphere ? (int32_t)g->sph_chunks.size() : pick_variant(g, g->dbl, true, false, g->desc.n_lambda_max).n_wg;
     return RT_OK;
 }
 }  // extern "C"

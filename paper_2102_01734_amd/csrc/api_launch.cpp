@@ -32,7 +32,8 @@ ChunkPtrs chunk_ptrs(const SphereChunkDev &ch, const void *stage)
 }
 // Resident-workgroup count and LDS size of one launch shape; ok = false when
 // the shape cannot hold all rays of a bundle or its tiles do not fit.
-Variant make_variant(rt_grid *g, bool dbl, bool wj, bool wl, int lb, int R, int occ, bool band, bool allow_spill)
+Variant make_variant(rt_grid *g, bool dbl, bool wj, bool wl, int lb, int R, int occ, bool band, bool allow_spill,
+                     int n_bundles)
 {
     Variant v;
     v.dbl = dbl; v.wj = wj; v.wl = wl; v.lb = lb; v.R = R; v.band = band;
@@ -43,7 +44,7 @@ Variant make_variant(rt_grid *g, bool dbl, bool wj, bool wl, int lb, int R, int 
     // the padded field of one wavelength must stay addressable by 32-bit buffer offsets
     if ((int64_t)4 * g->n_vox * 2 * (int64_t)esz > (int64_t)INT_MAX) return v;
     if (!band) {
-        const int nb = occ;
+        const int nb = n_bundles > 0 ? n_bundles : occ;
         const int Q = (rays + nb - 1) / nb;
         const int q_last = rays - (nb - 1) * Q;  // the smallest bundle
         if (q_last <= 0) return v;
@@ -62,7 +63,7 @@ Variant make_variant(rt_grid *g, bool dbl, bool wj, bool wl, int lb, int R, int 
         // workgroups per CU
         const int span = g->span_max;
         bool found = false;
-        for (int nb = 2; nb <= Ny && !found; ++nb) {
+        for (int nb = std::max(2, n_bundles); nb <= (n_bundles > 0 ? n_bundles : Ny) && !found; ++nb) {
             const int H = (Ny + nb - 1) / nb, Hmin = Ny / nb;
             if (H + span + 1 > Ny) continue;
             const int64_t Q = (int64_t)H * Nx;
@@ -121,6 +122,113 @@ void setup_variant(rt_grid *g, bool dbl, bool wj, bool wl)
     }
 }
 
+// Estimated time (cycles) of a launch of n_lambda x n_dirs items per bundle
+// whose directions have sum_m visits in all and max_m at most.  A visit costs a
+// workgroup a fixed part (barrier, visit set-up, the wave's own latency) plus
+// an issue part per ray-wave on its SIMD, which the workgroups of a CU share;
+// a layer end costs the memory latency of its flush, once per group of words
+// that a thread reads together, and an issue part per word.  Items are dealt
+// longest first, so a launch takes at least its longest item.  The constants
+// are fits to 33^3 .. 257^3 launches of 12 shapes each (one MI355X): single
+// precision 950 + 300 x, double 950 + 390 x (480 x for more than six rays a
+// thread, whose state does not stay in registers).
+static double shape_cost(const rt_grid *g, const Variant &v, int n_lambda, int n_dirs, double sum_m, double max_m)
+{
+    const double waves = v.nthr / 64, nz = g->geo.Nz;
+    const double items = (double)n_lambda * n_dirs * v.nb;
+    const double per_cu = std::ceil(std::min((double)v.n_wg, items) / g->n_cu);
+    const double conc = std::min(items, std::min((double)v.n_wg, per_cu * g->n_cu));
+    const double x = std::max(std::ceil(waves / 4.0) * v.R, per_cu * waves * v.R / 4.0);
+    double c = v.dbl ? (v.R > 6 ? 450.0 : 370.0) : v.band ? 270.0 : 290.0;
+    // a wavelength's padded field beyond the 256 MB Infinity Cache: the HBM latency
+    // shows at ten rays a thread and more, whose registers hold few pairs in
+    // flight (257^3 x 512: 768 x 10 168 ms, 768 x 8 156, 1024 x 4 152)
+    if (!v.dbl && v.R >= 10 && 32.0 * (double)g->n_vox > 256e6) c *= 1.3;
+    if (v.wj && v.wl) c *= 1.25;
+    else if (v.wl) c *= 0.8;
+    const bool wide = v.band && !v.dbl && !(v.wj && v.wl);
+    const double words = (v.band ? v.tile_words / (wide ? 2.0 : 1.0) : (double)g->geo.Nx * g->geo.Ny) *
+                         ((v.wj ? 1 : 0) + (v.wl ? 1 : 0));
+    const double group = !v.band ? 4.0 : !wide ? 4.0 : v.R >= 8 && v.lb <= 768 ? 18.0 : 8.0;
+    const double per_thr = std::ceil(words / v.nthr);
+    const bool reads = items > conc;  // a slot's first item only stores
+    const double flush = 300.0 + (reads ? 2500.0 * std::ceil(per_thr / group) : 0.0) + 40.0 * per_thr;
+    const double visit = 950.0 + c * x;
+    const double longest = max_m * visit + nz * flush;
+    const double mean = (sum_m * visit + n_dirs * nz * flush) * n_lambda * v.nb / conc;
+    // partial sums: written and read once at about 4 TB/s (2.3 GHz cycles)
+    const double slots = conc * (double)g->n_vox * (v.dbl ? 8 : 4) * ((v.wj ? 1 : 0) + (v.wl ? 1 : 0));
+    return std::max(longest, mean + 0.25 * longest) + 2.0 * slots / 1740.0;
+}
+
+static Variant estimate_variant(rt_grid *g, bool dbl, bool wj, bool wl, int n_lambda,
+                                const std::vector<int32_t> *subset)
+{
+    const Variant &base = variant(g, dbl, wj, wl);
+    if (g->sphere || !base.ok || n_lambda < 1) return base;
+    double sum_m = 0.0, max_m = 0.0;
+    const int n_dirs = subset ? (int)subset->size() : g->n_dir;
+    for (int i = 0; i < n_dirs; ++i) {
+        const double m = g->geo.dirs[subset ? (*subset)[i] : i].M;
+        sum_m += m;
+        max_m = std::max(max_m, m);
+    }
+    // small batches run the shape of a single wavelength, so that they give its
+    // results bit for bit
+    const int n_item = n_lambda * n_dirs;
+    const int n_eff = n_item < 2 * g->n_cu ? 1 : n_lambda;
+    char key[96];
+    snprintf(key, sizeof key, "%d%d%d/%d/%d/%.0f/%.0f", dbl, wj, wl, n_eff, n_dirs, sum_m, max_m);
+    auto it = g->picks.find(key);
+    if (it != g->picks.end()) return it->second;
+    if (g->picks.size() > 256) g->picks.clear();
+    // no more workgroups than items, and more partial sums than the fewest-bundle
+    // shape has only while they stay below a gigabyte
+    const double slot_bytes = (double)g->n_vox * (dbl ? 8 : 4) * ((wj ? 1 : 0) + (wl ? 1 : 0));
+    const int64_t most = std::max<int64_t>(base.n_wg, (int64_t)(1e9 / slot_bytes));
+    const int64_t items = std::max(n_item, 2 * g->n_cu);
+    auto trim = [&](Variant &v) {
+        v.n_wg = (int)std::min<int64_t>(v.n_wg, std::min<int64_t>(most, items * v.nb));
+        v.n_wg -= v.n_wg % v.nb;
+        return v.n_wg >= v.nb;
+    };
+    // Whole layers of a few thousand voxels flush in a few words a thread, which
+    // bands cannot better; larger ones let both kinds compete (65 x 65, 512
+    // directions: 2.8 ms on bands, 3.6 on layers).
+    const bool bands = g->band || (int64_t)g->geo.Nx * g->geo.Ny >= 2048;
+    Variant best = base;
+    double best_cost = base.spill ? 1e300 : shape_cost(g, base, n_eff, n_dirs, sum_m, max_m);
+    const FsShape *sh = nullptr;
+    const int n = fs_box_shapes(&sh);
+    for (int i = 0; i < n; ++i) {
+        if (!sh[i].full && !(wj && !wl)) continue;
+        if (sh[i].band ? !bands : g->band) continue;
+        int first = 0, tried = 0;
+        for (int nb = 1; nb <= std::min(32, g->geo.Nx * g->geo.Ny) && tried < 8; ++nb) {
+            if (sh[i].band && nb < 2) continue;
+            Variant v = make_variant(g, dbl, wj, wl, sh[i].lb, sh[i].R, sh[i].occ, sh[i].band, false, nb);
+            if (v.nthr == 0) continue;  // the bundle does not fit the shape
+            if (!first) first = nb;
+            ++tried;
+            if (!v.ok || !trim(v)) continue;
+            const double cost = shape_cost(g, v, n_eff, n_dirs, sum_m, max_m);
+            // a few per cent are within the estimate's error: the earlier shape stays
+            if (cost < 0.97 * best_cost) {
+                best = v;
+                best_cost = cost;
+            }
+        }
+    }
+    g->picks.emplace(key, best);
+    return best;
+}
+
+Variant pick_variant(rt_grid *g, bool dbl, bool wj, bool wl, int n_lambda, const std::vector<int32_t> *subset)
+{
+    if (wj && !wl && g->fixed[dbl]) return g->fixed_var[dbl];
+    return estimate_variant(g, dbl, wj, wl, n_lambda, subset);
+}
+
 // Rays swept by the workgroups of bundle b of a launch.
 static int64_t bundle_ray_count(const rt_grid *g, const Variant *v, int b)
 {
@@ -167,7 +275,9 @@ rt_status get_schedule(rt_grid *g, int n_wg, const std::vector<int32_t> &lambdas
                 ds->points += (int64_t)g->geo.dirs[sc.items[k].dir].M * nr;
         }
     }
+    // workgroups past the last one with work are not launched
     ds->n_wg = sc.n_wg;
+    while (ds->n_wg > 1 && sc.wg_begin[ds->n_wg - 1] == sc.wg_begin[ds->n_wg]) --ds->n_wg;
     ds->n_slots = sc.n_slots;
     ds->n_batch = (int)lambdas.size();
     auto up = [](DevBuf &b, const void *src, size_t n) -> hipError_t {
@@ -361,8 +471,20 @@ rt_status run_fs(rt_grid *g, bool dbl, bool wj, bool wl, const std::vector<int32
                         const void *fld, const void *I_bc, DevBuf &partJ, DevBuf &partL, DevSchedule **sched_out,
                         hipStream_t st, const std::vector<int32_t> *subset)
 {
-    return run_fs_with(g, variant(g, dbl, wj, wl), lambdas, fld, I_bc, partJ, partL, sched_out, st, subset);
+    const Variant v = pick_variant(g, dbl, wj, wl, (int)lambdas.size(), subset);
+    rt_status rs = run_fs_with(g, v, lambdas, fld, I_bc, partJ, partL, sched_out, st, subset);
+    const Variant &base = base_variant(g, dbl, wj, wl);
+    if (rs == RT_E_NOMEM && v.n_wg > base.n_wg)  // its partial sums do not fit: the shape with the fewest
+        rs = run_fs_with(g, base, lambdas, fld, I_bc, partJ, partL, sched_out, st, subset);
+    return rs;
 }
+// The J-only shape of this precision is v from now on.
+static void fix_variant(rt_grid *g, const Variant &v)
+{
+    g->fixed_var[v.dbl] = v;
+    g->fixed[v.dbl] = true;
+}
+
 extern "C" {
 static rt_status autotune(rt_grid *g, int32_t n_lambda, const void *chi, const void *S,
                          const std::vector<int32_t> *subset, int32_t *threads_out, int32_t *rays_out, void *stream)
@@ -387,7 +509,9 @@ static rt_status autotune(rt_grid *g, int32_t n_lambda, const void *chi, const v
     for (int i = 0; i < n_lambda; ++i) lams[i] = i;
     const FsShape *sh = nullptr;
     const int n = fs_box_shapes(&sh);
-    Variant best = variant(g, dbl, true, false);
+    // the grid's default shape competes with the compiled list
+    const Variant by_estimate = estimate_variant(g, dbl, true, false, g->desc.n_lambda_max, nullptr);
+    Variant best = by_estimate;
     float best_ms = 1e30f;
     hipEvent_t e0, e1;
     HIPCHK(hipEventCreate(&e0));
@@ -395,11 +519,12 @@ static rt_status autotune(rt_grid *g, int32_t n_lambda, const void *chi, const v
     const bool prof = g->prof;
     g->prof = false;
     rt_status rs = RT_OK;
-    for (int i = 0; i < n && rs == RT_OK; ++i) {
+    for (int i = -1; i < n && rs == RT_OK; ++i) {
         // band tiles compete on every grid (their flush covers only the rows a
         // bundle reaches); layer tiles wherever they fit
-        if (!g->layer_ok && !sh[i].band) continue;
-        const Variant v = make_variant(g, dbl, true, false, sh[i].lb, sh[i].R, sh[i].occ, sh[i].band, false);
+        if (i >= 0 && !g->layer_ok && !sh[i].band) continue;
+        const Variant v = i < 0 ? by_estimate
+                                : make_variant(g, dbl, true, false, sh[i].lb, sh[i].R, sh[i].occ, sh[i].band, false);
         if (!v.ok) continue;
         DevSchedule *sc = nullptr;
         DevBuf &pJ = dbl ? g->partJ64 : g->partJ;
@@ -421,8 +546,7 @@ static rt_status autotune(rt_grid *g, int32_t n_lambda, const void *chi, const v
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     if (rs != RT_OK) return rs;
-    variant(g, dbl, true, false) = best;
-    g->tuned = true;
+    fix_variant(g, best);
     if (threads_out) *threads_out = best.lb;
     if (rays_out) *rays_out = best.R;
     return RT_OK;
@@ -452,6 +576,12 @@ static rt_status set_shape(rt_grid *g, bool dbl, int32_t threads, int32_t rays, 
 {
     const FsShape *sh = nullptr;
     const int n = fs_box_shapes(&sh);
+    // the grid's default shape, whose bundle count may be its own (rt_autotune can keep it)
+    const Variant dflt = estimate_variant(g, dbl, true, false, g->desc.n_lambda_max, nullptr);
+    if (dflt.ok && dflt.lb == threads && dflt.R == rays && dflt.band == (band >= 0 ? band != 0 : g->band)) {
+        fix_variant(g, dflt);
+        return RT_OK;
+    }
     for (int pass = 0; pass < 2; ++pass)  // the grid's own tile kind first when band < 0
         for (int i = 0; i < n; ++i) {
             if (sh[i].lb != threads || sh[i].R != rays) continue;
@@ -459,7 +589,7 @@ static rt_status set_shape(rt_grid *g, bool dbl, int32_t threads, int32_t rays, 
             if (!g->layer_ok && !sh[i].band) continue;
             const Variant v = make_variant(g, dbl, true, false, threads, rays, sh[i].occ, sh[i].band, true);
             if (!v.ok) continue;
-            variant(g, dbl, true, false) = v;
+            fix_variant(g, v);
             return RT_OK;
         }
     return fail(RT_E_INVALID, "no compiled launch shape %d threads x %d rays%s that holds the rays of a direction",
@@ -470,18 +600,14 @@ rt_status rt_set_launch_shape_tiles(rt_grid_t g, int32_t threads, int32_t rays, 
 {
     if (!g) return fail(RT_E_INVALID, "grid is NULL");
     if (g->sphere) return fail(RT_E_UNSUPPORTED, "launch shapes apply to the box sweep only");
-    rt_status rs = set_shape(g, g->dbl, threads, rays, band ? 1 : 0);
-    if (rs == RT_OK) g->tuned = true;
-    return rs;
+    return set_shape(g, g->dbl, threads, rays, band ? 1 : 0);
 }
 
 rt_status rt_set_launch_shape(rt_grid_t g, int32_t threads, int32_t rays)
 {
     if (!g) return fail(RT_E_INVALID, "grid is NULL");
     if (g->sphere) return fail(RT_E_UNSUPPORTED, "launch shapes apply to the box sweep only");
-    rt_status rs = set_shape(g, g->dbl, threads, rays, -1);
-    if (rs == RT_OK) g->tuned = true;
-    return rs;
+    return set_shape(g, g->dbl, threads, rays, -1);
 }
 
 rt_status rt_set_anchor_shape(rt_grid_t g, int32_t threads, int32_t rays, int32_t band)
@@ -495,7 +621,7 @@ rt_status rt_launch_shape(rt_grid_t g, int32_t *threads, int32_t *rays, int32_t 
 {
     if (!g) return fail(RT_E_INVALID, "grid is NULL");
     if (g->sphere) return fail(RT_E_UNSUPPORTED, "launch shapes apply to the box sweep only");
-    const Variant &v = variant(g, g->dbl, true, false);
+    const Variant v = pick_variant(g, g->dbl, true, false, g->desc.n_lambda_max);
     if (threads) *threads = v.lb;
     if (rays) *rays = v.R;
     if (bundles) *bundles = v.nb;

@@ -130,7 +130,7 @@ extern "C" rt_status rt_formal_solution_noalloc(rt_grid_t g, int32_t n_lambda, c
     // validate every sweep before anything is enqueued
     std::vector<NoAllocPass> passes(outs.size());
     for (size_t i = 0; i < outs.size(); ++i) {
-        const Variant &v = variant(g, dbl, outs[i].wj, outs[i].wl);
+        const Variant &v = base_variant(g, dbl, outs[i].wj, outs[i].wl);
         if (!v.ok) return fail(RT_E_UNSUPPORTED, "no kernel configuration fits this grid");
         rt_status rs = plan_pass(g, v, n_lambda, fld_bytes, (outs[i].wj ? 1 : 0) + (outs[i].wl ? 1 : 0), passes[i]);
         if (rs != RT_OK) return rs;

@@ -30,8 +30,9 @@
 // that start at yb + (lowest template row of the layer); the visit table
 // carries each visit's row relative to that lowest row.  The tile index is
 // then (origin row - yb + relative row) * Nx + x, and the flush maps tile
-// word i to layer word (base * Nx + i) mod NxNy.  The workgroup clears its
-// partial slot when it opens it, because a band touches only part of it.
+// word i to layer word (base * Nx + i) mod NxNy.  A band covers only part of
+// a layer, so the first item of a slot also stores zeros to the rest of each
+// layer that it flushes.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -47,15 +48,20 @@ namespace rt3d {
 // per-ray byte offset sits in a VGPR, the per-visit byte offset in an SGPR,
 // so there is no per-lane address arithmetic
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t field_rsrc(const void *base, uint32_t bytes)
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t field_rsrc(const void *base, uint32_t bytes, int stride)
 {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), (short)0, (int)bytes, 0x00020000);
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), (short)stride, (int)bytes, 0x00020000);
 }
 
 template <typename T>
 struct Pair {
     T chi, S;
 };
+
+// Structured buffer load: byte address base + index * stride + soff.
+typedef int v2i __attribute__((ext_vector_type(2)));
+__device__ v2i struct_load_b64(__amdgpu_buffer_rsrc_t r, int index, int voff, int soff,
+                               int aux) __asm("llvm.amdgcn.struct.ptr.buffer.load.v2i32");
 
 template <typename T>
 __device__ __forceinline__ Pair<T> ld_pair(__amdgpu_buffer_rsrc_t r, int voff, int soff);
@@ -96,6 +102,14 @@ __device__ __forceinline__ float uniform(float v)
 }
 __device__ __forceinline__ double uniform(double v) { return v; }
 
+// A double loaded from the same address by every lane, in scalar registers (no
+// instruction where the compiler already has it there).
+__device__ __forceinline__ double scalar(double v)
+{
+    return __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(v)),
+                            __builtin_amdgcn_readfirstlane(__double2loint(v)));
+}
+
 template <typename T, int LB, int R, bool WJ, bool WL, bool PARA, int OCC, bool BAND>
 __global__ void __launch_bounds__(LB) __attribute__((amdgpu_waves_per_eu(OCC * LB / 256 > 0 ? OCC * LB / 256 : 1)))
 fs_box_kernel(FsBoxArgs a)
@@ -110,6 +124,40 @@ fs_box_kernel(FsBoxArgs a)
     T *tJ = reinterpret_cast<T *>(smem_raw);
     T *tL = tJ + (WJ ? TW + nthr : 0);
     constexpr int ES = 2 * (int)sizeof(T);  // bytes per (chi, S) pair
+    // Single-precision band tiles of single-output sweeps are two layer rows
+    // wide, like the padded field: a ray's column x0 + dx (below 2 Nx) then
+    // needs no wrap, and the layer flush adds word x + Nx of a tile row to
+    // column x.  (Two outputs at twice the width would leave room for fewer
+    // rows per band.)
+    constexpr bool WIDE = BAND && sizeof(T) == 4 && !(WJ && WL);
+    // What is kept in registers besides the intensities and addresses, by what
+    // the shape's waves per SIMD leave beside about kTmp temporaries of a point
+    // (set so that no kernel spills that would not otherwise):
+    //   CARRY  the state carried along a ray from visit to visit (see below)
+    //   DEPTH  of it, the half depth of the current point (else its opacity)
+    //   PRE    field pairs in flight, read this many rays ahead, past the barrier
+    //          into the next visit (at most all of a thread's rays); 0: the next
+    //          ray's pair, within the visit
+    //   TPRE   a ray's tile words are read while the ray before it is computed,
+    //          and the visit table two visits ahead
+    constexpr int kWaves = OCC * LB / 256 > 0 ? OCC * LB / 256 : 1;
+    constexpr int kRegs = kWaves > 2 ? (512 / kWaves) & ~7 : 256;
+    constexpr int kWords = (int)sizeof(T) / 4;
+    constexpr int kTmp = (sizeof(T) == 8 ? 84 : 74) + (WL ? 10 : 0);
+    constexpr int kAddr = WIDE ? 1 : 2, kPara = WL && PARA ? kWords : 0;
+    constexpr int kState = kAddr + 3 + (WJ ? 3 * kWords : 0) + kPara;
+    constexpr bool CARRY = sizeof(T) == 4 || R * (kState + 1) + kTmp <= kRegs;
+    constexpr bool DEPTH = CARRY && R * (kState + 1) + kTmp <= kRegs;
+    constexpr int kUsed = CARRY ? R * (kState + DEPTH) + kTmp : R * (kAddr + (WJ ? kWords : 0) + kPara) + kTmp + 16;
+    constexpr int kFree = kRegs > kUsed ? (kRegs - kUsed) / (2 * kWords) : 0;
+    constexpr int PRE = !CARRY ? 0 : kFree < R ? kFree : R;
+    constexpr bool TPRE = kUsed + 2 <= kRegs;
+    // Words of a layer flush per thread whose slot reads are issued together; a
+    // visit's temporaries are free by then.  Eighteen take the 98 rows of 129
+    // words of a 768-thread band in one go, where three groups of eight waited
+    // three times for memory at every layer.
+    constexpr int FLUSH = WIDE && R >= 8 && kRegs >= 160 ? 18 : 8;
+    constexpr bool kPrio = R >= 10 && R <= 12;  // long visits of three waves a SIMD; neutral or slower elsewhere
 
     for (int i = tid; i < TW + nthr; i += nthr) {
         if (WJ) tJ[i] = T(0);
@@ -137,26 +185,22 @@ fs_box_kernel(FsBoxArgs a)
         q_lo = bundle * a.bundle_rays;
         q_n = min(a.bundle_rays, NxNy - q_lo);
     }
-    // Two constants per ray j of this thread: vb[j], the byte offset of its
-    // origin in the padded field (the per-visit part of the address is
-    // scalar), and tw[j] = x0 << 19 | (tile word of its origin) * sizeof(T):
-    // its high field decides the x wrap of a visit by one unsigned comparison
-    // with a scalar, its low field (< 2^19: LDS bytes) is the tile address
-    // before the visit's scalar offset.  Rows are relative to the bundle's
-    // first row yb for band tiles.  Only the last slot of a thread can be a
-    // padding slot (padj).
+    // Constants per ray j of this thread: vb[j], the byte offset of its origin
+    // in the padded field (the per-visit part of the address is scalar), and
+    // tw[j] = x0 << 19 | (tile word of its origin) * sizeof(T): its high field
+    // decides the x wrap of a visit by one unsigned comparison with a scalar,
+    // its low field (< 2^19: LDS bytes) is the tile address before the visit's
+    // scalar offset.  Wide tiles have the pitch of the padded field, so one
+    // number serves both: vb[j] is then the pair's index (structured loads
+    // scale it by the pair size) and the tile address is 4 vb[j] + offset, and
+    // tw is not kept.  Rows are relative to the bundle's first row yb for band
+    // tiles.  Only the last slot of a thread can be a padding slot (padj).
     const uint32_t row_bytes = (uint32_t)(2 * Nx * ES);
-    // Single-precision band tiles of single-output sweeps are two layer rows
-    // wide, like the padded field: a ray's column x0 + dx (below 2 Nx) then
-    // needs no wrap, and the layer flush adds word x + Nx of a tile row to
-    // column x.  (Two outputs at twice the width would leave room for fewer
-    // rows per band.)
-    constexpr bool WIDE = BAND && sizeof(T) == 4 && !(WJ && WL);
     const uint32_t tpitch = WIDE ? 2u * (uint32_t)Nx : (uint32_t)Nx;
     const int gshift = BAND ? (int)((uint32_t)yb * row_bytes) : 0;
     constexpr uint32_t kTileMask = (1u << 19) - 1u;
     int vb[R];
-    uint32_t tw[R];
+    uint32_t tw[WIDE ? 1 : R];
     bool padj = false;
 #pragma unroll
     for (int j = 0; j < R; ++j) {
@@ -167,8 +211,12 @@ fs_box_kernel(FsBoxArgs a)
         const int y0 = q / Nx;
         const int x0 = q - y0 * Nx;
         const uint32_t yr = (uint32_t)(y0 - yb);
-        vb[j] = (int)(yr * row_bytes + (uint32_t)x0 * ES);
-        tw[j] = ((uint32_t)x0 << 19) | ((yr * tpitch + (uint32_t)x0) * (uint32_t)sizeof(T));
+        if constexpr (WIDE) {
+            vb[j] = (int)(yr * tpitch + (uint32_t)x0);
+        } else {
+            vb[j] = (int)(yr * row_bytes + (uint32_t)x0 * ES);
+            tw[j] = ((uint32_t)x0 << 19) | ((yr * tpitch + (uint32_t)x0) * (uint32_t)sizeof(T));
+        }
         if (j == R - 1) padj = pad;
     }
     unsigned char *const tJb = reinterpret_cast<unsigned char *>(tJ);
@@ -184,8 +232,17 @@ fs_box_kernel(FsBoxArgs a)
         const WorkItem item = a.items[it];
         const int lam = item.lambda;
         const int d = item.dir;
-        const __amdgpu_buffer_rsrc_t rf =
-            field_rsrc(reinterpret_cast<const T *>(a.field) + 2 * (int64_t)lam * a.pad_stride, slice_bytes);
+        const __amdgpu_buffer_rsrc_t rf = field_rsrc(
+            reinterpret_cast<const T *>(a.field) + 2 * (int64_t)lam * a.pad_stride, slice_bytes, WIDE ? ES : 0);
+        // the (chi, S) pair of ray j at scalar byte offset g
+        auto field = [&](int j, int g) {
+            if constexpr (WIDE) {
+                const v2i v = struct_load_b64(rf, vb[j], 0, g, 0);
+                return Pair<T>{__int_as_float(v.x), __int_as_float(v.y)};
+            } else {
+                return ld_pair<T>(rf, vb[j], g);
+            }
+        };
         T *__restrict__ pJ = WJ ? reinterpret_cast<T *>(a.partJ) + (int64_t)item.slot * a.n_vox : nullptr;
         T *__restrict__ pL = WL ? reinterpret_cast<T *>(a.partL) + (int64_t)item.slot * a.n_vox : nullptr;
         const bool first = item.first != 0;
@@ -200,20 +257,19 @@ fs_box_kernel(FsBoxArgs a)
         const int32_t *__restrict__ brow = BAND ? a.brow + vbeg : nullptr;
         const int span = BAND ? a.dir_span[d] : 0;
 
-        if (BAND && first) {
-            // a band touches only part of the slot: clear all of it once
-            for (int64_t i = tid; i < a.n_vox; i += nthr) {
-                if (WJ) pJ[i] = T(0);
-                if (WL) pL[i] = T(0);
-            }
-            __syncthreads();
-        }
-
         T I[R];
         T gprev[R];
         int layer = down ? 0 : a.Nz - 1;
         const int dlayer = down ? 1 : -1;
 
+        // first item of a slot: zeros to the layer's words outside the band
+        auto clear_rest = [&](T *__restrict__ part, int64_t lo, uint32_t g0, int n) {
+            if (!first) return;
+            for (int i = n + tid; i < NxNy; i += nthr) {
+                const uint32_t gi = g0 + (uint32_t)i;
+                part[lo + min(gi, gi - (uint32_t)NxNy)] = T(0);
+            }
+        };
         // w, r: offsets word and relative row of the layer's last visit
         auto flush_layer = [&](uint32_t w, int r) {
             const int64_t lo = (int64_t)layer * NxNy;
@@ -226,49 +282,48 @@ fs_box_kernel(FsBoxArgs a)
                 if (WIDE) {
                     // output word i = row Nx + x takes tile words row 2Nx + x and
                     // row 2Nx + x + Nx; row and x advance without division.  A
-                    // single-output sweep (one tile, one slot); eight words of a
+                    // single-output sweep (one tile, one slot); FLUSH words of a
                     // thread at a time, their slot reads issued together
                     T *const tile = WJ ? tJ : tL;
                     T *__restrict__ const part = WJ ? pJ : pL;
                     int row = f_row0, x = f_x0;
-                    auto word = [&](int i, uint32_t &gi, int &t0) {
-                        gi = g0 + (uint32_t)i;
-                        gi = min(gi, gi - (uint32_t)NxNy);
-                        t0 = i + row * Nx;
-                        x += f_dx;
-                        row += f_drow;
-                        if (x >= Nx) {
-                            x -= Nx;
-                            ++row;
-                        }
+                    auto layer_word = [&](int i) {
+                        const uint32_t gi = g0 + (uint32_t)i;
+                        return min(gi, gi - (uint32_t)NxNy);
                     };
-                    constexpr int U = 8;
+                    constexpr int U = FLUSH;
                     for (int i = tid; i < n; i += U * nthr) {
-                        uint32_t gi[U];
-                        int t0[U];
                         T old[U];
                         // slots past the band end only the thread's last group
 #pragma unroll
                         for (int u = 0; u < U; ++u)
-                            if (i + u * nthr < n) word(i + u * nthr, gi[u], t0[u]);
+                            if (i + u * nthr < n) old[u] = first ? T(0) : part[lo + layer_word(i + u * nthr)];
 #pragma unroll
-                        for (int u = 0; u < U; ++u)
-                            if (i + u * nthr < n) old[u] = part[lo + gi[u]];
-#pragma unroll
-                        for (int u = 0; u < U; ++u)
-                            if (i + u * nthr < n) {
-                                const T v = tile[t0[u]] + tile[t0[u] + Nx];
-                                tile[t0[u]] = T(0);
-                                tile[t0[u] + Nx] = T(0);
-                                part[lo + gi[u]] = old[u] + v;
+                        for (int u = 0; u < U; ++u) {
+                            int k = i + u * nthr;
+                            asm("" : "+v"(k));  // form the address again instead of keeping it from the read
+                            if (k < n) {
+                                T *const t0 = tile + (k + row * Nx);
+                                const T v = t0[0] + t0[Nx];
+                                t0[0] = T(0);
+                                t0[Nx] = T(0);
+                                part[lo + layer_word(k)] = old[u] + v;
+                                x += f_dx;
+                                row += f_drow;
+                                if (x >= Nx) {
+                                    x -= Nx;
+                                    ++row;
+                                }
                             }
+                        }
                     }
+                    clear_rest(part, lo, g0, n);
                     layer += dlayer;
                     __syncthreads();
                     return;
                 }
-                // four words of a thread at a time, their slot reads issued together
-                constexpr int U = 4;
+                // some words of a thread at a time, their slot reads issued together
+                constexpr int U = FLUSH / 2;
                 for (int i = tid; i < n; i += U * nthr) {
                     uint32_t gi[U];
                     T oJ[U], oL[U];
@@ -280,8 +335,8 @@ fs_box_kernel(FsBoxArgs a)
 #pragma unroll
                     for (int u = 0; u < U; ++u)
                         if (i + u * nthr < n) {
-                            if (WJ) oJ[u] = pJ[lo + gi[u]];
-                            if (WL) oL[u] = pL[lo + gi[u]];
+                            if (WJ) oJ[u] = first ? T(0) : pJ[lo + gi[u]];
+                            if (WL) oL[u] = first ? T(0) : pL[lo + gi[u]];
                         }
 #pragma unroll
                     for (int u = 0; u < U; ++u) {
@@ -300,17 +355,33 @@ fs_box_kernel(FsBoxArgs a)
                         }
                     }
                 }
+                if (WJ) clear_rest(pJ, lo, g0, n);
+                if (WL) clear_rest(pL, lo, g0, n);
             } else {
-                for (int i = tid; i < NxNy; i += nthr) {
-                    if (WJ) {
-                        const T v = tJ[i];
-                        tJ[i] = T(0);
-                        pJ[lo + i] = first ? v : pJ[lo + i] + v;
-                    }
-                    if (WL) {
-                        const T v = tL[i];
-                        tL[i] = T(0);
-                        pL[lo + i] = first ? v : pL[lo + i] + v;
+                constexpr int U = 4;
+                for (int i = tid; i < NxNy; i += U * nthr) {
+                    T oJ[U], oL[U];
+#pragma unroll
+                    for (int u = 0; u < U; ++u)
+                        if (i + u * nthr < NxNy) {
+                            if (WJ) oJ[u] = first ? T(0) : pJ[lo + i + u * nthr];
+                            if (WL) oL[u] = first ? T(0) : pL[lo + i + u * nthr];
+                        }
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        const int k = i + u * nthr;
+                        if (k < NxNy) {
+                            if (WJ) {
+                                const T v = tJ[k];
+                                tJ[k] = T(0);
+                                pJ[lo + k] = oJ[u] + v;
+                            }
+                            if (WL) {
+                                const T v = tL[k];
+                                tL[k] = T(0);
+                                pL[lo + k] = oL[u] + v;
+                            }
+                        }
                     }
                 }
             }
@@ -331,6 +402,9 @@ fs_box_kernel(FsBoxArgs a)
             if (BAND) {
                 s.off = ((uint32_t)r * tpitch + dx) * (uint32_t)sizeof(T);
                 s.thy = 0;
+                // opaque, so that 4 vb + off stays one shift-and-add per ray
+                s.off = (uint32_t)__builtin_amdgcn_readfirstlane((int)s.off);
+                asm("" : "+s"(s.off));
             } else {
                 const uint32_t dy = (w >> kOffBits) & kOffMask;
                 s.off = (dy * (uint32_t)Nx + dx) * (uint32_t)sizeof(T);
@@ -342,66 +416,72 @@ fs_box_kernel(FsBoxArgs a)
         // this thread's own word past the tile, so no two lanes ever update
         // the same word in one step
         auto tile_addr = [&](int j, const TileStep &s) {
-            const uint32_t base = tw[j] & kTileMask;
-            uint32_t a4 = base + s.off;
-            if (!WIDE) a4 -= tw[j] >= s.thx ? (uint32_t)Nx * (uint32_t)sizeof(T) : 0u;
-            if (!BAND) a4 -= base >= s.thy ? (uint32_t)NxNy * (uint32_t)sizeof(T) : 0u;
+            uint32_t a4;
+            if constexpr (WIDE) {
+                a4 = ((uint32_t)vb[j] << 2) + s.off;
+            } else {
+                const uint32_t base = tw[j] & kTileMask;
+                a4 = base + s.off;
+                a4 -= tw[j] >= s.thx ? (uint32_t)Nx * (uint32_t)sizeof(T) : 0u;
+                if (!BAND) a4 -= base >= s.thy ? (uint32_t)NxNy * (uint32_t)sizeof(T) : 0u;
+            }
             return (j == R - 1 && padj) ? pad_addr : a4;
         };
         // the visit weight, zero for a padding slot
         auto ray_weight = [&](int j, T cw) { return (j == R - 1 && padj) ? T(0) : cw; };
-        auto tile_add = [&](unsigned char *tile, uint32_t addr, T v) {
-            T *w = reinterpret_cast<T *>(tile + addr);
-            *w += v;
-        };
+        auto tile_word = [&](unsigned char *tile, uint32_t addr) -> T & { return *reinterpret_cast<T *>(tile + addr); };
 
-        // Single-precision sweeps carry along each ray, from one visit to the
-        // next, the sources of the previous and current points (Sp, Sc), the
-        // opacity of the current point (Xc) and the optical step from the
-        // previous point to the current one (Dc): each visit then reads only
-        // the next point's (chi, S) pair and forms one optical depth.  Double
-        // sweeps (twice the registers per value) read the previous, current
-        // and next pairs at every visit instead.
-        constexpr bool CARRY = sizeof(T) == 4;
-        T Sp[CARRY ? R : 1], Sc[CARRY ? R : 1], Xc[CARRY ? R : 1];
-        double Dc[CARRY ? R : 1];
+        // Carried along each ray from one visit to the next: the sources of the
+        // previous and current points (Sp, Sc), the half depth of the current
+        // point (tc; its opacity Xc where registers are short) and the optical
+        // step from the previous point to the current one (Dc); each visit then
+        // reads only the next point's (chi, S) pair.  Double sweeps with many rays per thread have no
+        // registers for it and read the previous, current and next pairs at
+        // every visit instead.
+        T Sp[CARRY ? R : 1], Sc[CARRY ? R : 1];
+        double tc[DEPTH ? R : 1], Dc[CARRY ? R : 1];
+        T Xc[CARRY && !DEPTH ? R : 1];
+        Pair<T> pf[PRE > 0 ? PRE : 1];  // queue of downwind pairs in flight
         int g_p = 0;
         double s_p = 0.0;
 
+        // The visit table is read ahead of its use, so that no wave waits for
+        // it right after a barrier: visit c is the current one, n the next, and
+        // g_2, s_2, w_2, r_2 (g_3) belong to the visit(s) after it; past the
+        // ray's end they repeat the last visit.  Path lengths are halved.
+        const int i1 = min(1, M - 1), i2 = min(2, M - 1), i3 = min(3, M - 1);
+        int g_c = goff[0] * ES + gshift, g_n = goff[i1] * ES + gshift, g_2 = goff[i2] * ES + gshift;
+        int g_3 = PRE > 0 ? goff[i3] * ES + gshift : 0;
+        double s_c = scalar(sv[0]), s_n = scalar(sv[i1]), s_2 = scalar(sv[i2]);
+        uint32_t w_c = dxy[0], w_n = dxy[i1], w_2 = dxy[i2];
+        int r_c = BAND ? brow[0] : 0, r_n = BAND ? brow[i1] : 0, r_2 = BAND ? brow[i2] : 0;
         // first point: entry half-segment with constant S; the second point's
         // pair is read too (the first optical step between points needs it)
-        int g_c = goff[0] * ES + gshift;
-        double s_c = sv[0];
-        uint32_t w_c = dxy[0];
-        int r_c = BAND ? brow[0] : 0;
-        int g_n = g_c;
-        double s_n = s_c;
-        if (M > 1) {
-            g_n = goff[1] * ES + gshift;
-            s_n = sv[1];
-        }
         {
-            const T cw = T(wmu * s_c);
+            const T cw = T(wmu * (2.0 * s_c));
             const TileStep ts = tile_step(w_c, r_c);
 #pragma unroll
             for (int j = 0; j < R; ++j) {
                 gprev[j] = T(0);
-                const Pair<T> f0 = ld_pair<T>(rf, vb[j], g_c);
-                const double t0 = seg_depth((double)f0.chi, s_c);
+                const Pair<T> f0 = field(j, g_c);
+                const double t0 = half_depth((double)f0.chi, s_c);
                 T ex, e0;
-                entry_weights<T>(0.5 * t0, ex, e0);
+                entry_weights<T>(t0, ex, e0);
                 I[j] = WJ ? Ibc * ex + f0.S * e0 : T(0);
                 const uint32_t ad = tile_addr(j, ts);
                 const T cj = ray_weight(j, cw);
-                if (WJ) tile_add(tJb, ad, cj * I[j]);
-                if (WL) tile_add(tLb, ad, cj * e0);
+                if (WJ) tile_word(tJb, ad) += cj * I[j];
+                if (WL) tile_word(tLb, ad) += cj * e0;
                 if constexpr (CARRY) {
-                    const Pair<T> f1 = ld_pair<T>(rf, vb[j], g_n);
+                    const Pair<T> f1 = field(j, g_n);
                     Sp[j] = f0.S;
                     Sc[j] = f1.S;
-                    Xc[j] = f1.chi;
-                    Dc[j] = step_depth(t0, seg_depth((double)f1.chi, s_n));
+                    const double t1 = half_depth((double)f1.chi, s_n);
+                    Dc[j] = step_of(t0, t1);
+                    if constexpr (DEPTH) tc[j] = t1;
+                    else Xc[j] = f1.chi;
                 }
+                if (j < PRE) pf[j] = field(j, g_2);
             }
             __syncthreads();
             if (w_c & kLayerEnd) flush_layer(w_c, r_c);
@@ -411,35 +491,68 @@ fs_box_kernel(FsBoxArgs a)
         // has no downwind neighbour
         auto step = [&](auto last_tag) {
             constexpr bool LAST = decltype(last_tag)::value;
-            const T cw = uniform(T(wmu * s_c));
+            const T cw = uniform(T(wmu * (2.0 * s_c)));
             const TileStep ts = tile_step(w_c, r_c);
-            // software pipeline over the rays of this thread: the loads of
-            // ray j+1 are in flight while ray j is computed
+            // software pipeline over the rays of this thread and on into the
+            // next visit: the loads of the next PRE rays are in flight while a
+            // ray is computed, so that no wave waits for memory right after the
+            // barrier, and a field larger than the caches (257^3) hides its HBM
+            // latency (one pair in flight: 174 ms at ten rays a thread, 168
+            // ms with three)
             const Pair<T> zero{T(0), T(0)};
-            Pair<T> nn = LAST ? zero : ld_pair<T>(rf, vb[0], g_n);
-            Pair<T> np = CARRY ? zero : ld_pair<T>(rf, vb[0], g_p);
-            Pair<T> nc = CARRY ? zero : ld_pair<T>(rf, vb[0], g_c);
+            Pair<T> nn = LAST || PRE > 0 ? zero : field(0, g_n);
+            Pair<T> np = CARRY ? zero : field(0, g_p);
+            Pair<T> nc = CARRY ? zero : field(0, g_c);
+            // so are its tile words: at one visit no two rays share a word
+            uint32_t na = tile_addr(0, ts);
+            T nJ = TPRE && WJ ? tile_word(tJb, na) : T(0), nL = TPRE && WL ? tile_word(tLb, na) : T(0);
 #pragma unroll
             for (int j = 0; j < R; ++j) {
-                const Pair<T> fn = nn, fp = np, fc = nc;
+                // a wave that is behind its neighbours goes first, so that the
+                // waves of a SIMD reach the barrier together instead of the last
+                // one running alone
+                if (kPrio) {
+                    if (j == 0) __builtin_amdgcn_s_setprio(3);
+                    else if (j == (R + 3) / 4) __builtin_amdgcn_s_setprio(2);
+                    else if (j == (2 * R + 3) / 4) __builtin_amdgcn_s_setprio(1);
+                    else if (j == (3 * R + 3) / 4) __builtin_amdgcn_s_setprio(0);
+                }
+                Pair<T> fn = nn;
+                const Pair<T> fp = np, fc = nc;
+                if constexpr (PRE > 0 && !LAST) {
+                    fn = pf[0];
+#pragma unroll
+                    for (int k = 0; k + 1 < PRE; ++k) pf[k] = pf[k + 1];
+                    pf[PRE - 1] = j + PRE < R ? field(j + PRE < R ? j + PRE : 0, g_n) : field(j + PRE < R ? 0 : j + PRE - R, g_2);
+                }
+                const uint32_t ad = TPRE ? na : tile_addr(j, ts);
+                T oJ = nJ, oL = nL;
                 if (j + 1 < R) {
-                    if (!LAST) nn = ld_pair<T>(rf, vb[j + 1], g_n);
+                    if (TPRE) {
+                        na = tile_addr(j + 1, ts);
+                        if (WJ) nJ = tile_word(tJb, na);
+                        if (WL) nL = tile_word(tLb, na);
+                    }
+                    if (!LAST && PRE == 0) nn = field(j + 1, g_n);
                     if (!CARRY) {
-                        np = ld_pair<T>(rf, vb[j + 1], g_p);
-                        nc = ld_pair<T>(rf, vb[j + 1], g_c);
+                        np = field(j + 1, g_p);
+                        nc = field(j + 1, g_c);
                     }
                 }
-                double D, Dp = 0.0;
+                double D, Dp = 0.0, tn = 0.0;
                 T S_prev, S_cur;
                 if constexpr (CARRY) {
                     D = Dc[j];
                     S_prev = Sp[j];
                     S_cur = Sc[j];
-                    if (!LAST) Dp = step_depth(seg_depth((double)Xc[j], s_c), seg_depth((double)fn.chi, s_n));
+                    if (!LAST) {
+                        tn = half_depth((double)fn.chi, s_n);
+                        Dp = step_of(DEPTH ? tc[DEPTH ? j : 0] : half_depth((double)Xc[DEPTH ? 0 : j], s_c), tn);
+                    }
                 } else {
-                    const double tc = seg_depth((double)fc.chi, s_c);
-                    D = step_depth(seg_depth((double)fp.chi, s_p), tc);
-                    if (!LAST) Dp = step_depth(tc, seg_depth((double)fn.chi, s_n));
+                    const double hc = half_depth((double)fc.chi, s_c);
+                    D = step_of(half_depth((double)fp.chi, s_p), hc);
+                    if (!LAST) Dp = step_of(hc, half_depth((double)fn.chi, s_n));
                     S_prev = fp.S;
                     S_cur = fc.S;
                 }
@@ -452,9 +565,10 @@ fs_box_kernel(FsBoxArgs a)
                     if (!LAST) Ij = fma_t(pw.g, fn.S, Ij);
                     I[j] = Ij;
                 }
-                const uint32_t ad = tile_addr(j, ts);
                 const T cj = ray_weight(j, cw);
-                if (WJ) tile_add(tJb, ad, cj * I[j]);
+                if (!TPRE && WJ) oJ = tile_word(tJb, ad);
+                if (!TPRE && WL) oL = tile_word(tLb, ad);
+                if (WJ) tile_word(tJb, ad) = oJ + cj * I[j];
                 if (WL) {
                     T dloc;
                     if (PARA) {
@@ -463,12 +577,13 @@ fs_box_kernel(FsBoxArgs a)
                     } else {
                         dloc = pw.dlin;
                     }
-                    tile_add(tLb, ad, cj * dloc);
+                    tile_word(tLb, ad) = oL + cj * dloc;
                 }
                 if constexpr (CARRY && !LAST) {
                     Sp[j] = Sc[j];
                     Sc[j] = fn.S;
-                    Xc[j] = fn.chi;
+                    if constexpr (DEPTH) tc[j] = tn;
+                    else Xc[j] = fn.chi;
                     Dc[j] = Dp;
                 }
             }
@@ -476,27 +591,45 @@ fs_box_kernel(FsBoxArgs a)
             if (w_c & kLayerEnd) flush_layer(w_c, r_c);
         };
 
-        // template entries of the current visit (c) and the next one (n); the
-        // final point is taken after the loop, so that the loop body has a
+        // the final point is taken after the loop, so that the loop body has a
         // single path (no merge of the carried per-ray state)
-        for (int m = 1; m + 1 < M; ++m) {
+        auto advance = [&](int m) {
             g_p = g_c;
             s_p = s_c;
             g_c = g_n;
             s_c = s_n;
-            w_c = dxy[m];
-            if (BAND) r_c = brow[m];
-            g_n = goff[m + 1] * ES + gshift;
-            s_n = sv[m + 1];
+            w_c = w_n;
+            r_c = r_n;
+            const int m2 = min(m + 2, M - 1);
+            if constexpr (!TPRE) {
+                const int m1 = min(m + 1, M - 1);
+                g_n = goff[m1] * ES + gshift;
+                s_n = scalar(sv[m1]);
+                w_n = dxy[m1];
+                if (BAND) r_n = brow[m1];
+                if (PRE > 0) g_2 = goff[m2] * ES + gshift;
+                return;
+            }
+            g_n = g_2;
+            s_n = s_2;
+            w_n = w_2;
+            r_n = r_2;
+            s_2 = scalar(sv[m2]);
+            w_2 = dxy[m2];
+            if (BAND) r_2 = brow[m2];
+            if (PRE > 0) {
+                g_2 = g_3;
+                g_3 = goff[min(m + 3, M - 1)] * ES + gshift;
+            } else {
+                g_2 = goff[m2] * ES + gshift;
+            }
+        };
+        for (int m = 1; m + 1 < M; ++m) {
+            advance(m);
             step(std::false_type{});
         }
         if (M > 1) {
-            g_p = g_c;
-            s_p = s_c;
-            g_c = g_n;
-            s_c = s_n;
-            w_c = dxy[M - 1];
-            if (BAND) r_c = brow[M - 1];
+            advance(M - 1);
             step(std::true_type{});
         }
     }
@@ -560,7 +693,9 @@ static hipError_t launch_one(const FsBoxArgs &a, int n_wg, int nthr, size_t lds,
 }
 
 // Resident workgroups per CU; negative when the compiled kernel spills
-// registers to scratch memory (the host then prefers other shapes).
+// registers to scratch memory (the host then prefers other shapes).  Up to five
+// words are tolerated: they are set-up values parked once per work item, and
+// such shapes time like their neighbours without any.
 template <typename T, int LB, int R, bool WJ, bool WL, bool PARA, int OCC, bool BAND>
 static int occ_one(int nthr, size_t lds)
 {
@@ -569,7 +704,7 @@ static int occ_one(int nthr, size_t lds)
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k, nthr, lds) != hipSuccess) return 0;
     hipFuncAttributes attr{};
     if (hipFuncGetAttributes(&attr, (const void *)k) != hipSuccess) return 0;
-    return attr.localSizeBytes > 0 ? -n : n;
+    return attr.localSizeBytes > 20 ? -n : n;
 }
 
 template <typename T, int LB, int R, int OCC, bool BAND>

@@ -15,7 +15,7 @@ struct FsBoxArgs {
     // visit table (directions back to back) and per-direction data
     const int32_t *goff;
     const uint32_t *dxy;
-    const double *s;
+    const double *s;  // half path lengths
     const int64_t *dir_vbegin;
     const int32_t *dir_M;
     const double *dir_wmu;  // w_d |mu_d|

@@ -12,14 +12,20 @@
 
 namespace rt3d {
 
-// a b + c by the three-address v_fma_f64 with every operand in a vector
-// register: the compiler's two-address v_fmac form would first copy a
-// constant addend (a polynomial coefficient held in a register) into the
-// destination at every use.
-__device__ __forceinline__ double fma3(double a, double b, double c)
+// c - a b with a constant c (a polynomial coefficient).  The negated factor
+// keeps the compiler on the three-address v_fma_f64, which reads c from a
+// scalar register pair: the two-address v_fmac form it prefers for a plain
+// a b + c would copy c into the destination at every use, and take 14 vector
+// registers for the coefficients.  The polynomials below are therefore written
+// in the negated argument.
+__device__ __forceinline__ double fma3(const double &a, double b, double c) { return __builtin_fma(a, -b, c); }
+
+// The same for a literal a: two constants, so an FMA by name (the compiler
+// would fold the negation into a and fall back to v_fmac).
+__device__ __forceinline__ double fma3(double &&a, double b, double c)
 {
     double d;
-    asm("v_fma_f64 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c));
+    asm("v_fma_f64 %0, %1, -%2, %3" : "=v"(d) : "v"(a), "v"(b), "s"(c));
     return d;
 }
 
@@ -111,16 +117,27 @@ __device__ __forceinline__ double exp_neg_single(double D)
 // exactly and the moments follow from u with no cancellation: e1 = u,
 // e0 = D - u, ex = 1 - e0, e2 = D^2 - 2 e1 = -2 r^3 P.  Elsewhere
 // ex = 2^n (1 + r + u) and the closed forms below, which lose at most about
-// five bits to cancellation from D = ln2/2 up.
+// five bits to cancellation from D = ln2/2 up.  (The code holds -n and -r.)
+//
+// WANT_H (the box sweep): the last output is h = D e1 - e2 instead of e2, the
+// only combination its weights need besides e1: D^3 (1/2 + r P - 2 P) where
+// n = 0 (no cancellation beyond a factor of three), 2 e1 - D e0 elsewhere, one
+// instruction fewer on either side than e2 and then h.  Both sides run under a
+// lane mask, 14 instructions; measured against it on 129^3 x 2048 (63.5 ms a
+// launch): jumps for wavefronts that are thin, thick or mixed as a whole, 64.5
+// ms with fewer instructions, and one formula for both sides without a mask,
+// 67.3 ms with three more.
+template <bool WANT_H = false>
 __device__ __forceinline__ void moments_single(double D, double &ex, double &e0, double &e1, double &e2)
 {
-    // x = max(-D, -745) by one instruction (the library minimum would first
+    // z = min(D, 745) by one instruction (the library minimum would first
     // quiet signalling NaNs, which arithmetic never produces); a NaN step
-    // gives a finite x, and e1, e2 keep the NaN
-    double x;
-    asm("v_max_f64 %0, -%1, %2" : "=v"(x) : "v"(D), "s"(-745.0));
-    const double n = __builtin_rint(x * 1.4426950408889634);
-    const double r = __builtin_fma(-n, 0.6931471805599453, x);
+    // gives a finite z, and e1, e2 keep the NaN.  r here is the negated
+    // reduced argument
+    double z;
+    asm("v_min_f64 %0, %1, %2" : "=v"(z) : "v"(D), "s"(745.0));
+    const double n = __builtin_rint(z * 1.4426950408889634);
+    const double r = __builtin_fma(n, -0.6931471805599453, z);
     // degree-6 Chebyshev interpolant of P on |r| <= ln2/2 (gen_moment_poly.py)
     double P = fma3(2.761004197490652e-06, r, 2.485957814859904e-05);
     P = fma3(P, r, 0.00019841238150245533);
@@ -129,18 +146,18 @@ __device__ __forceinline__ void moments_single(double D, double &ex, double &e0,
     P = fma3(P, r, 0.0416666667189806);
     P = fma3(P, r, 0.16666666666666652);
     const double r2 = r * r;
-    const double h = __builtin_fma(r, P, 0.5);  // u = r^2 h
+    const double h = __builtin_fma(-r, P, 0.5);  // u = r^2 h
     if (n == 0.0) {
         const double u = r2 * h;
         e1 = u;
         e0 = D - u;
         ex = 1.0 - e0;
-        e2 = (-2.0 * r2) * (r * P);
+        e2 = WANT_H ? (D * r2) * __builtin_fma(-2.0, P, h) : (2.0 * r2) * (r * P);
     } else {
-        ex = __builtin_ldexp(__builtin_fma(r2, h, 1.0 + r), (int)n);
+        ex = __builtin_ldexp(__builtin_fma(r2, h, 1.0 - r), -(int)n);
         e0 = 1.0 - ex;
         e1 = D - e0;
-        e2 = __builtin_fma(D, D, -2.0 * e1);
+        e2 = WANT_H ? __builtin_fma(2.0, e1, -(D * e0)) : __builtin_fma(D, D, -2.0 * e1);
     }
 }
 
@@ -263,58 +280,90 @@ __device__ __forceinline__ PointW<T> point_weights(double D, double Dp, bool las
     return w;
 }
 
-// point_weights for optical steps that are already at least kMinStep (formed
-// by step_depth): no clamping here.  LAST: the final point of a ray (linear
+// point_weights for optical steps that are already at least kMinStep (sums of
+// half_depth): no clamping here.  LAST: the final point of a ray (linear
 // weights; Dp is not read).  DLIN: also the linear operator's diagonal e1/D.
 // The linear weights are the parabolic ones in the limit of an infinite
-// downwind step, so a point that takes them is evaluated with Dp replaced by
-// 2^300: beta = e1/D (1 + O(D/2^300)) and gamma = -(D e1 - e2)/(2^300 (D +
-// 2^300)), far below the rounding of either for any physical step (gamma is
-// then zero in single precision), with one select in place of one per
-// weight.  D D'(D + D') stays finite for every D below 2^424.
+// downwind step.  Double results: a point that takes them is evaluated with Dp
+// replaced by 2^300 (beta = e1/D (1 + O(D/2^300)), gamma far below the rounding
+// for any physical step; D D'(D + D') stays finite for every D below 2^360).
+// Single results: with h = 0, which is the same limit at any D', by one select
+// of one word; D D'(D + D') stays finite for every D below 2^340, and float
+// opacities give steps below 2^140.
 template <typename T, bool LAST, bool DLIN = true>
 __device__ __forceinline__ PointW<T> point_weights_pos(double D, double Dp)
 {
     constexpr bool FULL = sizeof(T) == 8;
-    double ex, e0, e1, e2;
-    kernel_moments<FULL>(D, ex, e0, e1, e2);
-    const double h = __builtin_fma(D, e1, -e2);  // D e1 - e2
-    const bool lin = LAST || (Dp < 0.5 * D) || (Dp * e0 <= h);
-    const double Dq = lin ? 0x1p300 : Dp;
-    const double Ds = D + Dq;
-    // single-precision results take the hardware estimate as it is: its relative
-    // error, at most 4.6e-8 (2^-24.4) over a million random arguments, is below
-    // the rounding of the weights to single precision, and a = e0 - b - g keeps
-    // the three weights summing to e0 whatever the error of b and g
-    const double r = FULL ? rcp_f64<true>(D * Dq * Ds) : __builtin_amdgcn_rcp(D * Dq * Ds);
-    const double q = Ds * r;  // 1 / (D Dq)
-    const double b = __builtin_fma(Ds, e1, -e2) * q;
-    const double g = h * (-D * r);
     PointW<T> w;
-    w.ex = T(ex);
-    w.b = T(b);
-    w.g = T(g);
-    w.a = T(e0 - b - g);
     w.dlin = T(0);
-    if constexpr (DLIN) w.dlin = T(e1 * (FULL ? rcp_f64<true>(D) : __builtin_amdgcn_rcp(D)));
-    return w;
+    double ex, e0, e1;
+    if constexpr (FULL) {
+        double e2;
+        kernel_moments<true>(D, ex, e0, e1, e2);
+        const double h = __builtin_fma(D, e1, -e2);  // D e1 - e2
+        const bool lin = LAST || (Dp < 0.5 * D) || (Dp * e0 <= h);
+        const double Dq = lin ? 0x1p300 : Dp;
+        const double Ds = D + Dq;
+        const double r = rcp_f64<true>(D * Dq * Ds);
+        const double b = __builtin_fma(Ds, e1, -e2) * (Ds * r);
+        const double g = h * (-D * r);
+        w.ex = T(ex);
+        w.b = T(b);
+        w.g = T(g);
+        w.a = T(e0 - b - g);
+        if constexpr (DLIN) w.dlin = T(e1 * rcp_f64<true>(D));
+        return w;
+    } else {
+        double h;  // D e1 - e2
+        moments_single<true>(D, ex, e0, e1, h);
+        // single-precision results take the hardware reciprocal as it is: its relative
+        // error, at most 4.6e-8 (2^-24.4) over a million random arguments, is below
+        // the rounding of the weights to single precision, and a = e0 - b - g keeps
+        // the three weights summing to e0 whatever the error of b and g
+        w.ex = T(ex);
+        if constexpr (LAST) {
+            const double b = e1 * __builtin_amdgcn_rcp(D);
+            w.b = w.dlin = T(b);
+            w.g = T(0);
+            w.a = T(e0 - b);
+            return w;
+        }
+        const bool lin = (Dp < 0.5 * D) || (Dp * e0 <= h);
+        const double Ds = D + Dp;
+        const double r = __builtin_amdgcn_rcp(D * Dp * Ds);
+        // linear points: h = 0 in b = (h + D' e1) / (D D'), g = -h / (D' (D + D'))
+        // leaves b = e1/D and g = 0.  Clearing the high word is enough: what is
+        // left, below 1e-313, is nothing beside D' e1 > 1e-301.
+        h = __hiloint2double(lin ? 0 : __double2hiint(h), __double2loint(h));
+        const double b = __builtin_fma(Dp, e1, h) * (Ds * r);
+        const double g = h * (-D * r);
+        w.b = T(b);
+        w.g = T(g);
+        w.a = T(e0 - b - g);
+        if constexpr (DLIN) w.dlin = T(e1 * __builtin_amdgcn_rcp(D));
+        return w;
+    }
 }
 
-// Optical step between two points from their optical depths: D = (ta + tb)/2
-// + kMinStep by one FMA (the half sum is exact, so the sum rounds back to it
-// for every D above 2^-276; a vacuum step, ta = tb = 0, becomes kMinStep, and
-// so the shared reciprocal of the weights stays finite).  NaN and Inf
-// propagate.  Depths ta, tb >= 0 (opacities are non-negative).
-__device__ __forceinline__ double step_depth(double ta, double tb)
+// Half the optical depth of a segment, chi s / 2 + kMinStep / 2, from half its
+// path length (halving is exact): the optical step between two points is then
+// the plain sum of their half depths, and equals (ta + tb)/2 of the full depths
+// ta, tb >= 0 bit for bit for every depth above 2^-270.  A vacuum step,
+// ta = tb = 0, becomes kMinStep, and so the shared reciprocal of the weights
+// stays finite.  NaN and Inf propagate.
+__device__ __forceinline__ double half_depth(double chi, double s_half)
 {
-    double sum;
-    {
-#pragma clang fp contract(off)
-        sum = ta + tb;
-    }
     double d;
-    asm("v_fma_f64 %0, %1, 0.5, %2" : "=v"(d) : "v"(sum), "s"(kMinStep));
+    // three addresses: the two-address form would copy the constant addend first
+    asm("v_fma_f64 %0, %1, %2, %3" : "=v"(d) : "v"(chi), "s"(s_half), "v"(0.5 * kMinStep));
     return d;
+}
+
+// The same sum in the sweep's order, without contraction.
+__device__ __forceinline__ double step_of(double ha, double hb)
+{
+#pragma clang fp contract(off)
+    return ha + hb;
 }
 
 // Entry half-segment: constant S from the entry point to the first point.

@@ -50,6 +50,9 @@
 
 namespace rt3d {
 
+// Half the optical depth of a segment from its half path length.
+__device__ __forceinline__ double half_seg(double chi, double s_half) { return seg_depth(chi, s_half); }
+
 // One contribution w G in fixed point, round(w G 2^52) as a signed 64-bit
 // integer (ties to even).
 __device__ __forceinline__ long long fix52(double cw52, double G) { return __double2ll_rn(cw52 * G); }
@@ -68,7 +71,7 @@ __global__ void __launch_bounds__(256) lstar_stencil_kernel(StencilArgs a)
     unsigned long long *__restrict__ acc = a.acc + (int64_t)lam * kStencil * a.n_vox;
     const int64_t vb = a.dir_vbegin[d];
     const int M = a.dir_M[d];
-    const double wmu = a.dir_wmu[d];
+    const double wmu = 2.0 * a.dir_wmu[d];  // the visit table holds half path lengths
     const int dl = a.dir_mu[d] < 0.0 ? 1 : -1;
     const uint32_t *__restrict__ dxy = a.dxy + vb;
     const double *__restrict__ sv = a.s + vb;
@@ -98,7 +101,7 @@ __global__ void __launch_bounds__(256) lstar_stencil_kernel(StencilArgs a)
     int k_cur = dl > 0 ? 0 : a.Nz - 1;
     uint32_t w_cur = dxy[0];
     int64_t v_cur = voxel(w_cur, k_cur);
-    double t_cur = seg_depth((double)chi[v_cur], sv[0]);
+    double t_cur = half_seg((double)chi[v_cur], sv[0]);
     int k_nxt = k_cur + ((w_cur & kLayerEnd) ? dl : 0);
     uint32_t w_nxt = 0;
     int64_t v_nxt = 0;
@@ -106,12 +109,12 @@ __global__ void __launch_bounds__(256) lstar_stencil_kernel(StencilArgs a)
     if (M > 1) {
         w_nxt = dxy[1];
         v_nxt = voxel(w_nxt, k_nxt);
-        t_nxt = seg_depth((double)chi[v_nxt], sv[1]);
+        t_nxt = half_seg((double)chi[v_nxt], sv[1]);
     }
     double Gv[5] = {0.0, 0.0, 0.0, 0.0, 0.0};  // G_-1, G_0, G_1, G_2, G_3
     {
         double ex0, e00;
-        entry_weights<double>(0.5 * t_cur, ex0, e00);
+        entry_weights<double>(t_cur, ex0, e00);
         Gv[1] = e00;
         add(v_cur, wmu * sv[0], comp[0], Gv);
     }
@@ -126,10 +129,10 @@ __global__ void __launch_bounds__(256) lstar_stencil_kernel(StencilArgs a)
         if (!last) {
             w_nxt = dxy[m + 1];
             v_nxt = voxel(w_nxt, k_nxt);
-            t_nxt = seg_depth((double)chi[v_nxt], sv[m + 1]);
+            t_nxt = half_seg((double)chi[v_nxt], sv[m + 1]);
         }
-        const double D = half_sum(t_prev, t_cur);
-        const double Dp = last ? 0.0 : half_sum(t_cur, t_nxt);
+        const double D = step_of(t_prev, t_cur);
+        const double Dp = last ? 0.0 : step_of(t_cur, t_nxt);
         double ex, wa, wb, wg;
         // single-precision grids keep the stencil in float: the shorter
         // moment forms of the float sweep suffice there
@@ -169,7 +172,7 @@ __global__ void __launch_bounds__(1024) lstar_stencil_rows_kernel(StencilArgs a)
     unsigned long long *__restrict__ acc = a.acc + (int64_t)lam * kStencil * a.n_vox;
     const int64_t vb = a.dir_vbegin[d];
     const int M = a.dir_M[d];
-    const double wmu = a.dir_wmu[d];
+    const double wmu = 2.0 * a.dir_wmu[d];  // the visit table holds half path lengths
     const int dl = a.dir_mu[d] < 0.0 ? 1 : -1;
     const uint32_t *__restrict__ dxy = a.dxy + vb;
     const double *__restrict__ sv = a.s + vb;
@@ -215,12 +218,12 @@ __global__ void __launch_bounds__(1024) lstar_stencil_rows_kernel(StencilArgs a)
     for (int r = 0; r < R; ++r) {
         slot[r] = (yr[r] + br_cur) % W;
         x_cur[r] = col(x0[r], w_cur);
-        t_cur[r] = seg_depth((double)chi[(int64_t)k_cur * NxNy + (int64_t)row(y0[r], w_cur) * Nx + x_cur[r]], sv[0]);
+        t_cur[r] = half_seg((double)chi[(int64_t)k_cur * NxNy + (int64_t)row(y0[r], w_cur) * Nx + x_cur[r]], sv[0]);
         x_nxt[r] = 0;
         t_nxt[r] = 0.0;
         if (M > 1) {
             x_nxt[r] = col(x0[r], w_nxt);
-            t_nxt[r] = seg_depth((double)chi[(int64_t)k_nxt * NxNy + (int64_t)row(y0[r], w_nxt) * Nx + x_nxt[r]],
+            t_nxt[r] = half_seg((double)chi[(int64_t)k_nxt * NxNy + (int64_t)row(y0[r], w_nxt) * Nx + x_nxt[r]],
                                  sv[1]);
         }
 #pragma unroll
@@ -322,7 +325,7 @@ __global__ void __launch_bounds__(1024) lstar_stencil_rows_kernel(StencilArgs a)
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         double ex0, e00;
-        entry_weights<double>(0.5 * t_cur[r], ex0, e00);
+        entry_weights<double>(t_cur[r], ex0, e00);
         Gv[r][1] = e00;
     }
     add(wmu * sv[0], comp[0]);
@@ -341,11 +344,11 @@ __global__ void __launch_bounds__(1024) lstar_stencil_rows_kernel(StencilArgs a)
             t_cur[r] = t_nxt[r];
             if (!last) {
                 x_nxt[r] = col(x0[r], w_nxt);
-                t_nxt[r] = seg_depth(
+                t_nxt[r] = half_seg(
                     (double)chi[(int64_t)k_nxt * NxNy + (int64_t)row(y0[r], w_nxt) * Nx + x_nxt[r]], sv[m + 1]);
             }
-            const double D = half_sum(t_prev, t_cur[r]);
-            const double Dp = last ? 0.0 : half_sum(t_cur[r], t_nxt[r]);
+            const double D = step_of(t_prev, t_cur[r]);
+            const double Dp = last ? 0.0 : step_of(t_cur[r], t_nxt[r]);
             double ex, wa, wb, wg;
             if (PARA) {
                 const PointW<double> pw = point_weights<double, sizeof(G) == 8>(D, Dp, last);

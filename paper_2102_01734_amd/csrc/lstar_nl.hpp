@@ -24,7 +24,7 @@ struct StencilArgs {
     int Nx, Ny, Nz;
     int64_t n_vox;
     const uint32_t *dxy;       // per visit: di mod Nx | (dj mod Ny) << 15 | layer-end flag
-    const double *s;           // per visit: path length
+    const double *s;           // per visit: half path length
     const uint32_t *comp;      // per visit: packed stencil components (see above)
     const int64_t *dir_vbegin;
     const int32_t *dir_M;

@@ -173,8 +173,16 @@ struct rt_grid {
     int span_max = 0;   // largest per-layer row extent of any template
     bool band = false;  // the box sweep uses band tiles (see fs_box.hip)
     bool layer_ok = false;  // whole-layer tiles fit (and were not excluded by RT_F_BAND_TILES)
-    Variant var[2][2][2];  // [dbl][wj][wl]
-    bool tuned = false;
+    // Default shapes with the fewest bundles per direction [dbl][wj][wl]: they
+    // decide whether a grid is servable and on which tile kind, size its memory
+    // check and run the no-allocation path, whose scratch holds few slots.
+    Variant var[2][2][2];
+    // J-only shapes fixed by the caller (rt_autotune, rt_set_launch_shape*,
+    // rt_set_anchor_shape) [dbl], and the shapes chosen for a call's number of
+    // wavelengths and directions (pick_variant), by precision, outputs and counts
+    bool fixed[2] = {false, false};
+    Variant fixed_var[2];
+    std::map<std::string, Variant> picks;
 
     std::map<std::string, std::unique_ptr<DevSchedule>> schedules;
 
@@ -269,6 +277,16 @@ struct rt_grid {
 };
 
 inline Variant &variant(rt_grid *g, bool dbl, bool wj, bool wl) { return g->var[dbl][wj][wl]; }
+// The same, or the shape that the caller fixed.
+inline const Variant &base_variant(rt_grid *g, bool dbl, bool wj, bool wl)
+{
+    return wj && !wl && g->fixed[dbl] ? g->fixed_var[dbl] : g->var[dbl][wj][wl];
+}
+// The shape a formal solution of n_lambda wavelengths over `subset` (null: all
+// directions) runs: the caller's fixed one, else the one of least estimated
+// time (api_launch.cpp).
+Variant pick_variant(rt_grid *g, bool dbl, bool wj, bool wl, int n_lambda,
+                     const std::vector<int32_t> *subset = nullptr);
 
 // ---------------------------------------------------------------------------
 // functions shared between the modules
@@ -279,8 +297,10 @@ rt_status collect_graph_time(rt_grid *g, rt_grid::GraphStep &gs);
 
 // ok = false for shapes that cannot hold a bundle's rays, whose tiles do not
 // fit, or (unless allow_spill) whose kernel spills registers
+// n_bundles: ray bundles per direction (0: the shape's own count for layer
+// tiles, the fewest that fit for band tiles)
 Variant make_variant(rt_grid *g, bool dbl, bool wj, bool wl, int lb, int R, int occ = 1, bool band = false,
-                     bool allow_spill = false);
+                     bool allow_spill = false, int n_bundles = 0);
 void setup_variant(rt_grid *g, bool dbl, bool wj, bool wl);
 rt_status get_schedule(rt_grid *g, int n_wg, const std::vector<int32_t> &lambdas, DevSchedule **out,
                        const std::vector<int32_t> *subset = nullptr, const Variant *v = nullptr);
