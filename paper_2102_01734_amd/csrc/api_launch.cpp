@@ -141,9 +141,10 @@ static double shape_cost(const rt_grid *g, const Variant &v, int n_lambda, int n
     const double x = std::max(std::ceil(waves / 4.0) * v.R, per_cu * waves * v.R / 4.0);
     double c = v.dbl ? (v.R > 6 ? 450.0 : 370.0) : v.band ? 270.0 : 290.0;
     // a wavelength's padded field beyond the 256 MB Infinity Cache: the HBM latency
-    // shows at ten rays a thread and more, whose registers hold few pairs in
-    // flight (257^3 x 512: 768 x 10 168 ms, 768 x 8 156, 1024 x 4 152)
-    if (!v.dbl && v.R >= 10 && 32.0 * (double)g->n_vox > 256e6) c *= 1.3;
+    // shows where 30 rays and more share a SIMD lane's 512 registers, which then
+    // hold few pairs in flight (257^3 x 512: 1024 x 8 180 ms, 768 x 11 179, 768 x 10
+    // 168; 768 x 8 156, 768 x 6 154, 1024 x 4 152)
+    if (!v.dbl && v.R * v.lb >= 30 * 256 && 32.0 * (double)g->n_vox > 256e6) c *= 1.3;
     if (v.wj && v.wl) c *= 1.25;
     else if (v.wl) c *= 0.8;
     const bool wide = v.band && !v.dbl && !(v.wj && v.wl);
