@@ -3,14 +3,15 @@
 // The 3^3 convolutions between feature maps of 16, 32 or 64 channels are
 // implicit GEMMs on the matrix cores (v_mfma_f32_16x16x32_bf16): the
 // reduction index k runs over (tap, input channel), 27 CI values padded to a
-// multiple of 32, and one wavefront computes T tiles of 16 consecutive
-// output voxels (in flattened z, y, x order) times all output channels.  Per
-// 32-wide k chunk a lane loads 8 consecutive input channels of one tap for
-// its voxel (A, 16 bytes, channels last; zero for the padding taps and for
-// taps beyond the top or bottom layer) and 8 weights of one output channel
-// (B, 16 bytes); products accumulate in fp32.  Bias, ReLU and the U-Net skip
-// addition are fused into the store.  The small layers (3 input features,
-// the 1-channel head) and the upsampling are plain VALU kernels.
+// multiple of 32, in tiles of 16 voxels times 16 output channels.  Per 32-wide
+// k chunk a lane holds 8 consecutive input channels of one tap for its voxel
+// (16 bytes, channels last; zero for the padding taps and for taps beyond the
+// top or bottom layer) and 8 weights of one output channel (16 bytes);
+// products accumulate in fp32.  Bias, ReLU and the U-Net skip addition are
+// fused into the store, and the 1-channel head into the last convolution's.
+// Stride-1 layers stage their input in LDS (conv_tile_kernel), the stride-2
+// ones, an eighth of the voxels, read it from L2 (conv_mfma_kernel).  The input
+// layer (3 float features) and the upsampling are plain VALU kernels.
 // Activations never leave HBM between layers; at 129^3 with 16 channels a
 // level-0 map is 68 MB.
 #include <hip/hip_runtime.h>
@@ -51,7 +52,7 @@ struct Vol {
 };
 
 // ---------------------------------------------------------------------------
-// 3^3 convolution on the matrix cores
+// 3^3 convolution on the matrix cores, any stride: input from L2
 // ---------------------------------------------------------------------------
 struct ConvArgs {
     const uint16_t *in;
@@ -162,7 +163,198 @@ static hipError_t conv_mfma(const ConvArgs &a, int ci, int co, hipStream_t st)
 }
 
 // ---------------------------------------------------------------------------
-// input layer (3 features -> C channels) and head (C -> 1), fp32 VALU
+// stride-1 convolutions from LDS
+// ---------------------------------------------------------------------------
+// A block computes TX x TY x TZ output voxels (TX <= TXM, evened out over the
+// row) for all output channels from an LDS copy of their input with its halo,
+// so that a voxel's channels come from L2 once or twice instead of 27 times:
+// reading them from L1 per tap bounded the plain kernel (64 bytes a cycle and
+// CU, 48 cycles of loads for 8 of matrix instructions).  LDS gives 128, of which
+// 16 output channels use all (one 1 KB read per matrix instruction).  The 16-voxel
+// tiles run over the block's voxels in flattened order, so rows of 129 waste
+// no lanes; a wavefront keeps its tiles' sums in registers and walks the k
+// chunks in the plain kernel's order (the sums are the same to the bit), whose
+// weights it reads once per chunk.  Weights are the first operand, so a lane ends
+// up with four consecutive channels of one voxel: 8-byte stores.  Two blocks fit
+// a CU, so what bounds it is latency: the loads of the LDS copy are issued in
+// batches and the operands of the next chunk read ahead (without either: 116 and
+// 285 us).  Measured at 129^3: 16 -> 16 channels 170 -> 97 us, 32 -> 16 channels
+// with the skip 382 -> 190 us; the network 1149 -> 784 us.
+template <int CI>
+struct ConvTile {
+    static constexpr int TXM = CI == 16 ? 44 : CI == 32 ? 33 : 22, TY = 4, TZ = CI == 64 ? 2 : 4;
+    static constexpr int IX = TXM + 2, IY = TY + 2, IZ = TZ + 2;
+    static constexpr int kTiles = (TXM * TY * TZ + 15) / 16, kPerWave = (kTiles + 3) / 4;
+    static constexpr size_t kBytes = (size_t)IX * IY * IZ * CI * 2;
+};
+
+// Block origin (x0, y0, z0) and width tx of the tiles of a volume.
+__device__ __forceinline__ void tile_origin(Vol v, int txm, int ty, int tz, int &x0, int &y0, int &z0, int &tx)
+{
+    const int nbx = (v.nx + txm - 1) / txm, nby = (v.ny + ty - 1) / ty;
+    tx = (v.nx + nbx - 1) / nbx;
+    int b = blockIdx.x;
+    const int q = b / nbx;
+    x0 = (b - q * nbx) * tx;
+    z0 = (q / nby) * tz;
+    y0 = (q - (q / nby) * nby) * ty;
+}
+
+static unsigned tile_blocks(Vol v, int txm, int ty, int tz)
+{
+    const int64_t nbx = (v.nx + txm - 1) / txm, nby = (v.ny + ty - 1) / ty, nbz = (v.nz + tz - 1) / tz;
+    return (unsigned)(nbx * nby * nbz);
+}
+
+struct HeadArgs {
+    const float *w;     // [CO], null: no head, store the map
+    const float *bias;  // [1]
+    float *out;         // [vo]
+};
+
+template <int CI, int CO>
+__global__ void __launch_bounds__(256, 2) conv_tile_kernel(ConvArgs a, HeadArgs hd)
+{
+    using C = ConvTile<CI>;
+    constexpr int NB = CO / 16, NK = (27 * CI + 31) / 32, T = C::kPerWave;
+    extern __shared__ __align__(16) unsigned char in[];  // [IZ][IY][IX][CI] bf16
+    const Vol v = a.vo;
+    int x0, y0, z0, tx;
+    tile_origin(v, C::TXM, C::TY, C::TZ, x0, y0, z0, tx);
+    const int tid = threadIdx.x;
+    constexpr int kChunks = CI / 8;  // 16-byte chunks per voxel
+    // every thread's share in a few batches of loads in flight together: one by
+    // one, their latency was most of the kernel
+    constexpr int kN = C::IX * C::IY * C::IZ * kChunks, kPer = (kN + 255) / 256;
+    constexpr int kBatches = (kPer + 13) / 14, U = (kPer + kBatches - 1) / kBatches;
+    for (int k0 = tid; k0 < kN; k0 += 256 * U) {
+        v4u u[U];
+#pragma unroll
+        for (int n = 0; n < U; ++n) {
+            const int k = k0 + 256 * n;
+            const int c = k % kChunks, q = k / kChunks;
+            const int ix = q % C::IX, r = q / C::IX, iy = r % C::IY, iz = r / C::IY;
+            const int x = x0 + ix - 1, y = y0 + iy - 1, z = z0 + iz - 1;
+            u[n] = v4u{0u, 0u, 0u, 0u};
+            // input of voxels inside the volume: neighbours across the period, none beyond the top or bottom
+            if (k < kN && ix < tx + 2 && x <= v.nx && y <= v.ny && z >= 0 && z < v.nz)
+                u[n] = *reinterpret_cast<const v4u *>(
+                    a.in + (((int64_t)z * v.ny + wrap(y, v.ny)) * v.nx + wrap(x, v.nx)) * CI + 8 * c);
+        }
+#pragma unroll
+        for (int n = 0; n < U; ++n)
+            if (k0 + 256 * n < kN) *reinterpret_cast<v4u *>(in + 16 * (k0 + 256 * n)) = u[n];
+    }
+    const int lane = tid & 63, wave = tid >> 6, i = lane & 15, kq = (lane >> 4) * 8;
+    const int P = tx * C::TY * C::TZ;
+    int base[T];
+    v4f acc[T][NB];
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        const int q = min((wave + 4 * t) * 16 + i, P - 1);
+        const int r = q / tx;
+        base[t] = (((r / C::TY) * C::IY + r % C::TY) * C::IX + q - r * tx) * (2 * CI) + 2 * (kq % CI & (CI == 16 ? 8 : 31));
+#pragma unroll
+        for (int cb = 0; cb < NB; ++cb) acc[t][cb] = v4f{0.f, 0.f, 0.f, 0.f};
+    }
+    __syncthreads();
+    // k = 32 j + kq: with 16 channels a chunk spans two taps, else one
+    auto weights = [&](int j, int cb) {
+        const int k = j * 32 + kq;
+        const int tap = k / CI, c0 = k % CI;
+        const bool ok = CI != 16 || j + 1 < NK || tap < 27;
+        return load8(a.w + ((int64_t)(ok ? tap : 0) * CO + cb * 16 + i) * CI + c0, ok);
+    };
+    auto tap_off = [](int t) { return ((t / 9 * C::IY + t / 3 % 3) * C::IX + t % 3) * (2 * CI); };
+    auto voxels = [&](int j, int t) {
+        // byte offset of the lane's tap from its voxel's corner (its channels are in base)
+        const int off = CI == 16 ? ((kq & 16) ? tap_off(2 * j + 1 < 27 ? 2 * j + 1 : 26) : tap_off(2 * j))
+                                 : tap_off(j * 32 / CI) + 2 * (j * 32 % CI);
+        v4u u = *reinterpret_cast<const v4u *>(in + base[t] + off);
+        if (CI == 16 && j + 1 == NK) u = (kq & 16) ? v4u{0u, 0u, 0u, 0u} : u;  // tap 27 does not exist
+        return __builtin_bit_cast(v8bf, u);
+    };
+    // chunk j + 1's voxels and chunk j + 2's weights are read before chunk j's
+    // products; the barriers keep the scheduler from moving them together again
+    v8bf X[2][T], W[3][NB];
+#pragma unroll
+    for (int cb = 0; cb < NB; ++cb) {
+        W[0][cb] = weights(0, cb);
+        W[1][cb] = weights(1, cb);
+    }
+#pragma unroll
+    for (int t = 0; t < T; ++t) X[0][t] = voxels(0, t);
+#pragma unroll
+    for (int j = 0; j < NK; ++j) {
+        if (j + 2 < NK)
+#pragma unroll
+            for (int cb = 0; cb < NB; ++cb) W[(j + 2) % 3][cb] = weights(j + 2, cb);
+        if (j + 1 < NK)
+#pragma unroll
+            for (int t = 0; t < T; ++t) X[(j + 1) % 2][t] = voxels(j + 1, t);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int t = 0; t < T; ++t)
+#pragma unroll
+            for (int cb = 0; cb < NB; ++cb)
+                acc[t][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(W[j % 3][cb], X[j % 2][t], acc[t][cb], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    // D layout: a lane holds channels 16 cb + kq/2 .. + 3 of voxel i
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        const int q = (wave + 4 * t) * 16 + i;
+        const int r = q / tx, x = x0 + q - r * tx, y = y0 + r % C::TY, z = z0 + r / C::TY;
+        const bool ok = q < P && x < v.nx && y < v.ny && z < v.nz;
+        const int64_t o = ((int64_t)z * v.ny + y) * v.nx + x;
+        float dot = 0.f;
+#pragma unroll
+        for (int cb = 0; cb < NB; ++cb) {
+            const int co = cb * 16 + kq / 2;
+            uint16_t h[4];
+            uint16_t sk[4] = {0, 0, 0, 0};
+            if (a.skip && ok) *reinterpret_cast<uint64_t *>(sk) = *reinterpret_cast<const uint64_t *>(a.skip + o * CO + co);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                float val = fmaxf(acc[t][cb][e] + a.bias[co + e], 0.f);
+                if (a.skip) val += bf2f(sk[e]);
+                h[e] = f2bf(val);
+                if (hd.w) dot += hd.w[co + e] * bf2f(h[e]);
+            }
+            if (ok && !hd.w) *reinterpret_cast<uint64_t *>(a.out + o * CO + co) = *reinterpret_cast<uint64_t *>(h);
+        }
+        if (hd.w) {  // the four lanes of a voxel hold its channels between them
+            dot += __shfl_xor(dot, 16, 64);
+            dot += __shfl_xor(dot, 32, 64);
+            if (ok && lane < 16) hd.out[o] = dot + hd.bias[0];
+        }
+    }
+}
+
+template <int CI, int CO>
+static hipError_t conv_tile_t(const ConvArgs &a, const HeadArgs &hd, hipStream_t st)
+{
+    using C = ConvTile<CI>;
+    auto k = conv_tile_kernel<CI, CO>;
+    hipError_t e = hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)C::kBytes);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k, dim3(tile_blocks(a.vo, C::TXM, C::TY, C::TZ)), dim3(256), C::kBytes, st, a, hd);
+    return hipGetLastError();
+}
+
+static hipError_t conv_tile(const ConvArgs &a, int ci, int co, const HeadArgs &hd, hipStream_t st)
+{
+#define RT_CONV_CASE(I, O) \
+    if (ci == I && co == O) return conv_tile_t<I, O>(a, hd, st);
+    RT_CONV_CASE(16, 16)
+    RT_CONV_CASE(32, 16) RT_CONV_CASE(32, 32)
+    RT_CONV_CASE(64, 16) RT_CONV_CASE(64, 32) RT_CONV_CASE(64, 64)
+#undef RT_CONV_CASE
+    return hipErrorInvalidValue;
+}
+
+// ---------------------------------------------------------------------------
+// input layer (3 features -> C channels), fp32 VALU
 // ---------------------------------------------------------------------------
 template <int CO>
 __global__ void __launch_bounds__(256) conv_in_kernel(const float *__restrict__ f, Vol v, const float *__restrict__ w,
@@ -194,18 +386,6 @@ __global__ void __launch_bounds__(256) conv_in_kernel(const float *__restrict__ 
     }
 #pragma unroll
     for (int c = 0; c < CO; ++c) out[id * CO + c] = f2bf(fmaxf(acc[c], 0.f));
-}
-
-template <int C>
-__global__ void __launch_bounds__(256) head_kernel(const uint16_t *__restrict__ h, int64_t n, const float *__restrict__ w,
-                                                   const float *__restrict__ bias, float *__restrict__ out)
-{
-    const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (id >= n) return;
-    float acc = bias[0];
-#pragma unroll
-    for (int c = 0; c < C; ++c) acc += w[c] * bf2f(h[id * C + c]);
-    out[id] = acc;
 }
 
 // linear upsampling by 2 (align corners): fine index o takes the coarse
@@ -433,24 +613,21 @@ static hipError_t conv_in_t(const float *f, Vol v, const float *w, const float *
     return hipGetLastError();
 }
 
-template <int C>
-static hipError_t head_t(const uint16_t *h, int64_t n, const float *w, const float *b, float *out, hipStream_t st)
-{
-    hipLaunchKernelGGL((head_kernel<C>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, h, n, w, b, out);
-    return hipGetLastError();
-}
-
 hipError_t unet_forward(UNetDev *u, const float *features, float *out, hipStream_t st)
 {
     const UNetSpec &s = u->spec;
     const auto &C = s.C;
     size_t k = 0;  // conv index in blob order
     hipError_t e;
+    const size_t last = s.convs.size() - 2;  // the convolution that the head follows
     auto conv = [&](const uint16_t *in, Vol vi, Vol vo, int stride, int ci, int co, const uint16_t *skip,
                     uint16_t *o) {
         ConvArgs a{in, vi, vo, stride, (const uint16_t *)u->w[k], (const float *)u->b[k], skip, o};
+        HeadArgs hd{};
+        if (k == last) hd = HeadArgs{(const float *)u->w[k + 1], (const float *)u->b[k + 1], out};
         ++k;
-        return conv_mfma(a, ci, co, st);
+        // more output than input channels: the sums of a block's tiles would not stay in registers
+        return stride == 1 && co <= ci ? conv_tile(a, ci, co, hd, st) : conv_mfma(a, ci, co, st);
     };
     // level 0 input layer
     const Vol v0 = u->lv[0];
@@ -476,12 +653,7 @@ hipError_t unet_forward(UNetDev *u, const float *features, float *out, hipStream
         if ((e = conv(u->up, vf, vf, 1, C[l], C[l - 1], u->h[l - 1], u->t[l - 1])) != hipSuccess) return e;
         if ((e = conv(u->t[l - 1], vf, vf, 1, C[l - 1], C[l - 1], nullptr, u->h[l - 1])) != hipSuccess) return e;
     }
-    const float *hw = (const float *)u->w[k], *hb = (const float *)u->b[k];
-    switch (C[0]) {
-    case 16: return head_t<16>(u->h[0], v0.n(), hw, hb, out, st);
-    case 32: return head_t<32>(u->h[0], v0.n(), hw, hb, out, st);
-    default: return head_t<64>(u->h[0], v0.n(), hw, hb, out, st);
-    }
+    return hipSuccess;
 }
 
 }  // namespace rt3d
