@@ -116,7 +116,7 @@ hipError_t upload_chunk(SphereChunkDev &ch, const std::vector<SphereDirCache> &d
             const size_t e = (size_t)(bb[(size_t)b] + 64 * m + c);
             const size_t src = (size_t)(r.off + m);
             vx[e] = dirs[r.d].vox[src];
-            sv[e] = (TG)dirs[r.d].s[src];
+            sv[e] = (TG)(0.5 * dirs[r.d].s[src]);  // half path lengths, as the box's
             wv[e] = (TG)dirs[r.d].w[src];
         }
     }

@@ -372,16 +372,14 @@ static rt_status run_fs_sphere(rt_grid *g, const Variant &v, const std::vector<i
         a.lambda_of = sc->lambda_of.as<int32_t>();
         a.n_batch = nb;
         a.lam_stride = g->lx;
+        a.n_vox = g->n_vox;
         a.L = L;
         a.field = fld;
         a.I_bc = I_bc;
         a.outJ = wj ? g->sph_outJ.p : nullptr;
         a.outL = wl ? g->sph_outL.p : nullptr;
         HIPCHK(fs_sphere_launch(a, dbl, g->sph_gdouble, wj, wl, g->para, st));
-        if (wj)
-            HIPCHK(sphere_gather(g->sph_outJ.p, dbl, cp.row, cp.idx, g->n_vox, nb, partJ.p, dbl, c > 0, st));
-        if (wl)
-            HIPCHK(sphere_gather(g->sph_outL.p, dbl, cp.row, cp.idx, g->n_vox, nb, partL.p, dbl, c > 0, st));
+        HIPCHK(sphere_gather(a.outJ, a.outL, dbl, cp.row, cp.idx, g->n_vox, nb, partJ.p, partL.p, c > 0, st));
         if (sl >= 0) {
             HIPCHK(hipEventRecord(g->sph_done[sl], st));
             if (next_copy < host_order.size()) HIPCHK(issue_copy(next_copy++));

@@ -35,12 +35,6 @@ __device__ __forceinline__ double seg_depth(double chi, double s)
     return chi * s;
 }
 
-__device__ __forceinline__ double half_sum(double a, double b)
-{
-#pragma clang fp contract(off)
-    return 0.5 * (a + b);
-}
-
 // 1/x from the hardware reciprocal estimate refined by Newton steps
 // r <- r + r (1 - x r), each of which doubles the correct bits: two steps for
 // double results, one when the weights are rounded to single precision.
@@ -80,30 +74,6 @@ __device__ __forceinline__ double exp_neg(double D)
     p = __builtin_fma(p, r, 0.5);
     p = __builtin_fma(p, r, 1.0);
     p = __builtin_fma(p, r, 1.0);
-    return __builtin_ldexp(p, (int)n);
-}
-
-// exp(-D) for 1/4 <= D and single-precision results (the split moments
-// below): the reduction of exp_neg, then exp(r) = exp(r/16)^16 with exp(r/16)
-// (|r/16| <= 0.0217) from its degree-6 Taylor polynomial (truncation below
-// 1e-14 relative after the squarings, rounding ~3e-15).
-__device__ __forceinline__ double exp_neg_single(double D)
-{
-    const double x = -(D < 745.0 ? D : 745.0);
-    const double n = __builtin_rint(x * 1.4426950408889634);
-    double r = __builtin_fma(-n, 6.93147180369123816490e-01, x);
-    r = __builtin_fma(-n, 1.90821492927058770002e-10, r);
-    const double s = __builtin_ldexp(r, -4);
-    double p = __builtin_fma(s, 1.0 / 720.0, 1.0 / 120.0);
-    p = __builtin_fma(p, s, 1.0 / 24.0);
-    p = __builtin_fma(p, s, 1.0 / 6.0);
-    p = __builtin_fma(p, s, 0.5);
-    p = __builtin_fma(p, s, 1.0);
-    p = __builtin_fma(p, s, 1.0);
-    p = p * p;
-    p = p * p;
-    p = p * p;
-    p = p * p;
     return __builtin_ldexp(p, (int)n);
 }
 
@@ -167,28 +137,20 @@ __device__ __forceinline__ void moments_single(double D, double &ex, double &e0,
 // series 2 D^3 sum_j (-D)^j/(j+3)! and e1, e0, ex follow from it without
 // cancellation; from 1/4 up the closed forms are used (separate branches: a
 // wave whose steps straddle 1/4 runs both).  Single-precision results take
-// moments_single, one path for all D, or with SPLIT the same two branches
-// with a 7-term series (first omitted term below 1e-10 of e2 at D = 1/4) and
-// exp_neg_single: fewer registers, cheaper where the steps of a wave seldom
-// straddle 1/4 (the spherical sweep).
-template <bool FULL, bool SPLIT = false>
+// moments_single, one path for all D.
+template <bool FULL>
 __device__ __forceinline__ void kernel_moments(double D, double &ex, double &e0, double &e1, double &e2)
 {
-    if constexpr (!FULL && !SPLIT) {
+    if constexpr (!FULL) {
         moments_single(D, ex, e0, e1, e2);
         return;
     }
-    double p;
-    if constexpr (FULL) {
-        p = 1.0 / 87178291200.0;                       // 1/14!
-        p = __builtin_fma(-D, p, 1.0 / 6227020800.0);  // 1/13!
-        p = __builtin_fma(-D, p, 1.0 / 479001600.0);   // 1/12!
-        p = __builtin_fma(-D, p, 1.0 / 39916800.0);    // 1/11!
-        p = __builtin_fma(-D, p, 1.0 / 3628800.0);     // 1/10!
-        p = __builtin_fma(-D, p, 1.0 / 362880.0);      // 1/9!
-    } else {
-        p = 1.0 / 362880.0;                            // 1/9!
-    }
+    double p = 1.0 / 87178291200.0;                // 1/14!
+    p = __builtin_fma(-D, p, 1.0 / 6227020800.0);  // 1/13!
+    p = __builtin_fma(-D, p, 1.0 / 479001600.0);   // 1/12!
+    p = __builtin_fma(-D, p, 1.0 / 39916800.0);    // 1/11!
+    p = __builtin_fma(-D, p, 1.0 / 3628800.0);     // 1/10!
+    p = __builtin_fma(-D, p, 1.0 / 362880.0);      // 1/9!
     p = __builtin_fma(-D, p, 1.0 / 40320.0);       // 1/8!
     p = __builtin_fma(-D, p, 1.0 / 5040.0);        // 1/7!
     p = __builtin_fma(-D, p, 1.0 / 720.0);         // 1/6!
@@ -203,7 +165,7 @@ __device__ __forceinline__ void kernel_moments(double D, double &ex, double &e0,
         ex = 1.0 - e0;
         return;
     }
-    ex = FULL ? exp_neg(D) : exp_neg_single(D);
+    ex = exp_neg(D);
     e0 = 1.0 - ex;
     e1 = D - e0;
     e2 = __builtin_fma(D, D, -2.0 * e1);
@@ -230,34 +192,14 @@ struct PointW {
 };
 
 // FULL: double-accurate moments (the default for double results); false: the
-// shorter forms that suffice for single-precision results (SPLIT: their
-// two-branch variant).  LIMIT: linear points by the parabolic formulas with
-// the downwind step replaced by 2^300, as in point_weights_pos (DLIN: also
-// the linear diagonal e1/D, else dlin is left zero).
-template <typename T, bool FULL = sizeof(T) == 8, bool SPLIT = false, bool LIMIT = false, bool DLIN = true>
+// shorter forms that suffice where the results are rounded to single precision.
+template <typename T, bool FULL = sizeof(T) == 8>
 __device__ __forceinline__ PointW<T> point_weights(double D, double Dp, bool last)
 {
     const double Dv = D < kMinStep ? kMinStep : D;  // NaN propagates
     double ex, e0, e1, e2;
-    kernel_moments<FULL, SPLIT>(Dv, ex, e0, e1, e2);
+    kernel_moments<FULL>(Dv, ex, e0, e1, e2);
     const double Dq = Dp < kMinStep ? Dv : Dp;   // keeps r finite on last/vacuum points; NaN propagates
-    if constexpr (LIMIT) {
-        const double h = __builtin_fma(Dv, e1, -e2);  // D e1 - e2
-        const bool lin = last || (Dp < 0.5 * D) || (Dp * e0 <= h);
-        const double Dl = lin ? 0x1p300 : Dq;
-        const double Ds = Dv + Dl;
-        const double r = rcp_f64<FULL>(Dv * Dl * Ds);
-        const double b = __builtin_fma(Ds, e1, -e2) * (Ds * r);
-        const double g = h * (-Dv * r);
-        PointW<T> w;
-        w.ex = T(ex);
-        w.b = T(b);
-        w.g = T(g);
-        w.a = T(e0 - b - g);
-        w.dlin = T(0);
-        if constexpr (DLIN) w.dlin = T(e1 * rcp_f64<FULL>(Dv));
-        return w;
-    }
     const double Ds = Dv + Dq;
     const double r = rcp_f64<FULL>(Dv * Dq * Ds);
     const double bl = e1 * ((Dq * Ds) * r);      // e1 / D
@@ -282,7 +224,7 @@ __device__ __forceinline__ PointW<T> point_weights(double D, double Dp, bool las
 
 // point_weights for optical steps that are already at least kMinStep (sums of
 // half_depth): no clamping here.  LAST: the final point of a ray (linear
-// weights; Dp is not read).  DLIN: also the linear operator's diagonal e1/D.
+// weights; Dp is not read); `last` says the same per lane (Dp any step).  DLIN: also the linear operator's diagonal e1/D.
 // The linear weights are the parabolic ones in the limit of an infinite
 // downwind step.  Double results: a point that takes them is evaluated with Dp
 // replaced by 2^300 (beta = e1/D (1 + O(D/2^300)), gamma far below the rounding
@@ -291,7 +233,7 @@ __device__ __forceinline__ PointW<T> point_weights(double D, double Dp, bool las
 // of one word; D D'(D + D') stays finite for every D below 2^340, and float
 // opacities give steps below 2^140.
 template <typename T, bool LAST, bool DLIN = true>
-__device__ __forceinline__ PointW<T> point_weights_pos(double D, double Dp)
+__device__ __forceinline__ PointW<T> point_weights_pos(double D, double Dp, bool last = false)
 {
     constexpr bool FULL = sizeof(T) == 8;
     PointW<T> w;
@@ -301,7 +243,7 @@ __device__ __forceinline__ PointW<T> point_weights_pos(double D, double Dp)
         double e2;
         kernel_moments<true>(D, ex, e0, e1, e2);
         const double h = __builtin_fma(D, e1, -e2);  // D e1 - e2
-        const bool lin = LAST || (Dp < 0.5 * D) || (Dp * e0 <= h);
+        const bool lin = LAST || last || (Dp < 0.5 * D) || (Dp * e0 <= h);
         const double Dq = lin ? 0x1p300 : Dp;
         const double Ds = D + Dq;
         const double r = rcp_f64<true>(D * Dq * Ds);
@@ -328,7 +270,7 @@ __device__ __forceinline__ PointW<T> point_weights_pos(double D, double Dp)
             w.a = T(e0 - b);
             return w;
         }
-        const bool lin = (Dp < 0.5 * D) || (Dp * e0 <= h);
+        const bool lin = last || (Dp < 0.5 * D) || (Dp * e0 <= h);
         const double Ds = D + Dp;
         const double r = __builtin_amdgcn_rcp(D * Dp * Ds);
         // linear points: h = 0 in b = (h + D' e1) / (D D'), g = -h / (D' (D + D'))
@@ -359,7 +301,7 @@ __device__ __forceinline__ double half_depth(double chi, double s_half)
     return d;
 }
 
-// The same sum in the sweep's order, without contraction.
+// The step between two half depths, without contraction.
 __device__ __forceinline__ double step_of(double ha, double hb)
 {
 #pragma clang fp contract(off)
@@ -367,12 +309,12 @@ __device__ __forceinline__ double step_of(double ha, double hb)
 }
 
 // Entry half-segment: constant S from the entry point to the first point.
-template <typename T, bool SPLIT = false>
+template <typename T>
 __device__ __forceinline__ void entry_weights(double D0, T &ex_t, T &e0_t)
 {
     constexpr bool FULL = sizeof(T) == 8;
     double ex, e0, e1, e2;
-    kernel_moments<FULL, SPLIT>(D0 < kMinStep ? kMinStep : D0, ex, e0, e1, e2);
+    kernel_moments<FULL>(D0 < kMinStep ? kMinStep : D0, ex, e0, e1, e2);
     ex_t = T(ex);
     e0_t = T(e0);
 }

@@ -494,16 +494,16 @@ __global__ void __launch_bounds__(256) lstar_stencil_sphere_kernel(SphereStencil
     };
 
     set(1, a.vox[e0]);
-    double t_cur = seg_depth((double)chi[vv[1]], (double)sv[e0]);
+    double t_cur = half_seg((double)chi[vv[1]], (double)sv[e0]);
     double t_nxt = 0.0;
     if (len > 1) {
         set(0, a.vox[e0 + 64]);
-        t_nxt = seg_depth((double)chi[vv[0]], (double)sv[e0 + 64]);
+        t_nxt = half_seg((double)chi[vv[0]], (double)sv[e0 + 64]);
     }
     double Gv[5] = {0.0, 0.0, 0.0, 0.0, 0.0};  // G_-1, G_0, G_1, G_2, G_3
     {
         double ex0, e00;
-        entry_weights<double>(0.5 * t_cur, ex0, e00);
+        entry_weights<double>(t_cur, ex0, e00);
         Gv[1] = e00;
         add((double)wv[e0], Gv);
     }
@@ -519,12 +519,12 @@ __global__ void __launch_bounds__(256) lstar_stencil_sphere_kernel(SphereStencil
         t_cur = t_nxt;
         if (!last) {
             set(0, a.vox[e + 64]);
-            t_nxt = seg_depth((double)chi[vv[0]], (double)sv[e + 64]);
+            t_nxt = half_seg((double)chi[vv[0]], (double)sv[e + 64]);
         } else {
             vv[0] = -1;
         }
-        const double D = half_sum(t_prev, t_cur);
-        const double Dp = last ? 0.0 : half_sum(t_cur, t_nxt);
+        const double D = step_of(t_prev, t_cur);
+        const double Dp = last ? 0.0 : step_of(t_cur, t_nxt);
         double ex, wa, wb, wg;
         if (PARA) {
             const PointW<double> pw = point_weights<double, sizeof(G) == 8>(D, Dp, last);
