@@ -15,9 +15,16 @@ template <typename TS, typename TD>
 hipError_t pad_field(const TS *src, const double *anchor, TD *dst, int Nx, int Ny, int Nz, int n_lambda, int comp,
                      hipStream_t st);
 
+// Both components of formal-solution inputs in the same layouts.
+template <typename T>
+hipError_t pad_pair(const T *chi, const T *S, T *dst, int Nx, int Ny, int Nz, int n_lambda, hipStream_t st);
+
+// Sums of the partial slots; with part2 also those of a second output, in the
+// same launch.  one_slot: every batch entry has a single slot (sphere).
 template <typename TP, typename TO>
 hipError_t reduce_partials(const TP *part, const int32_t *slot_begin, const int32_t *slot_ids,
-                           const int32_t *lambda_of, int n_batch, TO *out, int64_t n_vox, hipStream_t st);
+                           const int32_t *lambda_of, int n_batch, TO *out, int64_t n_vox, hipStream_t st,
+                           bool one_slot = false, const TP *part2 = nullptr, TO *out2 = nullptr);
 
 template <typename G, typename TN>
 hipError_t source_update(const double *J, const G *eps, const G *B, double *S, const double *S_anchor, TN *next_pad,
@@ -50,6 +57,7 @@ struct AliUpdateArgs {
     const void *part;           // partial slots of the formal solution, or null
     const int32_t *slot_begin;  // per batch entry
     const int32_t *slot_ids;
+    bool one_slot;              // a single slot per batch entry (sphere)
     const double *J_anchor;     // double-precision anchor J_fs(S_anchor), or null
     const double *S_anchor;     // anchor source, or null
     const void *eps, *B, *lstar;  // grid precision

@@ -153,6 +153,7 @@ static rt_status plain_step_launches(rt_grid *g, rt_state *s, const std::vector<
     }
     ua.slot_begin = sc->slot_begin.as<int32_t>();
     ua.slot_ids = sc->slot_ids.as<int32_t>();
+    ua.one_slot = g->sphere;
     return os_update(g, nl, ua, g->dbl, g->dbl, g->dbl, nb, sweeps, st);
 }
 
@@ -380,6 +381,7 @@ static rt_status ali_step_batch(rt_grid *g, rt_state *s, const rt_solve_opts *o,
         ua.part = g->partJ64.p;
         ua.slot_begin = sc->slot_begin.as<int32_t>();
         ua.slot_ids = sc->slot_ids.as<int32_t>();
+        ua.one_slot = g->sphere;
         rs = join_stencil();
         if (rs != RT_OK) return rs;
         rs = os_update(g, nl, ua, true, true, true, nb, sweeps, st);
@@ -430,6 +432,7 @@ static rt_status ali_step_batch(rt_grid *g, rt_state *s, const rt_solve_opts *o,
             ua.part = nullptr;
             ua.slot_begin = sc->slot_begin.as<int32_t>();
             ua.slot_ids = sc->slot_ids.as<int32_t>();
+            ua.one_slot = g->sphere;
             rs = join_stencil();
             if (rs != RT_OK) return rs;
             rs = os_update(g, nl, ua, false, false, false, nb, sweeps, st);
@@ -445,6 +448,7 @@ static rt_status ali_step_batch(rt_grid *g, rt_state *s, const rt_solve_opts *o,
             ua.part = g->partJ.p;
             ua.slot_begin = sc->slot_begin.as<int32_t>();
             ua.slot_ids = sc->slot_ids.as<int32_t>();
+            ua.one_slot = g->sphere;
             rs = join_stencil();
             if (rs != RT_OK) return rs;
             rs = os_update(g, nl, ua, false, false, false, nb, sweeps, st);

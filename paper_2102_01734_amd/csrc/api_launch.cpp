@@ -497,13 +497,10 @@ static rt_status autotune(rt_grid *g, int32_t n_lambda, const void *chi, const v
     const bool dbl = g->dbl;
     const int Nx = g->geo.Nx, Ny = g->geo.Ny, Nz = g->geo.Nz;
     HIPCHK(g->fs_fld.ensure(8 * (size_t)n_lambda * g->n_vox * (dbl ? 8 : 4)));
-    if (dbl) {
-        HIPCHK(pad_field<double, double>((const double *)chi, nullptr, g->fs_fld.as<double>(), Nx, Ny, Nz, n_lambda, 0, st));
-        HIPCHK(pad_field<double, double>((const double *)S, nullptr, g->fs_fld.as<double>(), Nx, Ny, Nz, n_lambda, 1, st));
-    } else {
-        HIPCHK(pad_field<float, float>((const float *)chi, nullptr, g->fs_fld.as<float>(), Nx, Ny, Nz, n_lambda, 0, st));
-        HIPCHK(pad_field<float, float>((const float *)S, nullptr, g->fs_fld.as<float>(), Nx, Ny, Nz, n_lambda, 1, st));
-    }
+    if (dbl)
+        HIPCHK(pad_pair<double>((const double *)chi, (const double *)S, g->fs_fld.as<double>(), Nx, Ny, Nz, n_lambda, st));
+    else
+        HIPCHK(pad_pair<float>((const float *)chi, (const float *)S, g->fs_fld.as<float>(), Nx, Ny, Nz, n_lambda, st));
     std::vector<int32_t> lams(n_lambda);
     for (int i = 0; i < n_lambda; ++i) lams[i] = i;
     const FsShape *sh = nullptr;
@@ -706,13 +703,10 @@ rt_status formal_solution(rt_grid *g, int32_t n_lambda, const void *chi, const v
     const size_t padn = g->sphere ? (size_t)g->desc.n_lambda_max * g->n_vox : (size_t)n_lambda * 4 * g->n_vox;
     const int Nx = g->lx, Ny = g->ly, Nz = g->lz;
     HIPCHK(g->fs_fld.ensure(2 * padn * esz));
-    if (dbl) {
-        HIPCHK(pad_field<double, double>((const double *)chi, nullptr, g->fs_fld.as<double>(), Nx, Ny, Nz, n_lambda, 0, st));
-        HIPCHK(pad_field<double, double>((const double *)S, nullptr, g->fs_fld.as<double>(), Nx, Ny, Nz, n_lambda, 1, st));
-    } else {
-        HIPCHK(pad_field<float, float>((const float *)chi, nullptr, g->fs_fld.as<float>(), Nx, Ny, Nz, n_lambda, 0, st));
-        HIPCHK(pad_field<float, float>((const float *)S, nullptr, g->fs_fld.as<float>(), Nx, Ny, Nz, n_lambda, 1, st));
-    }
+    if (dbl)
+        HIPCHK(pad_pair<double>((const double *)chi, (const double *)S, g->fs_fld.as<double>(), Nx, Ny, Nz, n_lambda, st));
+    else
+        HIPCHK(pad_pair<float>((const float *)chi, (const float *)S, g->fs_fld.as<float>(), Nx, Ny, Nz, n_lambda, st));
     std::vector<int32_t> lams(n_lambda);
     for (int i = 0; i < n_lambda; ++i) lams[i] = i;
     const bool wl = lstar_out != nullptr;
@@ -730,26 +724,23 @@ rt_status formal_solution(rt_grid *g, int32_t n_lambda, const void *chi, const v
             if (rs != RT_OK) return rs;
             if (dbl)
                 HIPCHK(reduce_partials<double, double>(pL.as<double>(), sc->slot_begin.as<int32_t>(), sc->slot_ids.as<int32_t>(),
-                                                       sc->lambda_of.as<int32_t>(), n_lambda, (double *)lstar_out, g->n_vox, st));
+                                                       sc->lambda_of.as<int32_t>(), n_lambda, (double *)lstar_out, g->n_vox, st,
+                                                       g->sphere));
             else
                 HIPCHK(reduce_partials<float, float>(pL.as<float>(), sc->slot_begin.as<int32_t>(), sc->slot_ids.as<int32_t>(),
-                                                     sc->lambda_of.as<int32_t>(), n_lambda, (float *)lstar_out, g->n_vox, st));
+                                                     sc->lambda_of.as<int32_t>(), n_lambda, (float *)lstar_out, g->n_vox, st,
+                                                     g->sphere));
         }
         rs = run_fs(g, dbl, true, false, lams, g->fs_fld.p, I_bc, pJ, pL, &sc, st, subset);
         if (rs != RT_OK) return rs;
     }
-    if (dbl) {
+    if (dbl)
         HIPCHK(reduce_partials<double, double>(pJ.as<double>(), sc->slot_begin.as<int32_t>(), sc->slot_ids.as<int32_t>(),
-                                               sc->lambda_of.as<int32_t>(), n_lambda, (double *)J_out, g->n_vox, st));
-        if (joint)
-            HIPCHK(reduce_partials<double, double>(pL.as<double>(), sc->slot_begin.as<int32_t>(), sc->slot_ids.as<int32_t>(),
-                                                   sc->lambda_of.as<int32_t>(), n_lambda, (double *)lstar_out, g->n_vox, st));
-    } else {
+                                               sc->lambda_of.as<int32_t>(), n_lambda, (double *)J_out, g->n_vox, st, g->sphere,
+                                               joint ? pL.as<double>() : nullptr, (double *)lstar_out));
+    else
         HIPCHK(reduce_partials<float, float>(pJ.as<float>(), sc->slot_begin.as<int32_t>(), sc->slot_ids.as<int32_t>(),
-                                             sc->lambda_of.as<int32_t>(), n_lambda, (float *)J_out, g->n_vox, st));
-        if (joint)
-            HIPCHK(reduce_partials<float, float>(pL.as<float>(), sc->slot_begin.as<int32_t>(), sc->slot_ids.as<int32_t>(),
-                                                 sc->lambda_of.as<int32_t>(), n_lambda, (float *)lstar_out, g->n_vox, st));
-    }
+                                             sc->lambda_of.as<int32_t>(), n_lambda, (float *)J_out, g->n_vox, st, g->sphere,
+                                             joint ? pL.as<float>() : nullptr, (float *)lstar_out));
     return RT_OK;
 }

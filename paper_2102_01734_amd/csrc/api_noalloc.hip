@@ -136,13 +136,10 @@ extern "C" rt_status rt_formal_solution_noalloc(rt_grid_t g, int32_t n_lambda, c
         if (rs != RT_OK) return rs;
     }
     const int Nx = g->lx, Ny = g->ly, Nz = g->lz;
-    if (dbl) {
-        HIPCHK(pad_field<double, double>((const double *)chi, nullptr, (double *)base, Nx, Ny, Nz, n_lambda, 0, st));
-        HIPCHK(pad_field<double, double>((const double *)S, nullptr, (double *)base, Nx, Ny, Nz, n_lambda, 1, st));
-    } else {
-        HIPCHK(pad_field<float, float>((const float *)chi, nullptr, (float *)base, Nx, Ny, Nz, n_lambda, 0, st));
-        HIPCHK(pad_field<float, float>((const float *)S, nullptr, (float *)base, Nx, Ny, Nz, n_lambda, 1, st));
-    }
+    if (dbl)
+        HIPCHK(pad_pair<double>((const double *)chi, (const double *)S, (double *)base, Nx, Ny, Nz, n_lambda, st));
+    else
+        HIPCHK(pad_pair<float>((const float *)chi, (const float *)S, (float *)base, Nx, Ny, Nz, n_lambda, st));
     for (size_t i = 0; i < passes.size(); ++i) {
         const NoAllocPass &p = passes[i];
         const Variant &v = *p.v;
