@@ -55,6 +55,8 @@ rt_status ensure_state_buffers(rt_grid *g)
     HIPCHK(g->ng_coef.ensure(nl * 3 * 8));
     HIPCHK(g->resid.ensure(nl * 8));
     if (g->nonlocal) {
+        rt_status rs = ensure_near_tables(g);
+        if (rs != RT_OK) return rs;
         HIPCHK(g->nl_st.ensure(nl * kStencil * nv * esz));
         HIPCHK(g->os_r.ensure(nl * nv * 8));
         HIPCHK(g->os_x0.ensure(nl * nv * 8));

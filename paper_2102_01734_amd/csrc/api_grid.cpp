@@ -520,6 +520,7 @@ rt_status rt_create_grid(const rt_grid_desc *desc, rt_grid_t *out)
     }
     if (const char *e = std::getenv("RT3D_STENCIL_PER_CHARACTERISTIC"))
         if (e[0] == '1') g->nl_rows = false;
+    if (g->para || !g->nl_rows) g->nl_near = -1;
 
     // whole-layer tiles where they fit, else (or when asked for) band tiles
     auto setup_all = [&]() {

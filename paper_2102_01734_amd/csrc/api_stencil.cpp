@@ -4,6 +4,24 @@
 
 using namespace rt3d;
 
+// Tables of the voxel-wise kernel: about 16 bytes per visit, made on first use.
+rt_status ensure_near_tables(rt_grid *g)
+{
+    if (g->sphere || g->nl_near != 0) return RT_OK;
+    std::vector<NearVisit> visits;
+    std::vector<int32_t> begin;
+    if (!near_stencil_tables(g->geo, visits, begin)) {
+        g->nl_near = -1;
+        return RT_OK;
+    }
+    HIPCHK(g->nl_visits.ensure(visits.size() * sizeof(NearVisit)));
+    HIPCHK(g->nl_begin.ensure(begin.size() * 4));
+    HIPCHK(hipMemcpy(g->nl_visits.p, visits.data(), visits.size() * sizeof(NearVisit), hipMemcpyHostToDevice));
+    HIPCHK(hipMemcpy(g->nl_begin.p, begin.data(), begin.size() * 4, hipMemcpyHostToDevice));
+    g->nl_near = 1;
+    return RT_OK;
+}
+
 // Nearest-neighbour Lambda* of the batch from the caller's opacity, in two
 // parts: clear the fixed-point sums and accumulate every characteristic
 // (without the centre component when skip_centre), then convert into `out`
@@ -60,6 +78,12 @@ rt_status accumulate_stencil(rt_grid *g, const void *chi, int n_lambda, int nb, 
         a.brow = g->brow.as<int32_t>();
         a.dir_plane = g->nl_planes.as<int32_t>() + (size_t)(skip_centre ? 1 : 0) * g->n_dir * kPlaneStride;
         a.planes = g->nl_np[skip_centre ? 1 : 0];
+    }
+    rt_status rs = ensure_near_tables(g);
+    if (rs != RT_OK) return rs;
+    if (g->nl_near > 0) {
+        a.near_visits = g->nl_visits.as<NearVisit>();
+        a.near_begin = g->nl_begin.as<int32_t>();
     }
     HIPCHK(lstar_stencil_accumulate(a, g->dbl, g->para, g->n_dir, nb, g->max_lds, st));
     return RT_OK;

@@ -118,9 +118,8 @@ __device__ __forceinline__ void moments_single(double D, double &ex, double &e0,
     const double r2 = r * r;
     const double h = __builtin_fma(-r, P, 0.5);  // u = r^2 h
     if (n == 0.0) {
-        const double u = r2 * h;
-        e1 = u;
-        e0 = D - u;
+        e1 = r2 * h;
+        e0 = __builtin_fma(-r2, h, D);  // spelled out, as below: kernels that share the moments agree to the bit
         ex = 1.0 - e0;
         e2 = WANT_H ? (D * r2) * __builtin_fma(-2.0, P, h) : (2.0 * r2) * (r * P);
     } else {
@@ -159,9 +158,10 @@ __device__ __forceinline__ void kernel_moments(double D, double &ex, double &e0,
     p = __builtin_fma(-D, p, 1.0 / 6.0);           // 1/3!
     const double D2 = D * D;
     if (D < 0.25) {
-        e2 = 2.0 * D2 * D * p;
-        e1 = 0.5 * (D2 - e2);
-        e0 = D - e1;
+        const double c = (D2 + D2) * D, u = __builtin_fma(-c, p, D2);
+        e2 = c * p;
+        e1 = 0.5 * u;
+        e0 = __builtin_fma(-0.5, u, D);
         ex = 1.0 - e0;
         return;
     }

@@ -154,4 +154,61 @@ std::string build_box_geometry(int Nx, int Ny, int Nz, int n_mu, int n_phi, BoxG
     return std::string();
 }
 
+bool near_stencil_tables(const BoxGeometry &g, std::vector<NearVisit> &visits, std::vector<int32_t> &begin)
+{
+    if (g.di.size() > (size_t)INT32_MAX) return false;
+    int place[5][5][5] = {};
+    for (int p = 0; p < kNearVoxels; ++p) place[kNearSteps[p][0]][kNearSteps[p][1]][kNearSteps[p][2]] = p;
+    std::vector<NearVisit> raw(g.di.size());
+    std::vector<int32_t> key(g.di.size());  // (layer * 8 + octant) * kinds + kind
+    begin.assign((size_t)g.Nz * 8 * (kNearKinds + 1), 0);
+    for (const Direction &dir : g.dirs) {
+        const int32_t *di = g.di.data() + dir.vbegin, *dj = g.dj.data() + dir.vbegin;
+        const uint32_t *dxy = g.dxy.data() + dir.vbegin;
+        const int sx = di[dir.M - 1] < di[0] ? -1 : 1, sy = dj[dir.M - 1] < dj[0] ? -1 : 1;
+        const int octant = (sx < 0 ? 1 : 0) + (sy < 0 ? 2 : 0) + (dir.mu < 0.0 ? 0 : 4);
+        int axis[4] = {0, 0, 0, 0};  // of the last four steps, latest first
+        int t = 0;
+        for (int m = 0; m < dir.M; ++m) {
+            if (m > 0) {
+                const int dx = sx * (di[m] - di[m - 1]), dy = sy * (dj[m] - dj[m - 1]);
+                const int dz = (dxy[m - 1] & kLayerEnd) ? 1 : 0;
+                if (dx < 0 || dy < 0 || dx + dy + dz != 1) return false;
+                axis[3] = axis[2];
+                axis[2] = axis[1];
+                axis[1] = axis[0];
+                axis[0] = dx ? 0 : dy ? 1 : 2;
+            }
+            const bool edge = m >= 2 && axis[1] != axis[0];
+            const bool corner = m >= 3 && edge && axis[2] != axis[0] && axis[2] != axis[1];
+            const int need = corner ? 4 : edge ? 3 : 2;  // points upstream
+            uint32_t r = (uint32_t)std::min(m, 4) << kNearFirst | (edge ? 1u << kNearEdge : 0u) |
+                         (corner ? 1u << kNearCorner : 0u) | (uint32_t)axis[0] << kNearFaceAxis |
+                         (uint32_t)axis[1] << kNearEdgeAxis;
+            int st[3] = {};
+            for (int j = 1; j <= need && j <= m; ++j) {
+                ++st[axis[j - 1]];
+                r |= (uint32_t)place[st[0]][st[1]][st[2]] << (5 * (j - 1));
+            }
+            const int second = axis[1] > axis[0] ? axis[1] - 1 : axis[1];  // of the two other axes
+            const int kind = m < need ? kNearEntry : axis[0] * 5 + (edge ? 1 + 2 * second + (corner ? 1 : 0) : 0);
+            const size_t i = (size_t)dir.vbegin + m;
+            raw[i] = NearVisit{r, (int32_t)i, dir.w * std::fabs(dir.mu)};
+            key[i] = (t * 8 + octant) * (kNearKinds + 1) + kind;
+            ++begin[(size_t)key[i]];
+            if (dxy[m] & kLayerEnd) ++t;
+        }
+    }
+    int32_t sum = 0;
+    for (int32_t &b : begin) {
+        const int32_t n = b;
+        b = sum;
+        sum += n;
+    }
+    visits.resize(raw.size());
+    std::vector<int32_t> at(begin);
+    for (size_t i = 0; i < raw.size(); ++i) visits[(size_t)at[(size_t)key[i]]++] = raw[i];
+    return true;
+}
+
 }  // namespace rt3d

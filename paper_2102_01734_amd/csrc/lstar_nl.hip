@@ -26,7 +26,9 @@
 // contributions arrive.  |sum| <= 1 per element, so 2^52 leaves ample
 // headroom below 2^63.
 //
-// Row-window kernel: a workgroup takes one wavelength, one direction and a
+// The linear operator has a kernel that goes by voxels (below).
+//
+// Row-window kernel (parabolic operator): a workgroup takes one wavelength, one direction and a
 // bundle of H consecutive ray rows (all Nx rays of each row), its rays in
 // lockstep.  At visit m every ray of bundle row yr adds to target row
 // yr + brow_m of the current layer (brow: the visit's row above the lowest
@@ -56,6 +58,20 @@ __device__ __forceinline__ double half_seg(double chi, double s_half) { return s
 // One contribution w G in fixed point, round(w G 2^52) as a signed 64-bit
 // integer (ties to even).
 __device__ __forceinline__ long long fix52(double cw52, double G) { return __double2ll_rn(cw52 * G); }
+
+// Weights of the linear operator over the step of half depths ta, tb.
+template <bool FULL>
+__device__ __forceinline__ void linear_weights(double ta, double tb, double &ex, double &wa, double &wb)
+{
+#pragma clang fp contract(off)
+    const double D = step_of(ta, tb);
+    const double Dv = D < kMinStep ? kMinStep : D;
+    double e0, e1, e2;
+    kernel_moments<FULL>(Dv, ex, e0, e1, e2);
+    const double r = rcp_f64<FULL>(Dv);
+    wb = e1 * r;
+    wa = __builtin_fma(-e1, r, e0);
+}
 
 template <typename G, bool PARA>
 __global__ void __launch_bounds__(256) lstar_stencil_kernel(StencilArgs a)
@@ -140,17 +156,13 @@ __global__ void __launch_bounds__(256) lstar_stencil_kernel(StencilArgs a)
             const PointW<double> pw = point_weights<double, sizeof(G) == 8>(D, Dp, last);
             ex = pw.ex; wa = pw.a; wb = pw.b; wg = pw.g;
         } else {
-            const double Dv = D < kMinStep ? kMinStep : D;
-            double e0, e1, e2;
-            kernel_moments<sizeof(G) == 8>(Dv, ex, e0, e1, e2);
-            wb = e1 * rcp_f64<sizeof(G) == 8>(Dv);
-            wa = e0 - wb;
+            linear_weights<sizeof(G) == 8>(t_prev, t_cur, ex, wa, wb);
             wg = 0.0;
         }
         Gv[4] = ex * Gv[3];
         Gv[3] = ex * Gv[2];
-        Gv[2] = ex * Gv[1] + wa;
-        Gv[1] = ex * Gv[0] + wb;
+        Gv[2] = __builtin_fma(ex, Gv[1], wa);
+        Gv[1] = __builtin_fma(ex, Gv[0], wb);
         Gv[0] = wg;
         add(v_cur, wmu * sv[m], comp[m], Gv);
     }
@@ -158,7 +170,7 @@ __global__ void __launch_bounds__(256) lstar_stencil_kernel(StencilArgs a)
 
 constexpr int kFlushWords = 4;
 
-template <typename G, bool PARA, int R>
+template <typename G, int R>
 __global__ void __launch_bounds__(1024) lstar_stencil_rows_kernel(StencilArgs a)
 {
     extern __shared__ unsigned long long tile[];  // [plane][H + 1 circular rows][Nx]
@@ -252,7 +264,6 @@ __global__ void __launch_bounds__(1024) lstar_stencil_rows_kernel(StencilArgs a)
         for (int r = 0; r < R; ++r) word[r] = slot[r] * Nx + x_cur[r];
 #pragma unroll
         for (int j = 0; j < 5; ++j) {
-            if (!PARA && j == 0) continue;  // no downwind weight in the linear operator
             const uint32_t c = (comps >> (6 * j)) & 63u;
             if (c == kNoComp) continue;
             const int p = plane_of[c];
@@ -349,18 +360,8 @@ __global__ void __launch_bounds__(1024) lstar_stencil_rows_kernel(StencilArgs a)
             }
             const double D = step_of(t_prev, t_cur[r]);
             const double Dp = last ? 0.0 : step_of(t_cur[r], t_nxt[r]);
-            double ex, wa, wb, wg;
-            if (PARA) {
-                const PointW<double> pw = point_weights<double, sizeof(G) == 8>(D, Dp, last);
-                ex = pw.ex; wa = pw.a; wb = pw.b; wg = pw.g;
-            } else {
-                const double Dv = D < kMinStep ? kMinStep : D;
-                double e0, e1, e2;
-                kernel_moments<sizeof(G) == 8>(Dv, ex, e0, e1, e2);
-                wb = e1 * rcp_f64<sizeof(G) == 8>(Dv);
-                wa = e0 - wb;
-                wg = 0.0;
-            }
+            const PointW<double> pw = point_weights<double, sizeof(G) == 8>(D, Dp, last);
+            const double ex = pw.ex, wa = pw.a, wb = pw.b, wg = pw.g;
             Gv[r][4] = ex * Gv[r][3];
             Gv[r][3] = ex * Gv[r][2];
             Gv[r][2] = ex * Gv[r][1] + wa;
@@ -371,6 +372,220 @@ __global__ void __launch_bounds__(1024) lstar_stencil_rows_kernel(StencilArgs a)
         advance(m);
         if (!last) br_cur = brow[m + 1];
     }
+}
+
+// ---------------------------------------------------------------------------
+// Voxel-wise kernel of the linear operator.  Without a downwind weight G_j of a
+// visit depends on the opacities of at most four points upstream,
+//   G_0 = b_m,  G_1 = ex_m b_{m-1} + a_m,  G_2 = ex_m (ex_{m-1} b_{m-2} + a_{m-1}),
+//   G_3 = ex_m ex_{m-1} (ex_{m-2} b_{m-3} + a_{m-2}),
+// so a voxel can form its row of the operator by itself, from the visits that a
+// template makes in its layer.  All directions of an octant reach the same eight
+// components: their sums stay in registers, and a voxel's 20 opacities upstream
+// are read once, into LDS.  A lane is a voxel, a wavefront 64 voxels of a layer,
+// so the visit records are scalar; they are sorted by the components they reach,
+// which leaves no branch in the loops.  Weights are formed two to four times per
+// visit instead of once, but a workgroup per direction and rows of rays (as the
+// parabolic operator still has it) added to memory, atomically, for every
+// direction, component and voxel: 2e9 atomics on 97 x 97 x 65 x 256 directions,
+// 8.0 ms; here 6e7.  Contributions are the same numbers, and so are the
+// fixed-point sums.  Measured there, single: 8.0 -> 3.4 ms (branching by
+// component in one loop over directions 4.6 ms); 65^3 x 512 directions
+// 10.6 -> 5.0 ms.
+// ---------------------------------------------------------------------------
+// round(w G 2^52) added to a sum, for 0 <= w G <= 1/2 (w_d |mu_d| s_m is at most
+// the weight of a direction): adding 3 2^51 leaves the integer in the low bits.
+__device__ __forceinline__ void add_fix52(unsigned long long &acc, double cw52, double G)
+{
+#pragma clang fp contract(off)
+    const double p = cw52 * G;
+    acc += (unsigned long long)__double_as_longlong(p + 0x1.8p52) - 0x4338000000000000ull;
+}
+
+template <bool FINITE>
+__device__ __forceinline__ void add_near(unsigned long long &acc, double cw52, double Gv)
+{
+    if constexpr (FINITE) add_fix52(acc, cw52, Gv);
+    else acc += (unsigned long long)fix52(cw52, Gv);
+}
+
+// The visits [i, end) of one kind, whose stencil depends on N points upstream
+// (2: face, 3: edge, 4: corner).  Scalar records and LDS opacities are read a
+// visit ahead.
+template <typename G, bool FINITE, int N>
+__device__ __forceinline__ void near_kind(const StencilArgs &a, const G *tile, double chi0, int i, int end,
+                                          unsigned long long &c, unsigned long long &f, unsigned long long &e,
+                                          unsigned long long &k)
+{
+    constexpr bool FULL = sizeof(G) == 8;
+    if (i >= end) return;
+    struct Visit {
+        double s[N + 1], w;
+        G chi[N];
+    } cur, nxt;
+    auto read = [&](Visit &v, const NearVisit &r) {
+        v.w = r.w;
+#pragma unroll
+        for (int j = 0; j <= N; ++j) v.s[j] = a.s[r.m - j];
+#pragma unroll
+        for (int j = 1; j <= N; ++j) v.chi[j - 1] = tile[((r.bits >> (5 * (j - 1))) & 31u) * 256];
+    };
+    NearVisit r = a.near_visits[i];
+    read(cur, r);
+    r = a.near_visits[min(i + 1, end - 1)];
+    for (;;) {
+        read(nxt, r);
+        r = a.near_visits[min(i + 2, end - 1)];
+        const double cw52 = cur.w * 0x1p53 * cur.s[0];  // the visit table holds half path lengths
+        double t[N + 1], ex[N], wa[N], wb[N];
+        t[0] = half_seg(chi0, cur.s[0]);
+#pragma unroll
+        for (int j = 1; j <= N; ++j) t[j] = half_seg((double)cur.chi[j - 1], cur.s[j]);
+#pragma unroll
+        for (int j = 0; j < N; ++j) linear_weights<FULL>(t[j + 1], t[j], ex[j], wa[j], wb[j]);
+        add_near<FINITE>(c, cw52, wb[0]);
+        add_near<FINITE>(f, cw52, __builtin_fma(ex[0], wb[1], wa[0]));
+        if constexpr (N >= 3) add_near<FINITE>(e, cw52, ex[0] * __builtin_fma(ex[1], wb[2], wa[1]));
+        if constexpr (N >= 4) add_near<FINITE>(k, cw52, ex[0] * (ex[1] * __builtin_fma(ex[2], wb[3], wa[2])));
+        if (++i >= end) break;
+        cur = nxt;
+    }
+}
+
+// A visit whose stencil begins at its characteristic's first point, where G_0 is
+// 1 - exp of the entry half-segment: G_0 ... G_3 as far as they reach a neighbour.
+template <typename G>
+__device__ __forceinline__ void near_entry(const StencilArgs &a, const G *tile, double chi0, const NearVisit &r,
+                                           double (&Gv)[4])
+{
+    constexpr bool FULL = sizeof(G) == 8;
+    const int n = (int)((r.bits >> kNearFirst) & 7u);  // points upstream
+    auto depth = [&](int j) {
+        return half_seg((double)tile[((r.bits >> (5 * (j - 1))) & 31u) * 256], a.s[r.m - j]);
+    };
+    auto start = [](double t) {
+        double ex, e0;
+        entry_weights<double>(t, ex, e0);
+        return e0;
+    };
+    const double t0 = half_seg(chi0, a.s[r.m]);
+    if (n == 0) {
+        Gv[0] = start(t0);
+        return;
+    }
+    double ex0, a0, ex1 = 0.0, a1 = 0.0, ex2 = 0.0, a2 = 0.0, b, t2 = 0.0, t3 = 0.0;
+    const double t1 = depth(1);
+    linear_weights<FULL>(t1, t0, ex0, a0, b);
+    Gv[0] = b;
+    if (n == 1) b = start(t1);
+    else linear_weights<FULL>(t2 = depth(2), t1, ex1, a1, b);
+    Gv[1] = __builtin_fma(ex0, b, a0);
+    if (!((r.bits >> kNearEdge) & 1u)) return;
+    if (n == 2) b = start(t2);
+    else linear_weights<FULL>(t3 = depth(3), t2, ex2, a2, b);
+    Gv[2] = ex0 * __builtin_fma(ex1, b, a1);
+    if (!((r.bits >> kNearCorner) & 1u)) return;
+    Gv[3] = ex0 * (ex1 * __builtin_fma(ex2, start(t3), a2));  // n = 3: more points are another kind
+}
+
+template <typename G, bool FINITE>
+__device__ __forceinline__ void near_octant(const StencilArgs &a, const G *tile, double chi0, int t, int o, int part,
+                                            int n_split, unsigned long long *__restrict__ acc)
+{
+    const int s[3] = {(o & 1) ? -1 : 1, (o & 2) ? -1 : 1, (o & 4) ? -1 : 1};
+    const int32_t *__restrict__ begin = a.near_begin + (t * 8 + o) * (kNearKinds + 1);
+    auto part_of = [&](int kind, int &lo, int &hi) {
+        const int b = begin[kind], n = begin[kind + 1] - b;
+        lo = b + (int)((int64_t)n * part / n_split);
+        hi = b + (int)((int64_t)n * (part + 1) / n_split);
+    };
+    auto put = [&](unsigned long long sum, int dx, int dy, int dz) {
+        const int c = (1 - s[2] * dz) * 9 + (1 - s[1] * dy) * 3 + (1 - s[0] * dx);
+        if (sum != 0ull) atomicAdd(&acc[(int64_t)c * a.n_vox], sum);
+    };
+    unsigned long long c = 0, k = 0;
+    int lo, hi;
+#pragma unroll 1
+    for (int f = 0; f < 3; ++f) {
+        unsigned long long face = 0, none = 0;
+        part_of(5 * f, lo, hi);
+        near_kind<G, FINITE, 2>(a, tile, chi0, lo, hi, c, face, none, none);
+#pragma unroll 1
+        for (int q = 0; q < 2; ++q) {
+            const int e = q + (q >= f ? 1 : 0);
+            unsigned long long edge = 0;
+            part_of(5 * f + 1 + 2 * q, lo, hi);
+            near_kind<G, FINITE, 3>(a, tile, chi0, lo, hi, c, face, edge, none);
+            part_of(5 * f + 2 + 2 * q, lo, hi);
+            near_kind<G, FINITE, 4>(a, tile, chi0, lo, hi, c, face, edge, k);
+            put(edge, f == 0 || e == 0, f == 1 || e == 1, f == 2 || e == 2);
+        }
+        put(face, f == 0, f == 1, f == 2);
+    }
+    part_of(kNearEntry, lo, hi);
+#pragma unroll 1
+    for (int i = lo; i < hi; ++i) {
+        const NearVisit r = a.near_visits[i];
+        double Gv[4] = {0.0, 0.0, 0.0, 0.0};
+        near_entry<G>(a, tile, chi0, r, Gv);
+        const double cw52 = r.w * 0x1p53 * a.s[r.m];
+        add_near<FINITE>(c, cw52, Gv[0]);
+        add_near<FINITE>(k, cw52, Gv[3]);
+        unsigned long long face = 0, edge = 0;
+        add_near<FINITE>(face, cw52, Gv[1]);
+        add_near<FINITE>(edge, cw52, Gv[2]);
+        const int f = (int)((r.bits >> kNearFaceAxis) & 3u), e = (int)((r.bits >> kNearEdgeAxis) & 3u);
+        put(face, f == 0, f == 1, f == 2);
+        put(edge, f == 0 || e == 0, f == 1 || e == 1, f == 2 || e == 2);
+    }
+    if (!a.skip_centre) put(c, 0, 0, 0);
+    put(k, 1, 1, 1);
+}
+
+template <typename G>
+__global__ void __launch_bounds__(256) lstar_stencil_near_kernel(StencilArgs a, int n_split)
+{
+    __shared__ G tile[kNearVoxels * 256];  // a lane reads only what it wrote: no barrier
+    const int Nx = a.Nx, Ny = a.Ny, NxNy = Nx * Ny;
+    const int chunks = (NxNy + 63) / 64;
+    const int wave = (int)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int z = wave / chunks, q = (wave - z * chunks) * 64 + (int)(threadIdx.x & 63);
+    const int o = (int)blockIdx.y / n_split, part = (int)blockIdx.y - o * n_split;
+    if (z >= a.Nz || q >= NxNy) return;
+    const int lam = a.lambda_of[blockIdx.z];
+    const G *__restrict__ chi = reinterpret_cast<const G *>(a.chi) + (int64_t)lam * a.n_vox;
+    const int sx = (o & 1) ? -1 : 1, sy = (o & 2) ? -1 : 1, sz = (o & 4) ? -1 : 1;
+    const int y = q / Nx, x = q - y * Nx;
+    G *mine = tile + threadIdx.x;
+    bool finite = true;
+    G chi0 = G(0);
+#pragma unroll
+    for (int p = 0; p < kNearVoxels; ++p) {
+        int xx = (x - sx * kNearSteps[p][0]) % Nx, yy = (y - sy * kNearSteps[p][1]) % Ny;
+        xx += xx < 0 ? Nx : 0;
+        yy += yy < 0 ? Ny : 0;
+        const int zz = z - sz * kNearSteps[p][2];
+        const G c = zz >= 0 && zz < a.Nz ? chi[((int64_t)zz * Ny + yy) * Nx + xx] : G(0);
+        finite = finite && fabs((double)c) <= 1e100;
+        mine[p * 256] = c;
+        if (p == 0) chi0 = c;
+    }
+    const int t = sz > 0 ? z : a.Nz - 1 - z;  // layer in the direction of travel
+    unsigned long long *__restrict__ acc = a.acc + (int64_t)lam * kStencil * a.n_vox + (int64_t)z * NxNy + q;
+    if (__all(finite)) near_octant<G, true>(a, mine, (double)chi0, t, o, part, n_split, acc);
+    else near_octant<G, false>(a, mine, (double)chi0, t, o, part, n_split, acc);
+}
+
+// Directions of an octant are split over blocks until there are 4096 of them
+// (every block reads the 20 opacities and adds its eight sums to memory).
+template <typename G>
+static hipError_t launch_near(const StencilArgs &a, int n_batch, hipStream_t st)
+{
+    const int64_t waves = (int64_t)a.Nz * (((int64_t)a.Nx * a.Ny + 63) / 64), blocks = (waves + 3) / 4;
+    const int n_split = (int)std::min<int64_t>(64, std::max<int64_t>(1, 4096 / (blocks * 8 * n_batch)));
+    hipLaunchKernelGGL((lstar_stencil_near_kernel<G>), dim3((unsigned)blocks, (unsigned)(8 * n_split), (unsigned)n_batch),
+                       dim3(256), 0, st, a, n_split);
+    return hipGetLastError();
 }
 
 // Tile rows per workgroup for the row-window kernel: about 800 rays (two per
@@ -393,13 +608,13 @@ static int stencil_rows(const StencilArgs &a, size_t max_lds)
     return (a.Ny + nb - 1) / nb;
 }
 
-template <typename G, bool PARA, int R>
+template <typename G, int R>
 static hipError_t launch_rows(const StencilArgs &a, int n_dir, int n_batch, hipStream_t st)
 {
     const int rays = a.rows * a.Nx;
     const int nthr = ((rays + R - 1) / R + 63) / 64 * 64;
     const size_t lds = (size_t)a.planes * (a.rows + 1) * a.Nx * 8;
-    auto k = lstar_stencil_rows_kernel<G, PARA, R>;
+    auto k = lstar_stencil_rows_kernel<G, R>;
     hipError_t e = hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     dim3 grid((unsigned)((a.Ny + a.rows - 1) / a.rows), (unsigned)n_dir, (unsigned)n_batch);
@@ -407,28 +622,24 @@ static hipError_t launch_rows(const StencilArgs &a, int n_dir, int n_batch, hipS
     return hipGetLastError();
 }
 
-template <typename G, bool PARA>
+template <typename G>
 static hipError_t launch_rows_r(const StencilArgs &a, int n_dir, int n_batch, hipStream_t st)
 {
-    if (a.rows * a.Nx <= 512) return launch_rows<G, PARA, 1>(a, n_dir, n_batch, st);
-    return launch_rows<G, PARA, 2>(a, n_dir, n_batch, st);
+    if (a.rows * a.Nx <= 512) return launch_rows<G, 1>(a, n_dir, n_batch, st);
+    return launch_rows<G, 2>(a, n_dir, n_batch, st);
 }
 
 hipError_t lstar_stencil_accumulate(const StencilArgs &a0, bool grid_double, bool parabolic, int n_dir, int n_batch,
                                     size_t max_lds, hipStream_t st)
 {
     if (n_dir <= 0 || n_batch <= 0) return hipSuccess;
-    if (a0.dir_plane && a0.brow) {
+    if (a0.near_visits && !parabolic) return grid_double ? launch_near<double>(a0, n_batch, st) : launch_near<float>(a0, n_batch, st);
+    if (a0.dir_plane && a0.brow && parabolic) {
         StencilArgs a = a0;
         a.rows = a.planes > 0 ? stencil_rows(a, max_lds) : 0;
         if (a.planes == 0) return hipSuccess;  // no component is ever added
-        if (a.rows > 0) {
-            if (grid_double)
-                return parabolic ? launch_rows_r<double, true>(a, n_dir, n_batch, st)
-                                 : launch_rows_r<double, false>(a, n_dir, n_batch, st);
-            return parabolic ? launch_rows_r<float, true>(a, n_dir, n_batch, st)
-                             : launch_rows_r<float, false>(a, n_dir, n_batch, st);
-        }
+        if (a.rows > 0)
+            return grid_double ? launch_rows_r<double>(a, n_dir, n_batch, st) : launch_rows_r<float>(a, n_dir, n_batch, st);
     }
     const StencilArgs &a = a0;
     const int NxNy = a.Nx * a.Ny;

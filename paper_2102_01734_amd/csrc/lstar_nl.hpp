@@ -6,6 +6,8 @@
 
 #include <cstdint>
 
+#include "rt_internal.hpp"
+
 namespace rt3d {
 
 // Stencil components: c = (dz+1)*9 + (dy+1)*3 + (dx+1) for the neighbour
@@ -45,6 +47,10 @@ struct StencilArgs {
     const int32_t *dir_plane;
     int planes;
     int rows;
+    // voxel-wise kernel of the linear operator (used when near_visits is set): see
+    // near_stencil_tables
+    const NearVisit *near_visits;
+    const int32_t *near_begin;
 };
 
 constexpr int kPlaneStride = 64;

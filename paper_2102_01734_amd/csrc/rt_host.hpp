@@ -164,6 +164,10 @@ struct rt_grid {
     // most one row per visit, one way within a layer (else the per-
     // characteristic kernel is used)
     DevBuf nl_planes;
+    // tables of the voxel-wise stencil kernel (linear operator), made by the first
+    // call that needs them; nl_near: 0 not made yet, 1 made, -1 do not apply
+    DevBuf nl_visits, nl_begin;
+    int nl_near = 0;
     bool os_gs = false;  // the current step's OS sweeps are Gauss-Seidel (set from its options)
     int nl_np[2] = {0, 0};
     bool nl_rows = false;
@@ -320,6 +324,7 @@ rt_status accumulate_stencil(rt_grid *g, const void *chi, int n_lambda, int nb, 
                              bool skip_centre, hipStream_t st);
 rt_status finish_stencil(rt_grid *g, int nb, const int32_t *lambda_of, const void *centre, void *out,
                          bool out_double, hipStream_t st);
+rt_status ensure_near_tables(rt_grid *g);
 rt_status compute_stencil(rt_grid *g, const void *chi, int n_lambda, int nb, const int32_t *lambda_of, void *out,
                           bool out_double, hipStream_t st);
 

@@ -21,6 +21,39 @@ constexpr int kMaxSide = 1 << kOffBits;
 // that point's voxel seen from the voxel of point m), kNoComp if none.
 constexpr uint32_t kNoComp = 63;
 
+// Voxels that the points m, m-1, ... m-4 upstream of a visit can lie in, as far
+// as the visit's linear stencil depends on them, in steps along the direction's
+// octant (x, y, z): the voxel itself and its three faces, everything two steps
+// away, three steps away past an edge neighbour, four past the corner.
+constexpr int kNearVoxels = 20;
+constexpr int8_t kNearSteps[kNearVoxels][3] = {
+    {0, 0, 0}, {1, 0, 0}, {0, 1, 0}, {0, 0, 1}, {2, 0, 0}, {0, 2, 0}, {0, 0, 2}, {1, 1, 0}, {1, 0, 1}, {0, 1, 1},
+    {2, 1, 0}, {1, 2, 0}, {2, 0, 1}, {1, 0, 2}, {0, 2, 1}, {0, 1, 2}, {1, 1, 1}, {2, 1, 1}, {1, 2, 1}, {1, 1, 2}};
+
+// A visit as the voxel-wise stencil kernel reads it: places in kNearSteps of the
+// points m-1 ... m-4 (5 bits each; 0 where not needed), of the edge and corner
+// neighbours reached (kNearEdge: an edge, kNearCorner: also the corner) and of
+// min(m, 4); its place in the visit table; w_d |mu_d|.
+struct NearVisit {
+    uint32_t bits;
+    int32_t m;
+    double w;
+};
+constexpr int kNearEdge = 20, kNearCorner = 21, kNearFirst = 22;
+
+// Kinds of visits: per axis f of the last step, those that reach only the face
+// neighbour, then for the two other axes e (in the order y z, x z, x y) those that
+// reach the edge (f, e), and the corner beyond it; last the visits whose stencil
+// begins at a characteristic's first point (axes in bits 26: f, 28: e).
+constexpr int kNearKinds = 16, kNearEntry = 15;
+constexpr int kNearFaceAxis = 26, kNearEdgeAxis = 28;
+
+// The visits of every layer (in the direction of travel) and octant, sorted by
+// kind: begin[(layer * 8 + octant) * (kNearKinds + 1) + kind].  false when a
+// template steps backwards on an axis (there are no such tables then).
+struct BoxGeometry;
+bool near_stencil_tables(const BoxGeometry &g, std::vector<NearVisit> &visits, std::vector<int32_t> &begin);
+
 // One direction of the angle quadrature and its characteristic template.
 struct Direction {
     double mu = 0, phi = 0, w = 0;
