@@ -59,13 +59,15 @@ __device__ __forceinline__ double half_seg(double chi, double s_half) { return s
 // integer (ties to even).
 __device__ __forceinline__ long long fix52(double cw52, double G) { return __double2ll_rn(cw52 * G); }
 
-// Weights of the linear operator over the step of half depths ta, tb.
-template <bool FULL>
+// Weights of the linear operator over the step of half depths ta, tb (FINITE: no NaN).
+template <bool FULL, bool FINITE = false>
 __device__ __forceinline__ void linear_weights(double ta, double tb, double &ex, double &wa, double &wb)
 {
 #pragma clang fp contract(off)
     const double D = step_of(ta, tb);
-    const double Dv = D < kMinStep ? kMinStep : D;
+    double Dv;
+    if constexpr (FINITE) asm("v_max_f64 %0, %1, %2" : "=v"(Dv) : "v"(D), "s"(kMinStep));
+    else Dv = D < kMinStep ? kMinStep : D;
     double e0, e1, e2;
     kernel_moments<FULL>(Dv, ex, e0, e1, e2);
     const double r = rcp_f64<FULL>(Dv);
@@ -389,9 +391,9 @@ __global__ void __launch_bounds__(1024) lstar_stencil_rows_kernel(StencilArgs a)
 // parabolic operator still has it) added to memory, atomically, for every
 // direction, component and voxel: 2e9 atomics on 97 x 97 x 65 x 256 directions,
 // 8.0 ms; here 6e7.  Contributions are the same numbers, and so are the
-// fixed-point sums.  Measured there, single: 8.0 -> 3.4 ms (branching by
+// fixed-point sums.  Measured there, single: 8.0 -> 3.3 ms (branching by
 // component in one loop over directions 4.6 ms); 65^3 x 512 directions
-// 10.6 -> 5.0 ms.
+// 10.6 -> 4.8 ms.
 // ---------------------------------------------------------------------------
 // round(w G 2^52) added to a sum, for 0 <= w G <= 1/2 (w_d |mu_d| s_m is at most
 // the weight of a direction): adding 3 2^51 leaves the integer in the low bits.
@@ -442,7 +444,7 @@ __device__ __forceinline__ void near_kind(const StencilArgs &a, const G *tile, d
 #pragma unroll
         for (int j = 1; j <= N; ++j) t[j] = half_seg((double)cur.chi[j - 1], cur.s[j]);
 #pragma unroll
-        for (int j = 0; j < N; ++j) linear_weights<FULL>(t[j + 1], t[j], ex[j], wa[j], wb[j]);
+        for (int j = 0; j < N; ++j) linear_weights<FULL, FINITE>(t[j + 1], t[j], ex[j], wa[j], wb[j]);
         add_near<FINITE>(c, cw52, wb[0]);
         add_near<FINITE>(f, cw52, __builtin_fma(ex[0], wb[1], wa[0]));
         if constexpr (N >= 3) add_near<FINITE>(e, cw52, ex[0] * __builtin_fma(ex[1], wb[2], wa[1]));
@@ -828,21 +830,44 @@ __device__ __forceinline__ double os_row(const OsJacobiArgs &a, int64_t base, in
     den = den < os_den_min<G>() ? os_den_min<G>() : den;
     double acc = a.r[base + v];
     if (!first) {
-        for (int c = 0; c < kStencil; ++c) {
-            if (c == kStencilCentre) continue;
-            const double L = (double)st[(int64_t)c * n + v];
-            if (L == 0.0) continue;
-            int ku = k + c / 9 - 1;
-            if (a.per[2]) ku = ku < 0 ? ku + a.Nz : (ku >= a.Nz ? ku - a.Nz : ku);
-            else if (ku < 0 || ku >= a.Nz) continue;
-            int yu = y + (c / 3) % 3 - 1;
-            if (a.per[1]) yu = yu < 0 ? yu + Ny : (yu >= Ny ? yu - Ny : yu);
-            else if (yu < 0 || yu >= Ny) continue;
-            int xu = x + c % 3 - 1;
-            if (a.per[0]) xu = xu < 0 ? xu + Nx : (xu >= Nx ? xu - Nx : xu);
-            else if (xu < 0 || xu >= Nx) continue;
-            const int64_t u = (int64_t)ku * NxNy + (int64_t)yu * Nx + xu;
-            acc += L * (1.0 - (double)eps[u]) * xs[base + u];
+        // all coefficients in flight at once, then the neighbours of a layer
+        // together; a zero coefficient or a neighbour outside adds nothing, also
+        // beside an infinite iterate (a loop that waited for one neighbour at a
+        // time: 24 us on 65^3 voxels in single, now 12 us)
+        G L[kStencil];
+#pragma unroll
+        for (int c = 0; c < kStencil; ++c) L[c] = c == kStencilCentre ? G(0) : st[(int64_t)c * n + v];
+        auto near = [](int i, int d, int N, bool per, bool &in) {
+            const int j = i + d;
+            in = per || (j >= 0 && j < N);
+            return j < 0 ? (per ? j + N : i) : j >= N ? (per ? j - N : i) : j;
+        };
+        bool xi[3], yi[3], zi[3];
+        int xn[3], yn[3], zn[3];
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            xn[d] = near(x, d - 1, Nx, a.per[0] != 0, xi[d]);
+            yn[d] = near(y, d - 1, Ny, a.per[1] != 0, yi[d]);
+            zn[d] = near(k, d - 1, a.Nz, a.per[2] != 0, zi[d]);
+        }
+#pragma unroll
+        for (int z = 0; z < 3; ++z) {
+            G e[9];
+            double xv[9];
+#pragma unroll
+            for (int q = 0; q < 9; ++q) {
+                if (9 * z + q == kStencilCentre) continue;
+                const int64_t u = (int64_t)zn[z] * NxNy + (int64_t)yn[q / 3] * Nx + xn[q % 3];
+                e[q] = eps[u];
+                xv[q] = xs[base + u];
+            }
+#pragma unroll
+            for (int q = 0; q < 9; ++q) {
+                const int c = 9 * z + q;
+                if (c == kStencilCentre) continue;
+                const double sum = acc + (double)L[c] * (1.0 - (double)e[q]) * xv[q];
+                if (L[c] != G(0) && zi[z] && yi[q / 3] && xi[q % 3]) acc = sum;
+            }
         }
     }
     return acc / den;
