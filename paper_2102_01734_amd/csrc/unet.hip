@@ -16,6 +16,7 @@
 // level-0 map is 68 MB.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <memory>
@@ -34,6 +35,14 @@ __device__ __forceinline__ uint16_t f2bf(float f)
     uint32_t u = __float_as_uint(f);
     u += 0x7fffu + ((u >> 16) & 1u);
     return (uint16_t)(u >> 16);
+}
+
+// Two at a time by the conversion instruction, which rounds the same way.
+__device__ __forceinline__ uint32_t f2bf2(float a, float b)
+{
+    typedef float v2f __attribute__((ext_vector_type(2)));
+    typedef __bf16 v2b __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((v2f{a, b}), v2b));
 }
 
 static uint16_t f2bf_host(float f)
@@ -175,14 +184,19 @@ static hipError_t conv_mfma(const ConvArgs &a, int ci, int co, hipStream_t st)
 // no lanes; a wavefront keeps its tiles' sums in registers and walks the k
 // chunks in the plain kernel's order (the sums are the same to the bit), whose
 // weights it reads once per chunk.  Weights are the first operand, so a lane ends
-// up with four consecutive channels of one voxel: 8-byte stores.  Two blocks fit
-// a CU, so what bounds it is latency: the loads of the LDS copy are issued in
-// batches and the operands of the next chunk read ahead (without either: 116 and
-// 285 us).  Measured at 129^3: 16 -> 16 channels 170 -> 97 us, 32 -> 16 channels
-// with the skip 382 -> 190 us; the network 1149 -> 784 us.
+// up with four consecutive channels of one voxel: 8-byte stores.  Two or three
+// blocks fit a CU, so latency and the instructions around the products bound it:
+// the next chunk's operands and the skip map are read ahead, the LDS copy is made
+// by rows whose addresses are scalar, tiles are found by a multiplication (before
+// that 2400 vector instructions a wavefront for 243 matrix ones: 97 and 190 us;
+// without reading ahead 116 and 285 us).  Tiles of other sizes (rows of 22 or
+// 33, two or four layers): 1 to 7 % slower; neighbouring blocks on one XCD, and
+// channels in separate planes against bank conflicts: no change.  Measured at
+// 129^3: 16 -> 16 channels 170 -> 61 us, 32 -> 16 with the skip 382 -> 119 us; the
+// network 1149 -> 539 us.
 template <int CI>
 struct ConvTile {
-    static constexpr int TXM = CI == 16 ? 44 : CI == 32 ? 33 : 22, TY = 4, TZ = CI == 64 ? 2 : 4;
+    static constexpr int TXM = CI == 16 ? 44 : CI == 32 ? 33 : 22, TY = 4, TZ = CI == 32 ? 4 : 2;
     static constexpr int IX = TXM + 2, IY = TY + 2, IZ = TZ + 2;
     static constexpr int kTiles = (TXM * TY * TZ + 15) / 16, kPerWave = (kTiles + 3) / 4;
     static constexpr size_t kBytes = (size_t)IX * IY * IZ * CI * 2;
@@ -222,40 +236,65 @@ __global__ void __launch_bounds__(256, 2) conv_tile_kernel(ConvArgs a, HeadArgs 
     int x0, y0, z0, tx;
     tile_origin(v, C::TXM, C::TY, C::TZ, x0, y0, z0, tx);
     const int tid = threadIdx.x;
-    constexpr int kChunks = CI / 8;  // 16-byte chunks per voxel
-    // every thread's share in a few batches of loads in flight together: one by
-    // one, their latency was most of the kernel
-    constexpr int kN = C::IX * C::IY * C::IZ * kChunks, kPer = (kN + 255) / 256;
-    constexpr int kBatches = (kPer + 13) / 14, U = (kPer + kBatches - 1) / kBatches;
-    for (int k0 = tid; k0 < kN; k0 += 256 * U) {
-        v4u u[U];
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), i = lane & 15, kq = (lane >> 4) * 8;
+    // A wavefront copies whole rows: the row's address is scalar, and a lane's
+    // 16-byte chunks lie at the same places in every row.  All rows' loads are in
+    // flight together (one by one, their latency was most of the kernel).  Rows
+    // and voxels outside the volume: neighbours across the period, zeros beyond
+    // the top or bottom; what lies past the tile feeds only outputs that are not
+    // stored.
+    constexpr int kRow = C::IX * CI * 2, kChunks = kRow / 16, kPer = (kChunks + 63) / 64;  // bytes, chunks a row and lane
+    constexpr int kRows = (C::IY * C::IZ + 3) / 4;  // rows a wavefront
+    {
+        uint32_t at[kPer];
 #pragma unroll
-        for (int n = 0; n < U; ++n) {
-            const int k = k0 + 256 * n;
-            const int c = k % kChunks, q = k / kChunks;
-            const int ix = q % C::IX, r = q / C::IX, iy = r % C::IY, iz = r / C::IY;
-            const int x = x0 + ix - 1, y = y0 + iy - 1, z = z0 + iz - 1;
-            u[n] = v4u{0u, 0u, 0u, 0u};
-            // input of voxels inside the volume: neighbours across the period, none beyond the top or bottom
-            if (k < kN && ix < tx + 2 && x <= v.nx && y <= v.ny && z >= 0 && z < v.nz)
-                u[n] = *reinterpret_cast<const v4u *>(
-                    a.in + (((int64_t)z * v.ny + wrap(y, v.ny)) * v.nx + wrap(x, v.nx)) * CI + 8 * c);
+        for (int n = 0; n < kPer; ++n) {
+            const int k = lane + 64 * n, x = x0 + k / (CI / 8) - 1;
+            at[n] = (uint32_t)((x > v.nx ? 0 : wrap(x, v.nx)) * (CI * 2) + k % (CI / 8) * 16);
+        }
+        v4u u[kRows][kPer];
+#pragma unroll
+        for (int m = 0; m < kRows; ++m) {
+            const int r = wave + 4 * m, y = y0 + r % C::IY - 1, z = z0 + r / C::IY - 1;
+            const bool in_vol = y <= v.ny && z >= 0 && z < v.nz;  // uniform
+            const char *row = reinterpret_cast<const char *>(
+                a.in + (in_vol ? ((int64_t)z * v.ny + wrap(y, v.ny)) * v.nx * CI : 0));
+#pragma unroll
+            for (int n = 0; n < kPer; ++n) {
+                u[m][n] = *reinterpret_cast<const v4u *>(row + at[n]);
+                if (!in_vol) u[m][n] = v4u{0u, 0u, 0u, 0u};
+            }
         }
 #pragma unroll
-        for (int n = 0; n < U; ++n)
-            if (k0 + 256 * n < kN) *reinterpret_cast<v4u *>(in + 16 * (k0 + 256 * n)) = u[n];
+        for (int m = 0; m < kRows; ++m)
+#pragma unroll
+            for (int n = 0; n < kPer; ++n)
+                if ((C::IY * C::IZ % 4 == 0 || wave + 4 * m < C::IY * C::IZ) && lane + 64 * n < kChunks)
+                    *reinterpret_cast<v4u *>(in + (wave + 4 * m) * kRow + (lane + 64 * n) * 16) = u[m][n];
     }
-    const int lane = tid & 63, wave = tid >> 6, i = lane & 15, kq = (lane >> 4) * 8;
     const int P = tx * C::TY * C::TZ;
+    // the lane's voxels (one per tile): LDS offset, place in the volume, whether it is stored
+    const uint32_t inv = (65536u + (uint32_t)tx - 1) / (uint32_t)tx;  // q / tx for q < 1024, tx <= 44
+    static_assert(C::kTiles * 16 < 1024 && C::TXM <= 44, "");
     int base[T];
+    uint32_t place[T];
+    bool store[T];
+    uint2 sk[T][NB];
     v4f acc[T][NB];
 #pragma unroll
     for (int t = 0; t < T; ++t) {
-        const int q = min((wave + 4 * t) * 16 + i, P - 1);
-        const int r = q / tx;
-        base[t] = (((r / C::TY) * C::IY + r % C::TY) * C::IX + q - r * tx) * (2 * CI) + 2 * (kq % CI & (CI == 16 ? 8 : 31));
+        const int q0 = (wave + 4 * t) * 16 + i, q = min(q0, P - 1);
+        const int r = (int)(((uint32_t)q * inv) >> 16), xl = q - r * tx;
+        base[t] = (((r / C::TY) * C::IY + r % C::TY) * C::IX + xl) * (2 * CI) + 2 * (kq % CI & (CI == 16 ? 8 : 31));
+        const int x = x0 + xl, y = y0 + r % C::TY, z = z0 + r / C::TY;
+        store[t] = q0 < P && x < v.nx && y < v.ny && z < v.nz;
+        place[t] = store[t] ? ((uint32_t)z * (uint32_t)v.ny + (uint32_t)y) * (uint32_t)v.nx + (uint32_t)x : 0u;
 #pragma unroll
-        for (int cb = 0; cb < NB; ++cb) acc[t][cb] = v4f{0.f, 0.f, 0.f, 0.f};
+        for (int cb = 0; cb < NB; ++cb) {
+            acc[t][cb] = v4f{0.f, 0.f, 0.f, 0.f};
+            sk[t][cb] = uint2{0u, 0u};
+            if (a.skip) sk[t][cb] = *reinterpret_cast<const uint2 *>(a.skip + (int64_t)place[t] * CO + cb * 16 + kq / 2);
+        }
     }
     __syncthreads();
     // k = 32 j + kq: with 16 channels a chunk spans two taps, else one
@@ -301,32 +340,35 @@ __global__ void __launch_bounds__(256, 2) conv_tile_kernel(ConvArgs a, HeadArgs 
         __builtin_amdgcn_sched_barrier(0);
     }
     // D layout: a lane holds channels 16 cb + kq/2 .. + 3 of voxel i
+    v4f bias[NB], head[NB];
+#pragma unroll
+    for (int cb = 0; cb < NB; ++cb) {
+        bias[cb] = *reinterpret_cast<const v4f *>(a.bias + cb * 16 + kq / 2);
+        head[cb] = hd.w ? *reinterpret_cast<const v4f *>(hd.w + cb * 16 + kq / 2) : v4f{0.f, 0.f, 0.f, 0.f};
+    }
 #pragma unroll
     for (int t = 0; t < T; ++t) {
-        const int q = (wave + 4 * t) * 16 + i;
-        const int r = q / tx, x = x0 + q - r * tx, y = y0 + r % C::TY, z = z0 + r / C::TY;
-        const bool ok = q < P && x < v.nx && y < v.ny && z < v.nz;
-        const int64_t o = ((int64_t)z * v.ny + y) * v.nx + x;
         float dot = 0.f;
 #pragma unroll
         for (int cb = 0; cb < NB; ++cb) {
-            const int co = cb * 16 + kq / 2;
-            uint16_t h[4];
-            uint16_t sk[4] = {0, 0, 0, 0};
-            if (a.skip && ok) *reinterpret_cast<uint64_t *>(sk) = *reinterpret_cast<const uint64_t *>(a.skip + o * CO + co);
+            float val[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                float val = fmaxf(acc[t][cb][e] + a.bias[co + e], 0.f);
-                if (a.skip) val += bf2f(sk[e]);
-                h[e] = f2bf(val);
-                if (hd.w) dot += hd.w[co + e] * bf2f(h[e]);
+                val[e] = fmaxf(acc[t][cb][e] + bias[cb][e], 0.f);
+                if (a.skip) val[e] += bf2f((uint16_t)((e < 2 ? sk[t][cb].x : sk[t][cb].y) >> (16 * (e % 2))));
             }
-            if (ok && !hd.w) *reinterpret_cast<uint64_t *>(a.out + o * CO + co) = *reinterpret_cast<uint64_t *>(h);
+            const uint2 h{f2bf2(val[0], val[1]), f2bf2(val[2], val[3])};
+            if (hd.w) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) dot += head[cb][e] * bf2f((uint16_t)((e < 2 ? h.x : h.y) >> (16 * (e % 2))));
+            } else if (store[t]) {
+                *reinterpret_cast<uint2 *>(a.out + (int64_t)place[t] * CO + cb * 16 + kq / 2) = h;
+            }
         }
         if (hd.w) {  // the four lanes of a voxel hold its channels between them
             dot += __shfl_xor(dot, 16, 64);
             dot += __shfl_xor(dot, 32, 64);
-            if (ok && lane < 16) hd.out[o] = dot + hd.bias[0];
+            if (store[t] && lane < 16) hd.out[place[t]] = dot + hd.bias[0];
         }
     }
 }
@@ -391,43 +433,39 @@ __global__ void __launch_bounds__(256) conv_in_kernel(const float *__restrict__ 
 // linear upsampling by 2 (align corners): fine index o takes the coarse
 // point o/2 (o even) or the mean of (o-1)/2 and (o+1)/2 (o odd); the upper
 // neighbour wraps in x, y and is clamped in z.  One thread per fine voxel
-// and 8 channels (16-byte loads and stores; C is a multiple of 16).
-__global__ void __launch_bounds__(256) upsample_kernel(const uint16_t *__restrict__ in, Vol vc, uint16_t *__restrict__ out,
-                                                       Vol vf, int C)
+// and 8 channels (16-byte loads and stores; C is a multiple of 16), a block per
+// row, so that rows are found without divisions (129^3 x 32 channels: 67 -> 51 us).
+__global__ void __launch_bounds__(1024) upsample_kernel(const uint16_t *__restrict__ in, Vol vc, uint16_t *__restrict__ out,
+                                                        Vol vf, int log_groups)
 {
-    const int groups = C / 8;
-    const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (id >= vf.n() * groups) return;
-    const int c0 = (int)(id % groups) * 8;
-    const int64_t v = id / groups;
-    const int x = (int)(v % vf.nx);
-    const int64_t r = v / vf.nx;
-    const int y = (int)(r % vf.ny);
-    const int z = (int)(r / vf.ny);
-    int xs[2], ys[2], zs[2];
-    xs[0] = x >> 1; xs[1] = (x & 1) ? wrap((x + 1) >> 1, vc.nx) : xs[0];
-    ys[0] = y >> 1; ys[1] = (y & 1) ? wrap((y + 1) >> 1, vc.ny) : ys[0];
-    zs[0] = z >> 1; zs[1] = (z & 1) ? min((z + 1) >> 1, vc.nz - 1) : zs[0];
-    float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    const int groups = 1 << log_groups, C = 8 * groups;
+    const int y = blockIdx.x, ys[2] = {y >> 1, (y & 1) ? wrap((y + 1) >> 1, vc.ny) : y >> 1};
+    for (int z = blockIdx.y; z < vf.nz; z += gridDim.y) {
+        const int zs[2] = {z >> 1, (z & 1) ? min((z + 1) >> 1, vc.nz - 1) : z >> 1};
+        for (int i = threadIdx.x; i < vf.nx * groups; i += blockDim.x) {
+            const int x = i >> log_groups, c0 = (i & (groups - 1)) * 8;
+            const int xs[2] = {x >> 1, (x & 1) ? wrap((x + 1) >> 1, vc.nx) : x >> 1};
+            float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+            for (int a = 0; a < 2; ++a)
 #pragma unroll
-        for (int b = 0; b < 2; ++b)
+                for (int b = 0; b < 2; ++b)
 #pragma unroll
-            for (int d = 0; d < 2; ++d) {
-                const v4u q = *reinterpret_cast<const v4u *>(
-                    in + (((int64_t)zs[a] * vc.ny + ys[b]) * vc.nx + xs[d]) * C + c0);
+                    for (int d = 0; d < 2; ++d) {
+                        const v4u q = *reinterpret_cast<const v4u *>(
+                            in + ((int64_t)zs[a] * vc.ny + ys[b]) * vc.nx * C + xs[d] * C + c0);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    acc[2 * e] += __uint_as_float(q[e] << 16);
-                    acc[2 * e + 1] += __uint_as_float(q[e] & 0xffff0000u);
-                }
-            }
-    v4u o;
+                        for (int e = 0; e < 4; ++e) {
+                            acc[2 * e] += __uint_as_float(q[e] << 16);
+                            acc[2 * e + 1] += __uint_as_float(q[e] & 0xffff0000u);
+                        }
+                    }
+            v4u o;
 #pragma unroll
-    for (int e = 0; e < 4; ++e)
-        o[e] = (uint32_t)f2bf(0.125f * acc[2 * e]) | ((uint32_t)f2bf(0.125f * acc[2 * e + 1]) << 16);
-    *reinterpret_cast<v4u *>(out + v * C + c0) = o;
+            for (int e = 0; e < 4; ++e) o[e] = f2bf2(0.125f * acc[2 * e], 0.125f * acc[2 * e + 1]);
+            *reinterpret_cast<v4u *>(out + ((int64_t)z * vf.ny + y) * vf.nx * C + x * C + c0) = o;
+        }
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -646,9 +684,10 @@ hipError_t unet_forward(UNetDev *u, const float *features, float *out, hipStream
     }
     for (int l = s.L - 1; l >= 1; --l) {
         const Vol vc = u->lv[l], vf = u->lv[l - 1];
-        const int64_t nup = vf.n() * (C[l] / 8);
-        hipLaunchKernelGGL(upsample_kernel, dim3((unsigned)((nup + 255) / 256)), dim3(256), 0, st, u->h[l], vc, u->up,
-                           vf, C[l]);
+        const int log_groups = C[l] == 16 ? 1 : C[l] == 32 ? 2 : 3;
+        const int threads = std::min(1024, ((vf.nx << log_groups) + 63) / 64 * 64);
+        hipLaunchKernelGGL(upsample_kernel, dim3((unsigned)vf.ny, (unsigned)std::min(vf.nz, 65535)), dim3(threads), 0, st,
+                           u->h[l], vc, u->up, vf, log_groups);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         if ((e = conv(u->up, vf, vf, 1, C[l], C[l - 1], u->h[l - 1], u->t[l - 1])) != hipSuccess) return e;
         if ((e = conv(u->t[l - 1], vf, vf, 1, C[l - 1], C[l - 1], nullptr, u->h[l - 1])) != hipSuccess) return e;
