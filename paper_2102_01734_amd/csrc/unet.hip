@@ -9,9 +9,8 @@
 // top or bottom layer) and 8 weights of one output channel (16 bytes);
 // products accumulate in fp32.  Bias, ReLU and the U-Net skip addition are
 // fused into the store, and the 1-channel head into the last convolution's.
-// Stride-1 layers stage their input in LDS (conv_tile_kernel), the stride-2
-// ones, an eighth of the voxels, read it from L2 (conv_mfma_kernel).  The input
-// layer (3 float features) and the upsampling are plain VALU kernels.
+// They stage their input in LDS (conv_tile_kernel).  The input layer (3 float
+// features) and the upsampling are plain VALU kernels.
 // Activations never leave HBM between layers; at 129^3 with 16 channels a
 // level-0 map is 68 MB.
 #include <hip/hip_runtime.h>
@@ -61,7 +60,7 @@ struct Vol {
 };
 
 // ---------------------------------------------------------------------------
-// 3^3 convolution on the matrix cores, any stride: input from L2
+// 3^3 convolutions on the matrix cores
 // ---------------------------------------------------------------------------
 struct ConvArgs {
     const uint16_t *in;
@@ -82,97 +81,8 @@ __device__ __forceinline__ v8bf load8(const uint16_t *p, bool ok)
     return __builtin_bit_cast(v8bf, u);
 }
 
-constexpr int kConvTiles = 2;  // 16-voxel tiles per wavefront
-
-template <int CI, int CO>
-__global__ void __launch_bounds__(256) conv_mfma_kernel(ConvArgs a)
-{
-    constexpr int T = kConvTiles;
-    constexpr int NB = CO / 16;
-    constexpr int NK = (27 * CI + 31) / 32;  // 32-wide chunks of (tap, channel)
-    const int lane = threadIdx.x & 63;
-    const int64_t wave = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int64_t nvo = a.vo.n();
-    const int64_t v0 = wave * (16 * T);
-    if (v0 >= nvo) return;  // uniform per wavefront
-    const int i = lane & 15;       // A row (voxel) / B column (output channel)
-    const int kq = (lane >> 4) * 8;  // first of the 8 k values of this lane in a chunk
-    const int S = a.stride;
-    int xs[T], ys[T], zs[T];
-#pragma unroll
-    for (int t = 0; t < T; ++t) {
-        int64_t v = v0 + 16 * t + i;
-        v = v < nvo ? v : nvo - 1;  // loads of the tail tile repeat the last voxel; its stores are masked
-        const int64_t r = v / a.vo.nx;
-        xs[t] = (int)(v - r * a.vo.nx) * S - 1;
-        ys[t] = (int)(r % a.vo.ny) * S - 1;
-        zs[t] = (int)(r / a.vo.ny) * S - 1;
-    }
-    v4f acc[T][NB];
-#pragma unroll
-    for (int t = 0; t < T; ++t)
-#pragma unroll
-        for (int c = 0; c < NB; ++c) acc[t][c] = v4f{0.f, 0.f, 0.f, 0.f};
-
-    for (int j = 0; j < NK; ++j) {
-        const int k = j * 32 + kq;
-        const int tap = k / CI, c0 = k % CI;  // CI is a power of two
-        const bool tap_ok = tap < 27;
-        const int dz = tap / 9, dy = (tap / 3) % 3, dx = tap % 3;
-        v8bf B[NB];
-#pragma unroll
-        for (int cb = 0; cb < NB; ++cb)
-            B[cb] = load8(a.w + ((int64_t)(tap_ok ? tap : 0) * CO + cb * 16 + i) * CI + c0, tap_ok);
-#pragma unroll
-        for (int t = 0; t < T; ++t) {
-            const int zi = zs[t] + dz;
-            const bool ok = tap_ok && zi >= 0 && zi < a.vi.nz;
-            const int yi = wrap(ys[t] + dy, a.vi.ny);
-            const int xi = wrap(xs[t] + dx, a.vi.nx);
-            const v8bf A = load8(a.in + (((int64_t)(ok ? zi : 0) * a.vi.ny + yi) * a.vi.nx + xi) * CI + c0, ok);
-#pragma unroll
-            for (int cb = 0; cb < NB; ++cb) acc[t][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, B[cb], acc[t][cb], 0, 0, 0);
-        }
-    }
-    // D layout: lane holds rows kq/2 .. kq/2 + 3 (voxels) of column i (output channel)
-#pragma unroll
-    for (int t = 0; t < T; ++t)
-#pragma unroll
-        for (int cb = 0; cb < NB; ++cb) {
-            const int co = cb * 16 + i;
-            const float b = a.bias[co];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int64_t v = v0 + 16 * t + (lane >> 4) * 4 + r;
-                if (v >= nvo) continue;
-                float val = fmaxf(acc[t][cb][r] + b, 0.f);
-                if (a.skip) val += bf2f(a.skip[v * CO + co]);
-                a.out[v * CO + co] = f2bf(val);
-            }
-        }
-}
-
-template <int CI, int CO>
-static hipError_t conv_t(const ConvArgs &a, hipStream_t st)
-{
-    const int64_t waves = (a.vo.n() + 16 * kConvTiles - 1) / (16 * kConvTiles);
-    hipLaunchKernelGGL((conv_mfma_kernel<CI, CO>), dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, st, a);
-    return hipGetLastError();
-}
-
-static hipError_t conv_mfma(const ConvArgs &a, int ci, int co, hipStream_t st)
-{
-#define RT_CONV_CASE(I, O) \
-    if (ci == I && co == O) return conv_t<I, O>(a, st);
-    RT_CONV_CASE(16, 16) RT_CONV_CASE(16, 32) RT_CONV_CASE(16, 64)
-    RT_CONV_CASE(32, 16) RT_CONV_CASE(32, 32) RT_CONV_CASE(32, 64)
-    RT_CONV_CASE(64, 16) RT_CONV_CASE(64, 32) RT_CONV_CASE(64, 64)
-#undef RT_CONV_CASE
-    return hipErrorInvalidValue;
-}
-
 // ---------------------------------------------------------------------------
-// stride-1 convolutions from LDS
+// the convolutions, from LDS
 // ---------------------------------------------------------------------------
 // A block computes TX x TY x TZ output voxels (TX <= TXM, evened out over the
 // row) for all output channels from an LDS copy of their input with its halo,
@@ -193,11 +103,18 @@ static hipError_t conv_mfma(const ConvArgs &a, int ci, int co, hipStream_t st)
 // 33, two or four layers): 1 to 7 % slower; neighbouring blocks on one XCD, and
 // channels in separate planes against bank conflicts: no change.  Measured at
 // 129^3: 16 -> 16 channels 170 -> 61 us, 32 -> 16 with the skip 382 -> 119 us; the
-// network 1149 -> 539 us.
-template <int CI>
+// network 1149 -> 550 us.
+//
+// Stride 2 (an eighth of the voxels, a halo of two and more inputs per output) and
+// more output than input channels take smaller tiles, so that the copy and the
+// sums fit.  Reading the inputs from L2 for every tap instead, as all of them once
+// did: 16 -> 32 channels 42 us, 32 -> 32 27 us; now 34 and 14.
+template <int CI, int CO, int S>
 struct ConvTile {
-    static constexpr int TXM = CI == 16 ? 44 : CI == 32 ? 33 : 22, TY = 4, TZ = CI == 32 ? 4 : 2;
-    static constexpr int IX = TXM + 2, IY = TY + 2, IZ = TZ + 2;
+    static constexpr bool kSmall = S == 2 || CO > CI;
+    static constexpr int TXM = S == 2 && CI >= 32 ? 11 : kSmall || CI == 64 ? 22 : CI == 16 ? 44 : 33;
+    static constexpr int TY = S == 2 && CI == 64 ? 2 : 4, TZ = CI == 32 && !kSmall ? 4 : 2;
+    static constexpr int IX = S * (TXM - 1) + 3, IY = S * (TY - 1) + 3, IZ = S * (TZ - 1) + 3;
     static constexpr int kTiles = (TXM * TY * TZ + 15) / 16, kPerWave = (kTiles + 3) / 4;
     static constexpr size_t kBytes = (size_t)IX * IY * IZ * CI * 2;
 };
@@ -226,13 +143,13 @@ struct HeadArgs {
     float *out;         // [vo]
 };
 
-template <int CI, int CO>
+template <int CI, int CO, int S>
 __global__ void __launch_bounds__(256, 2) conv_tile_kernel(ConvArgs a, HeadArgs hd)
 {
-    using C = ConvTile<CI>;
+    using C = ConvTile<CI, CO, S>;
     constexpr int NB = CO / 16, NK = (27 * CI + 31) / 32, T = C::kPerWave;
     extern __shared__ __align__(16) unsigned char in[];  // [IZ][IY][IX][CI] bf16
-    const Vol v = a.vo;
+    const Vol v = a.vo, vi = a.vi;
     int x0, y0, z0, tx;
     tile_origin(v, C::TXM, C::TY, C::TZ, x0, y0, z0, tx);
     const int tid = threadIdx.x;
@@ -249,16 +166,16 @@ __global__ void __launch_bounds__(256, 2) conv_tile_kernel(ConvArgs a, HeadArgs 
         uint32_t at[kPer];
 #pragma unroll
         for (int n = 0; n < kPer; ++n) {
-            const int k = lane + 64 * n, x = x0 + k / (CI / 8) - 1;
-            at[n] = (uint32_t)((x > v.nx ? 0 : wrap(x, v.nx)) * (CI * 2) + k % (CI / 8) * 16);
+            const int k = lane + 64 * n, x = S * x0 + k / (CI / 8) - 1;
+            at[n] = (uint32_t)((x > vi.nx ? 0 : wrap(x, vi.nx)) * (CI * 2) + k % (CI / 8) * 16);
         }
         v4u u[kRows][kPer];
 #pragma unroll
         for (int m = 0; m < kRows; ++m) {
-            const int r = wave + 4 * m, y = y0 + r % C::IY - 1, z = z0 + r / C::IY - 1;
-            const bool in_vol = y <= v.ny && z >= 0 && z < v.nz;  // uniform
+            const int r = wave + 4 * m, y = S * y0 + r % C::IY - 1, z = S * z0 + r / C::IY - 1;
+            const bool in_vol = y <= vi.ny && z >= 0 && z < vi.nz;  // uniform
             const char *row = reinterpret_cast<const char *>(
-                a.in + (in_vol ? ((int64_t)z * v.ny + wrap(y, v.ny)) * v.nx * CI : 0));
+                a.in + (in_vol ? ((int64_t)z * vi.ny + wrap(y, vi.ny)) * vi.nx * CI : 0));
 #pragma unroll
             for (int n = 0; n < kPer; ++n) {
                 u[m][n] = *reinterpret_cast<const v4u *>(row + at[n]);
@@ -285,7 +202,7 @@ __global__ void __launch_bounds__(256, 2) conv_tile_kernel(ConvArgs a, HeadArgs 
     for (int t = 0; t < T; ++t) {
         const int q0 = (wave + 4 * t) * 16 + i, q = min(q0, P - 1);
         const int r = (int)(((uint32_t)q * inv) >> 16), xl = q - r * tx;
-        base[t] = (((r / C::TY) * C::IY + r % C::TY) * C::IX + xl) * (2 * CI) + 2 * (kq % CI & (CI == 16 ? 8 : 31));
+        base[t] = S * (((r / C::TY) * C::IY + r % C::TY) * C::IX + xl) * (2 * CI) + 2 * (kq % CI & (CI == 16 ? 8 : 31));
         const int x = x0 + xl, y = y0 + r % C::TY, z = z0 + r / C::TY;
         store[t] = q0 < P && x < v.nx && y < v.ny && z < v.nz;
         place[t] = store[t] ? ((uint32_t)z * (uint32_t)v.ny + (uint32_t)y) * (uint32_t)v.nx + (uint32_t)x : 0u;
@@ -373,11 +290,11 @@ __global__ void __launch_bounds__(256, 2) conv_tile_kernel(ConvArgs a, HeadArgs 
     }
 }
 
-template <int CI, int CO>
+template <int CI, int CO, int S>
 static hipError_t conv_tile_t(const ConvArgs &a, const HeadArgs &hd, hipStream_t st)
 {
-    using C = ConvTile<CI>;
-    auto k = conv_tile_kernel<CI, CO>;
+    using C = ConvTile<CI, CO, S>;
+    auto k = conv_tile_kernel<CI, CO, S>;
     hipError_t e = hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)C::kBytes);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k, dim3(tile_blocks(a.vo, C::TXM, C::TY, C::TZ)), dim3(256), C::kBytes, st, a, hd);
@@ -387,9 +304,9 @@ static hipError_t conv_tile_t(const ConvArgs &a, const HeadArgs &hd, hipStream_t
 static hipError_t conv_tile(const ConvArgs &a, int ci, int co, const HeadArgs &hd, hipStream_t st)
 {
 #define RT_CONV_CASE(I, O) \
-    if (ci == I && co == O) return conv_tile_t<I, O>(a, hd, st);
-    RT_CONV_CASE(16, 16)
-    RT_CONV_CASE(32, 16) RT_CONV_CASE(32, 32)
+    if (ci == I && co == O) return a.stride == 1 ? conv_tile_t<I, O, 1>(a, hd, st) : conv_tile_t<I, O, 2>(a, hd, st);
+    RT_CONV_CASE(16, 16) RT_CONV_CASE(16, 32) RT_CONV_CASE(16, 64)
+    RT_CONV_CASE(32, 16) RT_CONV_CASE(32, 32) RT_CONV_CASE(32, 64)
     RT_CONV_CASE(64, 16) RT_CONV_CASE(64, 32) RT_CONV_CASE(64, 64)
 #undef RT_CONV_CASE
     return hipErrorInvalidValue;
@@ -664,8 +581,7 @@ hipError_t unet_forward(UNetDev *u, const float *features, float *out, hipStream
         HeadArgs hd{};
         if (k == last) hd = HeadArgs{(const float *)u->w[k + 1], (const float *)u->b[k + 1], out};
         ++k;
-        // more output than input channels: the sums of a block's tiles would not stay in registers
-        return stride == 1 && co <= ci ? conv_tile(a, ci, co, hd, st) : conv_mfma(a, ci, co, st);
+        return conv_tile(a, ci, co, hd, st);
     };
     // level 0 input layer
     const Vol v0 = u->lv[0];

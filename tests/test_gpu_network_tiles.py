@@ -1,5 +1,6 @@
 """The tiled convolutions of the correction network at the edges of their tiles: rows
-of one block and just more (44, 33 and 22 voxels for 16, 32 and 64 input channels),
+of one block and just more (44, 33 and 22 voxels for 16, 32 and 64 input channels; with stride 2
+22, 11 and 11),
 layers and rows that fill a tile or leave one over, volumes smaller than a tile, every
 pair of channel numbers.  Reference and tolerance as for the other forward tests."""
 import numpy as np
@@ -16,7 +17,9 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("shape,C", [((44, 4, 4), (16,)), ((45, 5, 3), (16, 16)), ((2, 2, 1), (16, 32)),
                                      ((89, 3, 5), (16, 64)), ((33, 4, 4), (32, 32)), ((67, 9, 5), (32, 64)),
                                      ((34, 5, 9), (32, 16)), ((22, 4, 2), (64, 16)), ((45, 5, 3), (64, 32)),
-                                     ((3, 17, 6), (64, 64)), ((130, 6, 7), (16, 32, 16))])
+                                     ((3, 17, 6), (64, 64)), ((130, 6, 7), (16, 32, 16)),
+                                     ((88, 8, 4), (16, 32)), ((45, 17, 5), (32, 64)), ((46, 9, 9), (64, 32)),
+                                     ((23, 5, 3), (64, 64, 64)), ((1, 1, 2), (32, 64, 16))])
 def test_forward_at_tile_edges(shape, C):
     torch = torch_cuda()
     Nx, Ny, Nz = shape
