@@ -145,6 +145,11 @@ static double shape_cost(const rt_grid *g, const Variant &v, int n_lambda, int n
     // hold few pairs in flight (257^3 x 512: 1024 x 8 180 ms, 768 x 11 179, 768 x 10
     // 168; 768 x 8 156, 768 x 6 154, 1024 x 4 152)
     if (!v.dbl && v.R * v.lb >= 30 * 256 && 32.0 * (double)g->n_vox > 256e6) c *= 1.3;
+    // two outputs at eight rays and more on 1024 threads: their state and the
+    // point's temporaries pass the 128 registers (J and Lambda* in single, 129^3 x
+    // 256 directions: 1024 x 8 12.2 ms, 768 x 6 11.2; x 2048 88.6 and 86.8;
+    // 161 x 161 x 65 x 256 x 2 wavelengths 16.5 and 15.4)
+    if (!v.dbl && v.wj && v.wl && v.lb == 1024 && v.R >= 8) c *= 1.15;
     if (v.wj && v.wl) c *= 1.25;
     else if (v.wl) c *= 0.8;
     const bool wide = v.band && !v.dbl && !(v.wj && v.wl);
