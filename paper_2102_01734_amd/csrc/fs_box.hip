@@ -157,7 +157,10 @@ fs_box_kernel(FsBoxArgs a)
     // words of a 768-thread band in one go, where three groups of eight waited
     // three times for memory at every layer.
     constexpr int FLUSH = WIDE && R >= 8 && kRegs >= 160 ? 18 : 8;
-    constexpr bool kPrio = R >= 10 && R <= 12;  // long visits of three waves a SIMD; neutral or slower elsewhere
+    // long visits of three waves a SIMD; neutral or slower elsewhere, and with two
+    // outputs the registers around the rays' blocks spill (768 x 11 on 129^3 x 2048
+    // directions, J and Lambda*: 88.8 ms with, 77.8 without)
+    constexpr bool kPrio = R >= 10 && R <= 12 && !(WJ && WL);
 
     for (int i = tid; i < TW + nthr; i += nthr) {
         if (WJ) tJ[i] = T(0);

@@ -601,7 +601,8 @@ hipError_t unet_forward(UNetDev *u, const float *features, float *out, hipStream
     for (int l = s.L - 1; l >= 1; --l) {
         const Vol vc = u->lv[l], vf = u->lv[l - 1];
         const int log_groups = C[l] == 16 ? 1 : C[l] == 32 ? 2 : 3;
-        const int threads = std::min(1024, ((vf.nx << log_groups) + 63) / 64 * 64);
+        const int width = vf.nx << log_groups, turns = (width + 1023) / 1024;
+        const int threads = ((width + turns - 1) / turns + 63) / 64 * 64;
         hipLaunchKernelGGL(upsample_kernel, dim3((unsigned)vf.ny, (unsigned)std::min(vf.nz, 65535)), dim3(threads), 0, st,
                            u->h[l], vc, u->up, vf, log_groups);
         if ((e = hipGetLastError()) != hipSuccess) return e;
