@@ -148,7 +148,7 @@ static double shape_cost(const rt_grid *g, const Variant &v, int n_lambda, int n
     // two outputs at eight rays and more on 1024 threads: their state and the
     // point's temporaries pass the 128 registers (J and Lambda* in single, 129^3 x
     // 256 directions: 1024 x 8 12.2 ms, 768 x 6 11.2; x 2048 88.6 and 86.8;
-    // 161 x 161 x 65 x 256 x 2 wavelengths 16.5 and 15.4)
+    // 161 x 161 x 65 x 256 x 2 wavelengths 16.5 and 15.4; 768 x 11: 12.0, 78.3)
     if (!v.dbl && v.wj && v.wl && v.lb == 1024 && v.R >= 8) c *= 1.15;
     if (v.wj && v.wl) c *= 1.25;
     else if (v.wl) c *= 0.8;
