@@ -232,6 +232,7 @@ static rt_status ali_step_batch(rt_grid *g, rt_state *s, const rt_solve_opts *o,
     rt_status rs = ensure_state_buffers(g);
     if (rs != RT_OK) return rs;
     g->os_gs = o->os_method == RT_OS_GAUSS_SEIDEL;
+    g->begin_step();
     DevSchedule *lam_sc = nullptr;  // for lambda_of of the batch
     rs = get_schedule(g, variant(g, g->dbl, true, false).n_wg, lams, &lam_sc);
     if (rs != RT_OK) return rs;

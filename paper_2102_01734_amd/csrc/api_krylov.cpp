@@ -18,6 +18,7 @@ rt_status solve_bicgstab(rt_grid *g, rt_state *s, const rt_solve_opts *o, rt_sol
     if (rs != RT_OK) return rs;
     std::vector<int32_t> lams(nl);
     for (int i = 0; i < nl; ++i) lams[i] = i;
+    g->begin_step();  // the batch is the same throughout
     DevSchedule *lsc = nullptr;
     rs = get_schedule(g, variant(g, g->dbl, true, false).n_wg, lams, &lsc);
     if (rs != RT_OK) return rs;

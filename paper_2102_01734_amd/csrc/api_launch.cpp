@@ -259,6 +259,7 @@ rt_status get_schedule(rt_grid *g, int n_wg, const std::vector<int32_t> &lambdas
     }
     auto it = g->schedules.find(key);
     if (it != g->schedules.end()) {
+        it->second->step = g->step;
         *out = it->second.get();
         return RT_OK;
     }
@@ -299,8 +300,10 @@ rt_status get_schedule(rt_grid *g, int n_wg, const std::vector<int32_t> &lambdas
     HIPCHK(up(ds->lambda_of, lambdas.data(), lambdas.size() * sizeof(int32_t)));
     if (g->schedules.size() > 64) {
         g->drop_graphs();  // captured graphs reference schedule buffers
-        g->schedules.clear();
+        for (auto old = g->schedules.begin(); old != g->schedules.end();)
+            old = old->second->step == g->step ? std::next(old) : g->schedules.erase(old);
     }
+    ds->step = g->step;
     *out = ds.get();
     g->schedules[key] = std::move(ds);
     return RT_OK;
@@ -499,6 +502,7 @@ static rt_status autotune(rt_grid *g, int32_t n_lambda, const void *chi, const v
     if (!chi || !S) return fail(RT_E_INVALID, "chi and S must not be NULL");
     if (g->sphere) return fail(RT_E_UNSUPPORTED, "launch shapes apply to the box sweep only");
     hipStream_t st = (hipStream_t)stream;
+    g->begin_step();
     const bool dbl = g->dbl;
     const int Nx = g->geo.Nx, Ny = g->geo.Ny, Nz = g->geo.Nz;
     HIPCHK(g->fs_fld.ensure(8 * (size_t)n_lambda * g->n_vox * (dbl ? 8 : 4)));
@@ -703,6 +707,7 @@ rt_status formal_solution(rt_grid *g, int32_t n_lambda, const void *chi, const v
     if (n_lambda == 0) return RT_OK;
     if (!chi || !S || !J_out) return fail(RT_E_INVALID, "chi, S and J_out must not be NULL");
     hipStream_t st = (hipStream_t)stream;
+    g->begin_step();
     const bool dbl = g->dbl;
     const size_t esz = dbl ? 8 : 4;
     const size_t padn = g->sphere ? (size_t)g->desc.n_lambda_max * g->n_vox : (size_t)n_lambda * 4 * g->n_vox;

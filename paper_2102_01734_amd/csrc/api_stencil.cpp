@@ -116,6 +116,7 @@ rt_status rt_lstar_stencil(rt_grid_t g, int32_t n_lambda, const void *chi, void 
         return fail(RT_E_INVALID, "the spherical nearest-neighbour Lambda* needs Nphi >= 3");
     std::vector<int32_t> lams(n_lambda);
     for (int i = 0; i < n_lambda; ++i) lams[i] = i;
+    g->begin_step();
     DevSchedule *sc = nullptr;
     rt_status rs = get_schedule(g, g->sphere ? 0 : variant(g, g->dbl, true, false).n_wg, lams, &sc);
     if (rs != RT_OK) return rs;

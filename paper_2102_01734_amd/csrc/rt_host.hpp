@@ -88,6 +88,7 @@ struct Variant {
 struct DevSchedule {
     int n_wg = 0, n_slots = 0, n_batch = 0;
     int64_t points = 0;  // characteristic points evaluated by one launch
+    uint64_t step = 0;   // the grid's step that used it last (see rt_grid::schedules)
     DevBuf wg_begin, items, slot_begin, slot_ids, lambda_of;
 };
 
@@ -188,7 +189,14 @@ struct rt_grid {
     Variant fixed_var[2];
     std::map<std::string, Variant> picks;
 
+    // Schedules by shape, wavelengths and directions.  Beyond 64 a new one takes the
+    // place of all that the current step has not used, with the captured steps, whose
+    // graphs refer to them.  A step is one call, or one iteration of a solve
+    // (begin_step before its first look-up): the pointers that it holds, the wavelength
+    // list of its batch among them, stay valid until it ends.
     std::map<std::string, std::unique_ptr<DevSchedule>> schedules;
+    uint64_t step = 0;
+    void begin_step() { ++step; }
 
     // formal-solution inputs: interleaved (chi, S) doubly periodic padded copies
     DevBuf fs_fld;           // rt_formal_solution

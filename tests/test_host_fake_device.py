@@ -1,0 +1,56 @@
+"""The library's host side without a GPU: tests/native/fake_device.cpp stands in for
+the HIP runtime and the kernel launchers, and is built with AddressSanitizer and
+UndefinedBehaviorSanitizer, so that a launch that is handed freed memory ends the
+program."""
+import concurrent.futures as cf
+import os
+import shutil
+import subprocess
+
+import pytest
+
+from tests.test_sanitize_native import CSRC, ROOT, SAN
+
+SOURCES = ["geometry.cpp", "sphere_geometry.cpp", "schedule.cpp", "api_grid.cpp", "api_launch.cpp", "api_stencil.cpp",
+           "api_ali.cpp", "api_krylov.cpp"]
+
+pytestmark = pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not available")
+
+
+@pytest.fixture(scope="module")
+def fake(tmp_path_factory):
+    tmp = tmp_path_factory.mktemp("fake_device")
+    flags = ["-std=c++17", *SAN, "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I" + os.path.join(ROOT, "include"),
+             "-I" + CSRC]
+
+    def compile(src):
+        obj = str(tmp / (os.path.basename(src) + ".o"))
+        r = subprocess.run(["g++", *flags, "-c", src, "-o", obj], capture_output=True, text=True, timeout=300)
+        assert r.returncode == 0, r.stderr[-4000:]
+        return obj
+
+    files = [os.path.join(CSRC, f) for f in SOURCES] + [os.path.join(ROOT, "tests", "native", "fake_device.cpp")]
+    with cf.ThreadPoolExecutor(max_workers=4) as ex:
+        objs = list(ex.map(compile, files))
+    exe = str(tmp / "fake_device")
+    r = subprocess.run(["g++", *SAN, *objs, "-pthread", "-o", exe], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stderr[-4000:]
+    return exe
+
+
+def _case(fake, name):
+    env = dict(os.environ, ASAN_OPTIONS="detect_leaks=1:abort_on_error=0", UBSAN_OPTIONS="print_stacktrace=1")
+    r = subprocess.run([fake, name], capture_output=True, text=True, timeout=300, env=env)
+    assert r.returncode == 0 and f"{name} passed" in r.stdout, (r.stdout + r.stderr)[:4000]
+
+
+def test_schedules_of_a_step_outlive_it(fake):
+    """Solves whose batch shrinks at every step pass the 64 schedules that a grid
+    keeps; the wavelength list and the Lambda* schedule that a step took at its
+    beginning must not be freed by its later look-ups."""
+    _case(fake, "shrinking_batches")
+
+
+def test_schedules_of_many_calls(fake):
+    """The same for formal solutions, direction subsets, stencils and BiCGStab."""
+    _case(fake, "mixed_calls")
