@@ -232,7 +232,19 @@ __device__ __forceinline__ PointW<T> point_weights(double D, double Dp, bool las
 // Single results: with h = 0, which is the same limit at any D', by one select
 // of one word; D D'(D + D') stays finite for every D below 2^340, and float
 // opacities give steps below 2^140.
-template <typename T, bool LAST, bool DLIN = true>
+//
+// Reciprocals of single results: REFINE takes one Newton step after the hardware
+// estimate (about 2^-48), which the shell's sweep needs: its opacities reach optical
+// steps of 1e6 and more, where alpha is about 1/D and is left of e0 - beta - gamma, so
+// that an error d of the reciprocal is one of d D in alpha.  Without, d is at most
+// 4.6e-8 (2^-24.4) over a million random arguments: below the rounding of beta and
+// gamma to single precision, and the three weights still sum to e0 whatever it is, but
+// alpha is good to its own rounding only for steps of order one; at D = 1e6 it is a
+// few per cent off, and from about 2e7 up it may be negative.  The box sweep does
+// without (two of its 71 vector instructions a point): what alpha then misses is at
+// most 4.6e-8 of the upwind source, which is that source's own rounding, and shows
+// only where the sources downwind of a thick step are that much weaker.
+template <typename T, bool LAST, bool DLIN = true, bool REFINE = false>
 __device__ __forceinline__ PointW<T> point_weights_pos(double D, double Dp, bool last = false)
 {
     constexpr bool FULL = sizeof(T) == 8;
@@ -258,13 +270,9 @@ __device__ __forceinline__ PointW<T> point_weights_pos(double D, double Dp, bool
     } else {
         double h;  // D e1 - e2
         moments_single<true>(D, ex, e0, e1, h);
-        // single-precision results take the hardware reciprocal as it is: its relative
-        // error, at most 4.6e-8 (2^-24.4) over a million random arguments, is below
-        // the rounding of the weights to single precision, and a = e0 - b - g keeps
-        // the three weights summing to e0 whatever the error of b and g
         w.ex = T(ex);
         if constexpr (LAST) {
-            const double b = e1 * __builtin_amdgcn_rcp(D);
+            const double b = e1 * (REFINE ? rcp_f64<false>(D) : __builtin_amdgcn_rcp(D));
             w.b = w.dlin = T(b);
             w.g = T(0);
             w.a = T(e0 - b);
@@ -272,7 +280,7 @@ __device__ __forceinline__ PointW<T> point_weights_pos(double D, double Dp, bool
         }
         const bool lin = last || (Dp < 0.5 * D) || (Dp * e0 <= h);
         const double Ds = D + Dp;
-        const double r = __builtin_amdgcn_rcp(D * Dp * Ds);
+        const double r = REFINE ? rcp_f64<false>(D * Dp * Ds) : __builtin_amdgcn_rcp(D * Dp * Ds);
         // linear points: h = 0 in b = (h + D' e1) / (D D'), g = -h / (D' (D + D'))
         // leaves b = e1/D and g = 0.  Clearing the high word is enough: what is
         // left, below 1e-313, is nothing beside D' e1 > 1e-301.
@@ -282,7 +290,7 @@ __device__ __forceinline__ PointW<T> point_weights_pos(double D, double Dp, bool
         w.b = T(b);
         w.g = T(g);
         w.a = T(e0 - b - g);
-        if constexpr (DLIN) w.dlin = T(e1 * __builtin_amdgcn_rcp(D));
+        if constexpr (DLIN) w.dlin = T(e1 * (REFINE ? rcp_f64<false>(D) : __builtin_amdgcn_rcp(D)));
         return w;
     }
 }

@@ -171,7 +171,7 @@ __global__ void __launch_bounds__(256) fs_sphere_kernel(FsSphereArgs a)
             const double tn = seg_depth((double)fn.chi, (double)sl[u]);
             const bool last = m + 1 == len;
             const double Dp = last ? D : step(tc, tn);  // a padding row may hold any voxel
-            const PointW<T> pw = point_weights_pos<T, false, WL && !PARA>(D, Dp, last);
+            const PointW<T> pw = point_weights_pos<T, false, WL && !PARA, true>(D, Dp, last);
             const T wk = T(w[u]);
             if (WJ) {
                 I = I * pw.ex + pw.a * Sp + pw.b * Sc + (last ? T(0) : pw.g * fn.S);
