@@ -38,7 +38,7 @@ rt_status check_opts(const rt_solve_opts *o)
 }
 
 // Allocates the per-state buffers (sized for n_lambda_max) once.
-rt_status ensure_state_buffers(rt_grid *g)
+static rt_status allocate_state(rt_grid *g)
 {
     const size_t nl = (size_t)g->desc.n_lambda_max;
     const size_t nv = (size_t)g->n_vox;
@@ -69,6 +69,11 @@ rt_status ensure_state_buffers(rt_grid *g)
         HIPCHK(g->net_out.ensure(nv * 4));
     }
     return RT_OK;
+}
+
+rt_status ensure_state_buffers(rt_grid *g)
+{
+    return with_room(g, [&] { return allocate_state(g); });
 }
 
 static int os_sweeps_of(const rt_solve_opts *o) { return o->os_sweeps > 0 ? o->os_sweeps : 16; }
@@ -165,16 +170,21 @@ static rt_status plain_step_launches(rt_grid *g, rt_state *s, const std::vector<
 static rt_status graph_plain_step(rt_grid *g, rt_state *s, const std::vector<int32_t> &lams,
                                   const int32_t *lambda_of, hipStream_t st, int sweeps)
 {
-    const Variant v = pick_variant(g, g->dbl, true, false, (int)lams.size());
-    DevSchedule *sc = nullptr;
-    rt_status rs = get_schedule(g, v.n_wg, lams, &sc, nullptr, &v);
-    if (rs != RT_OK) return rs;
+    Variant v;
     DevBuf &pJ = g->dbl ? g->partJ64 : g->partJ;
-    HIPCHK(pJ.ensure((size_t)sc->n_slots * g->n_vox * (g->dbl ? 8 : 4)));
+    rt_status rs = with_room(g, [&]() -> rt_status {
+        v = pick_variant(g, g->dbl, true, false, (int)lams.size());
+        DevSchedule *sc = nullptr;
+        const rt_status r = get_schedule(g, v.n_wg, lams, &sc, nullptr, &v);
+        if (r != RT_OK) return r;
+        HIPCHK(pJ.ensure((size_t)sc->n_slots * g->n_vox * (g->dbl ? 8 : 4)));
+        return RT_OK;
+    });
+    if (rs != RT_OK) return rs;
     char buf[512];
-    snprintf(buf, sizeof buf, "%d|%p|%p|%p|%p|%p|%p|%p|%p|%p|%p|%d|%d.%d|%d.%d|%d:", g->hist_count % 4, (void *)s->J,
+    snprintf(buf, sizeof buf, "%d|%p|%p|%p|%p|%p|%p|%p|%p|%p|%p|%d|%d.%d.%d|%d.%d|%d:", g->hist_count % 4, (void *)s->J,
              (void *)s->S, s->lstar, s->eps, s->B, (void *)s->rel_change, pJ.p, (void *)st,
-             g->net ? g->net_r.p : nullptr, g->resid.p, s->n_lambda, v.lb, v.nb, v.R, v.band ? 1 : 0,
+             g->net ? g->net_r.p : nullptr, g->resid.p, s->n_lambda, v.lb, v.nb, v.n_wg, v.R, v.band ? 1 : 0,
              g->nonlocal ? (g->os_gs ? 1000000 + sweeps : sweeps) : -1);
     std::string key(buf);
     for (int l : lams) key += std::to_string(l) + ",";
@@ -336,7 +346,11 @@ static rt_status ali_step_batch(rt_grid *g, rt_state *s, const rt_solve_opts *o,
         if (!g->nl_side) HIPCHK(hipStreamCreateWithFlags(&g->nl_side, hipStreamNonBlocking));
         if (!g->nl_fork) HIPCHK(hipEventCreateWithFlags(&g->nl_fork, hipEventDisableTiming));
         if (!g->nl_join) HIPCHK(hipEventCreateWithFlags(&g->nl_join, hipEventDisableTiming));
-        HIPCHK(g->nl_acc.ensure((size_t)nl * kStencil * (size_t)nv * 8));  // no reallocation once forked
+        rs = with_room(g, [&]() -> rt_status {  // no reallocation once forked
+            HIPCHK(g->nl_acc.ensure((size_t)nl * kStencil * (size_t)nv * 8));
+            return RT_OK;
+        });
+        if (rs != RT_OK) return rs;
         HIPCHK(hipEventRecord(g->nl_fork, st));  // chi and the work before this step are ready
     }
     auto fork_stencil = [&]() -> rt_status {
@@ -361,8 +375,12 @@ static rt_status ali_step_batch(rt_grid *g, rt_state *s, const rt_solve_opts *o,
         return finish_stencil(g, nb, lambda_of, g->sphere ? nullptr : s->lstar, g->nl_st.p, g->dbl, st);
     };
 
+    const bool joint = g->dbl && want_l && variant(g, true, true, true).ok;
+    if (want_l && !joint) {  // Lambda*'s sums wait for the other sweep
+        rs = reserve_sweeps(g, {{g->dbl, false, true}, {g->dbl || anchor, true, false}}, lams);
+        if (rs != RT_OK) return rs;
+    }
     if (g->dbl) {
-        const bool joint = want_l && variant(g, true, true, true).ok;
         DevSchedule *scL = nullptr;
         if (want_l && !joint) {
             rs = run_fs(g, true, false, true, lams, g->fld.p, s->I_bc, g->partJ64, g->partL64, &scL, st);

@@ -23,6 +23,7 @@ void clear_error() { g_err.clear(); }
 rt_status hip_fail(hipError_t e, const char *file, int line)
 {
     const rt_status st = (e == hipErrorOutOfMemory || e == hipErrorMemoryAllocation) ? RT_E_NOMEM : RT_E_HIP;
+    (void)hipGetLastError();  // reported here: the next launch must not find it again
     return fail(st, "HIP error %s at %s:%d", hipGetErrorString(e), file, line);
 }
 
@@ -340,11 +341,12 @@ rt_status rt_sphere_tracks(const rt_grid_desc *desc, int32_t dir, double *h_out,
     return RT_OK;
 }
 
-// Device bytes a box grid uses at most for its geometry, the partial sums
+// Device bytes a box grid cannot do without for its geometry, the partial sums
 // of a formal solution with J and Lambda* of n_lambda_max wavelengths (a
 // schedule opens at most n_wg + n_lambda slots), both padded-input copies,
 // the ALI state (Ng ring, double anchors and their sweep on FP32 grids) and
-// the nearest-neighbour stencil.
+// the nearest-neighbour stencil.  Shapes with more slots and the tables of the
+// voxel-wise stencil kernel come on top while there is room (make_room).
 static int64_t box_device_bytes(rt_grid *g)
 {
     const int64_t nl = g->desc.n_lambda_max, nv = g->n_vox, nvis = g->n_visits, nd = g->n_dir;

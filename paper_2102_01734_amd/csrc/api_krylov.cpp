@@ -24,10 +24,14 @@ rt_status solve_bicgstab(rt_grid *g, rt_state *s, const rt_solve_opts *o, rt_sol
     if (rs != RT_OK) return rs;
     const int32_t *lambda_of = lsc->lambda_of.as<int32_t>();
     const int nblk = 64;
-    HIPCHK(g->kvec.ensure(13 * vn * 8));
-    HIPCHK(g->kblk.ensure((size_t)nl * nblk * 4 * 8));
-    HIPCHK(g->kout.ensure((size_t)nl * 4 * 8));
-    HIPCHK(g->kc.ensure((size_t)nl * 4 * 8));
+    rs = with_room(g, [&]() -> rt_status {
+        HIPCHK(g->kvec.ensure(13 * vn * 8));
+        HIPCHK(g->kblk.ensure((size_t)nl * nblk * 4 * 8));
+        HIPCHK(g->kout.ensure((size_t)nl * 4 * 8));
+        HIPCHK(g->kc.ensure((size_t)nl * 4 * 8));
+        return RT_OK;
+    });
+    if (rs != RT_OK) return rs;
     double *V = g->kvec.as<double>();
     KVec a{};
     a.eps = s->eps; a.B = s->B; a.lstar = s->lstar; a.c = g->kc.as<double>();

@@ -171,7 +171,7 @@ static Variant estimate_variant(rt_grid *g, bool dbl, bool wj, bool wl, int n_la
                                 const std::vector<int32_t> *subset)
 {
     const Variant &base = variant(g, dbl, wj, wl);
-    if (g->sphere || !base.ok || n_lambda < 1) return base;
+    if (g->sphere || g->tight || !base.ok || n_lambda < 1) return base;
     double sum_m = 0.0, max_m = 0.0;
     const int n_dirs = subset ? (int)subset->size() : g->n_dir;
     for (int i = 0; i < n_dirs; ++i) {
@@ -478,12 +478,39 @@ rt_status run_fs(rt_grid *g, bool dbl, bool wj, bool wl, const std::vector<int32
                         const void *fld, const void *I_bc, DevBuf &partJ, DevBuf &partL, DevSchedule **sched_out,
                         hipStream_t st, const std::vector<int32_t> *subset)
 {
-    const Variant v = pick_variant(g, dbl, wj, wl, (int)lambdas.size(), subset);
-    rt_status rs = run_fs_with(g, v, lambdas, fld, I_bc, partJ, partL, sched_out, st, subset);
-    const Variant &base = base_variant(g, dbl, wj, wl);
-    if (rs == RT_E_NOMEM && v.n_wg > base.n_wg)  // its partial sums do not fit: the shape with the fewest
-        rs = run_fs_with(g, base, lambdas, fld, I_bc, partJ, partL, sched_out, st, subset);
-    return rs;
+    return with_room(g, [&] {  // everything is allocated before anything is launched
+        const Variant v = pick_variant(g, dbl, wj, wl, (int)lambdas.size(), subset);
+        return run_fs_with(g, v, lambdas, fld, I_bc, partJ, partL, sched_out, st, subset);
+    });
+}
+
+bool make_room(rt_grid *g)
+{
+    if (g->sphere || g->tight) return false;
+    g->tight = true;
+    g->drop_graphs();
+    for (DevBuf *b : {&g->partJ, &g->partL, &g->partJ64, &g->partL64, &g->nl_visits, &g->nl_begin}) b->release();
+    g->nl_near = -1;
+    return true;
+}
+
+rt_status reserve_sweeps(rt_grid *g, const std::vector<SweepOuts> &sweeps, const std::vector<int32_t> &lambdas,
+                         const std::vector<int32_t> *subset)
+{
+    if (g->sphere) return RT_OK;  // one slot per wavelength
+    return with_room(g, [&]() -> rt_status {
+        for (const SweepOuts &o : sweeps) {
+            const Variant v = pick_variant(g, o.dbl, o.wj, o.wl, (int)lambdas.size(), subset);
+            if (!v.ok) continue;
+            DevSchedule *sc = nullptr;
+            const rt_status rs = get_schedule(g, v.n_wg, lambdas, &sc, subset, &v);
+            if (rs != RT_OK) return rs;
+            const size_t bytes = (size_t)sc->n_slots * g->n_vox * (o.dbl ? 8 : 4);
+            if (o.wj) HIPCHK((o.dbl ? g->partJ64 : g->partJ).ensure(bytes));
+            if (o.wl) HIPCHK((o.dbl ? g->partL64 : g->partL).ensure(bytes));
+        }
+        return RT_OK;
+    });
 }
 // The J-only shape of this precision is v from now on.
 static void fix_variant(rt_grid *g, const Variant &v)
@@ -505,7 +532,11 @@ static rt_status autotune(rt_grid *g, int32_t n_lambda, const void *chi, const v
     g->begin_step();
     const bool dbl = g->dbl;
     const int Nx = g->geo.Nx, Ny = g->geo.Ny, Nz = g->geo.Nz;
-    HIPCHK(g->fs_fld.ensure(8 * (size_t)n_lambda * g->n_vox * (dbl ? 8 : 4)));
+    rt_status rs = with_room(g, [&]() -> rt_status {
+        HIPCHK(g->fs_fld.ensure(8 * (size_t)n_lambda * g->n_vox * (dbl ? 8 : 4)));
+        return RT_OK;
+    });
+    if (rs != RT_OK) return rs;
     if (dbl)
         HIPCHK(pad_pair<double>((const double *)chi, (const double *)S, g->fs_fld.as<double>(), Nx, Ny, Nz, n_lambda, st));
     else
@@ -523,7 +554,6 @@ static rt_status autotune(rt_grid *g, int32_t n_lambda, const void *chi, const v
     HIPCHK(hipEventCreate(&e1));
     const bool prof = g->prof;
     g->prof = false;
-    rt_status rs = RT_OK;
     for (int i = -1; i < n && rs == RT_OK; ++i) {
         // band tiles compete on every grid (their flush covers only the rows a
         // bundle reaches); layer tiles wherever they fit
@@ -535,6 +565,10 @@ static rt_status autotune(rt_grid *g, int32_t n_lambda, const void *chi, const v
         DevBuf &pJ = dbl ? g->partJ64 : g->partJ;
         DevBuf &pL = dbl ? g->partL64 : g->partL;
         rs = run_fs_with(g, v, lams, g->fs_fld.p, nullptr, pJ, pL, &sc, st, subset);  // warm-up
+        if (rs == RT_E_NOMEM) {  // another may do with fewer slots
+            rs = RT_OK;
+            continue;
+        }
         if (rs != RT_OK) break;
         if (hipEventRecord(e0, st) != hipSuccess) { rs = fail(RT_E_HIP, "event record failed"); break; }
         rs = run_fs_with(g, v, lams, g->fs_fld.p, nullptr, pJ, pL, &sc, st, subset);
@@ -551,6 +585,7 @@ static rt_status autotune(rt_grid *g, int32_t n_lambda, const void *chi, const v
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     if (rs != RT_OK) return rs;
+    if (best_ms == 1e30f) return fail(RT_E_NOMEM, "no launch shape's partial sums fit the device memory");
     fix_variant(g, best);
     if (threads_out) *threads_out = best.lb;
     if (rays_out) *rays_out = best.R;
@@ -712,19 +747,22 @@ rt_status formal_solution(rt_grid *g, int32_t n_lambda, const void *chi, const v
     const size_t esz = dbl ? 8 : 4;
     const size_t padn = g->sphere ? (size_t)g->desc.n_lambda_max * g->n_vox : (size_t)n_lambda * 4 * g->n_vox;
     const int Nx = g->lx, Ny = g->ly, Nz = g->lz;
-    HIPCHK(g->fs_fld.ensure(2 * padn * esz));
+    std::vector<int32_t> lams(n_lambda);
+    for (int i = 0; i < n_lambda; ++i) lams[i] = i;
+    const bool wl = lstar_out != nullptr;
+    const bool joint = wl && variant(g, dbl, true, true).ok;
+    rt_status rs = with_room(g, [&]() -> rt_status {
+        HIPCHK(g->fs_fld.ensure(2 * padn * esz));
+        return RT_OK;
+    });
+    if (rs != RT_OK) return rs;
     if (dbl)
         HIPCHK(pad_pair<double>((const double *)chi, (const double *)S, g->fs_fld.as<double>(), Nx, Ny, Nz, n_lambda, st));
     else
         HIPCHK(pad_pair<float>((const float *)chi, (const float *)S, g->fs_fld.as<float>(), Nx, Ny, Nz, n_lambda, st));
-    std::vector<int32_t> lams(n_lambda);
-    for (int i = 0; i < n_lambda; ++i) lams[i] = i;
-    const bool wl = lstar_out != nullptr;
     DevBuf &pJ = dbl ? g->partJ64 : g->partJ;
     DevBuf &pL = dbl ? g->partL64 : g->partL;
-    const bool joint = wl && variant(g, dbl, true, true).ok;
     DevSchedule *sc = nullptr;
-    rt_status rs;
     if (joint) {
         rs = run_fs(g, dbl, true, true, lams, g->fs_fld.p, I_bc, pJ, pL, &sc, st, subset);
         if (rs != RT_OK) return rs;

@@ -14,8 +14,19 @@ rt_status ensure_near_tables(rt_grid *g)
         g->nl_near = -1;
         return RT_OK;
     }
-    HIPCHK(g->nl_visits.ensure(visits.size() * sizeof(NearVisit)));
-    HIPCHK(g->nl_begin.ensure(begin.size() * 4));
+    auto alloc = [&]() -> rt_status {
+        HIPCHK(g->nl_visits.ensure(visits.size() * sizeof(NearVisit)));
+        HIPCHK(g->nl_begin.ensure(begin.size() * 4));
+        return RT_OK;
+    };
+    const rt_status rs = alloc();
+    if (rs == RT_E_NOMEM) {  // the kernel that goes by characteristics needs none
+        g->nl_visits.release();
+        g->nl_begin.release();
+        g->nl_near = -1;
+        return RT_OK;
+    }
+    if (rs != RT_OK) return rs;
     HIPCHK(hipMemcpy(g->nl_visits.p, visits.data(), visits.size() * sizeof(NearVisit), hipMemcpyHostToDevice));
     HIPCHK(hipMemcpy(g->nl_begin.p, begin.data(), begin.size() * 4, hipMemcpyHostToDevice));
     g->nl_near = 1;
@@ -31,7 +42,11 @@ rt_status accumulate_stencil(rt_grid *g, const void *chi, int n_lambda, int nb, 
                                     bool skip_centre, hipStream_t st)
 {
     const int64_t per = (int64_t)kStencil * g->n_vox;
-    HIPCHK(g->nl_acc.ensure((size_t)n_lambda * per * 8));
+    rt_status rs = with_room(g, [&]() -> rt_status {
+        HIPCHK(g->nl_acc.ensure((size_t)n_lambda * per * 8));
+        return RT_OK;
+    });
+    if (rs != RT_OK) return rs;
     for (int64_t off = 0; off < (int64_t)n_lambda * per; off += (int64_t)1 << 30) {
         const int64_t cnt = std::min<int64_t>((int64_t)1 << 30, (int64_t)n_lambda * per - off);
         HIPCHK(fill_u64(g->nl_acc.as<unsigned long long>() + off, 0ull, (int)cnt, st));
@@ -79,7 +94,7 @@ rt_status accumulate_stencil(rt_grid *g, const void *chi, int n_lambda, int nb, 
         a.dir_plane = g->nl_planes.as<int32_t>() + (size_t)(skip_centre ? 1 : 0) * g->n_dir * kPlaneStride;
         a.planes = g->nl_np[skip_centre ? 1 : 0];
     }
-    rt_status rs = ensure_near_tables(g);
+    rs = ensure_near_tables(g);
     if (rs != RT_OK) return rs;
     if (g->nl_near > 0) {
         a.near_visits = g->nl_visits.as<NearVisit>();

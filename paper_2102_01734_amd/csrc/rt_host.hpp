@@ -188,6 +188,9 @@ struct rt_grid {
     bool fixed[2] = {false, false};
     Variant fixed_var[2];
     std::map<std::string, Variant> picks;
+    // an allocation has failed: from then on the default shapes, with the fewest
+    // slots, and no tables of the voxel-wise stencil kernel
+    bool tight = false;
 
     // Schedules by shape, wavelengths and directions.  Beyond 64 a new one takes the
     // place of all that the current step has not used, with the captured steps, whose
@@ -299,6 +302,26 @@ inline const Variant &base_variant(rt_grid *g, bool dbl, bool wj, bool wl)
 // time (api_launch.cpp).
 Variant pick_variant(rt_grid *g, bool dbl, bool wj, bool wl, int n_lambda,
                      const std::vector<int32_t> *subset = nullptr);
+
+// Gives back what the grid holds beyond its necessary working set (partial sums,
+// tables of the voxel-wise stencil kernel; captured steps, which refer to them) and
+// keeps to that set from now on.  False if it already does.  Only where no partial
+// sums wait to be added.
+bool make_room(rt_grid *g);
+// The result of alloc(), with a second try after make_room when it is RT_E_NOMEM.
+template <typename F>
+rt_status with_room(rt_grid *g, F alloc)
+{
+    const rt_status rs = alloc();
+    return rs == RT_E_NOMEM && make_room(g) ? alloc() : rs;
+}
+// Schedules and partial-sum buffers of the sweeps that a call is about to run, so
+// that none of them allocates once another's sums are waiting.
+struct SweepOuts {
+    bool dbl, wj, wl;
+};
+rt_status reserve_sweeps(rt_grid *g, const std::vector<SweepOuts> &sweeps, const std::vector<int32_t> &lambdas,
+                         const std::vector<int32_t> *subset = nullptr);
 
 // ---------------------------------------------------------------------------
 // functions shared between the modules

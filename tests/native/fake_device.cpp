@@ -17,7 +17,7 @@
 // ---------------------------------------------------------------------------
 namespace dev {
 std::unordered_map<void *, size_t> live;
-size_t used = 0, limit = (size_t)1 << 36;
+size_t used = 0, peak = 0, limit = (size_t)1 << 36;
 bool capturing = false;
 hipError_t last = hipSuccess;  // sticky until hipGetLastError, as in the runtime
 using Graph = std::vector<std::function<void()>>;
@@ -60,6 +60,7 @@ hipError_t hipMalloc(void **p, size_t n)
     *p = std::calloc(1, n);
     dev::live[*p] = n;
     dev::used += n;
+    dev::peak = std::max(dev::peak, dev::used);
     return hipSuccess;
 }
 hipError_t hipFree(void *p)
@@ -426,11 +427,71 @@ static void mixed_calls()
     }
 }
 
+// What a grid does with the default shapes and no stencil tables fits the memory that
+// this takes, also from a start with the shapes of least estimated time.
+static void calls_of_a_grid(Owner &o, bool graph, bool tune)
+{
+    const int n = 6;
+    const size_t k = (size_t)n * o.g->n_vox;
+    std::vector<double> in(k), out(k), L(k), st(27 * k);
+    hipStream_t stream = nullptr;
+    hipStreamCreateWithFlags(&stream, 0);
+    CHECK(rt_formal_solution(o.g, 1, in.data(), in.data(), nullptr, out.data(), nullptr, stream) == RT_OK);
+    updates = 0;
+    rel_of = [=](int l) { return l < updates - 2 ? 0.0 : 1.0; };
+    StateArrays a(o, n);
+    rt_solve_opts opt = options(graph);
+    const rt_status rs = rt_solve(o.g, &a.s, &opt, nullptr, stream);
+    if (rs != RT_OK) std::fprintf(stderr, "%s\n", rt_last_error());
+    CHECK(rs == RT_OK);
+    CHECK(rt_formal_solution(o.g, n, in.data(), in.data(), nullptr, out.data(), L.data(), stream) == RT_OK);
+    CHECK(rt_lstar_stencil(o.g, n, in.data(), st.data(), stream) == RT_OK);
+    opt.method = RT_SOLVER_BICGSTAB;
+    opt.max_iter = 2;
+    CHECK(rt_solve(o.g, &a.s, &opt, nullptr, stream) == RT_E_NOT_CONVERGED);
+    if (tune) CHECK(rt_autotune(o.g, 1, in.data(), in.data(), nullptr, nullptr, stream) == RT_OK);
+    hipStreamDestroy(stream);
+}
+
+static void short_memory()
+{
+    const size_t all = dev::limit;
+    for (rt_prec prec : {RT_FP64, RT_FP32})
+        for (uint32_t flags : {0u, RT_F_BAND_TILES, RT_F_LSTAR_NONLOCAL, RT_F_LSTAR_NONLOCAL | RT_F_LSTAR_PARABOLIC})
+            for (bool graph : {false, true}) {
+                size_t plain, room;
+                {
+                    Owner o(24, 20, 4, 4, 8, prec, 6, flags);
+                    o.g->tight = true;
+                    dev::peak = 0;
+                    calls_of_a_grid(o, graph, false);
+                    plain = dev::peak;
+                }
+                {
+                    Owner o(24, 20, 4, 4, 8, prec, 6, flags);
+                    dev::peak = 0;
+                    calls_of_a_grid(o, graph, false);
+                    room = dev::peak;
+                }
+                CHECK(room > plain || flags == RT_F_BAND_TILES);
+                // half a megabyte for the schedules of two shapes
+                for (size_t extra = (size_t)1 << 19; plain + extra < room; extra = 2 * extra) {
+                    Owner o(24, 20, 4, 4, 8, prec, 6, flags);
+                    dev::limit = plain + extra;
+                    dev::failed_allocs = 0;
+                    calls_of_a_grid(o, graph, true);
+                    CHECK(dev::failed_allocs > 0);
+                    dev::limit = all;
+                }
+            }
+}
+
 int main(int argc, char **argv)
 {
     const std::string which = argc > 1 ? argv[1] : "";
     if (which == "shrinking_batches") shrinking_batches();
     else if (which == "mixed_calls") mixed_calls();
+    else if (which == "short_memory") short_memory();
     else return 2;
     if (g_fail == 0) std::printf("%s passed\n", which.c_str());
     return g_fail == 0 ? 0 : 1;

@@ -54,3 +54,9 @@ def test_schedules_of_a_step_outlive_it(fake):
 def test_schedules_of_many_calls(fake):
     """The same for formal solutions, direction subsets, stencils and BiCGStab."""
     _case(fake, "mixed_calls")
+
+
+def test_short_memory_falls_back(fake):
+    """Where the chosen shapes' partial sums or the stencil's tables do not fit, every
+    call goes on with the default shapes and the kernel without tables."""
+    _case(fake, "short_memory")
