@@ -494,9 +494,10 @@ rt_status rt_autotune_dirs(rt_grid_t grid, int32_t n_lambda, const void *chi, co
  * than the bound when a direction has fewer rays.  RT_E_INVALID if no
  * compiled shape matches or the shape cannot hold one direction's rays in
  * the device's LDS; RT_E_UNSUPPORTED on spherical grids.  Does not launch
- * anything.  Where a shape is compiled for both tile kinds, the grid's own
- * kind (row bands with RT_F_BAND_TILES or a layer beyond the LDS, else whole
- * layers) is taken; rt_set_launch_shape_tiles names the kind.
+ * anything.  Where a shape is compiled for both tile kinds, the default shape's
+ * kind is taken if it is that shape, else the grid's own (row bands with
+ * RT_F_BAND_TILES or a layer beyond the LDS, else whole layers);
+ * rt_set_launch_shape_tiles names the kind.
  */
 rt_status rt_set_launch_shape(rt_grid_t grid, int32_t threads, int32_t rays);
 

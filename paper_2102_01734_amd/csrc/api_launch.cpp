@@ -616,9 +616,10 @@ static rt_status set_shape(rt_grid *g, bool dbl, int32_t threads, int32_t rays, 
 {
     const FsShape *sh = nullptr;
     const int n = fs_box_shapes(&sh);
-    // the grid's default shape, whose bundle count may be its own (rt_autotune can keep it)
+    // the grid's default shape, whose bundle count and tile kind may be its own
+    // (rt_autotune can keep it)
     const Variant dflt = estimate_variant(g, dbl, true, false, g->desc.n_lambda_max, nullptr);
-    if (dflt.ok && dflt.lb == threads && dflt.R == rays && dflt.band == (band >= 0 ? band != 0 : g->band)) {
+    if (dflt.ok && dflt.lb == threads && dflt.R == rays && (band < 0 || dflt.band == (band != 0))) {
         fix_variant(g, dflt);
         return RT_OK;
     }

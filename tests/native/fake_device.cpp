@@ -486,12 +486,32 @@ static void short_memory()
             }
 }
 
+// The shape that a fresh grid reports can be set again, through either entry point.
+static void default_shape_again()
+{
+    int bands = 0;
+    for (int nx : {12, 33, 46, 65, 97})
+        for (rt_prec prec : {RT_FP64, RT_FP32})
+            for (uint32_t flags : {0u, RT_F_BAND_TILES})
+                for (bool named : {false, true}) {
+                    Owner o(nx, 45, 5, 4, 8, prec, 2, flags);
+                    int32_t t, r, nb, band, t1, r1, nb1, band1;
+                    CHECK(rt_launch_shape(o.g, &t, &r, &nb, &band) == RT_OK);
+                    CHECK((named ? rt_set_launch_shape_tiles(o.g, t, r, band) : rt_set_launch_shape(o.g, t, r)) == RT_OK);
+                    CHECK(rt_launch_shape(o.g, &t1, &r1, &nb1, &band1) == RT_OK);
+                    CHECK(t == t1 && r == r1 && nb == nb1 && band == band1);
+                    bands += band && !(flags & RT_F_BAND_TILES);
+                }
+    CHECK(bands > 0);  // layer grids whose default is band tiles are among them
+}
+
 int main(int argc, char **argv)
 {
     const std::string which = argc > 1 ? argv[1] : "";
     if (which == "shrinking_batches") shrinking_batches();
     else if (which == "mixed_calls") mixed_calls();
     else if (which == "short_memory") short_memory();
+    else if (which == "default_shape_again") default_shape_again();
     else return 2;
     if (g_fail == 0) std::printf("%s passed\n", which.c_str());
     return g_fail == 0 ? 0 : 1;

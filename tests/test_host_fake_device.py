@@ -60,3 +60,8 @@ def test_short_memory_falls_back(fake):
     """Where the chosen shapes' partial sums or the stencil's tables do not fit, every
     call goes on with the default shapes and the kernel without tables."""
     _case(fake, "short_memory")
+
+
+def test_default_shape_can_be_set_again(fake):
+    """Also where a grid whose layers fit the LDS has band tiles for its default."""
+    _case(fake, "default_shape_again")
