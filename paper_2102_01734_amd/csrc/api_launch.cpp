@@ -558,6 +558,11 @@ static rt_status autotune(rt_grid *g, int32_t n_lambda, const void *chi, const v
         // band tiles compete on every grid (their flush covers only the rows a
         // bundle reaches); layer tiles wherever they fit
         if (i >= 0 && !g->layer_ok && !sh[i].band) continue;
+        // the default shape with another number of bundles could not be set again:
+        // its threads, rays and tile kind name the default
+        if (i >= 0 && by_estimate.ok && sh[i].lb == by_estimate.lb && sh[i].R == by_estimate.R &&
+            sh[i].band == by_estimate.band)
+            continue;
         const Variant v = i < 0 ? by_estimate
                                 : make_variant(g, dbl, true, false, sh[i].lb, sh[i].R, sh[i].occ, sh[i].band, false);
         if (!v.ok) continue;

@@ -8,6 +8,7 @@
 // usage: fake_device CASE; exits non-zero on a failed check.
 #include <cstdio>
 #include <functional>
+#include <set>
 #include <unordered_map>
 
 #include "rt_host.hpp"
@@ -505,6 +506,28 @@ static void default_shape_again()
     CHECK(bands > 0);  // layer grids whose default is band tiles are among them
 }
 
+// The shape that the autotuner keeps can be set again on a fresh grid, whichever is
+// the fastest: it is known by threads, rays and tile kind alone.
+static void tuned_shape_again()
+{
+    std::set<std::pair<int, int>> kept;
+    for (uint32_t flags : {0u, RT_F_BAND_TILES})
+        for (int fast = 0; fast < 12; ++fast) {
+            sweep_ms = [=](const LastSweep &w) { return w.nb == fast ? 1.f : 2.f + w.nb; };
+            std::vector<double> in(65 * 45 * 5);
+            Owner o(65, 45, 5, 4, 8, RT_FP64, 1, flags), fresh(65, 45, 5, 4, 8, RT_FP64, 1, flags);
+            int32_t t, r, nb, band, t1, r1, nb1, band1;
+            CHECK(rt_autotune(o.g, 1, in.data(), in.data(), nullptr, nullptr, nullptr) == RT_OK);
+            CHECK(rt_launch_shape(o.g, &t, &r, &nb, &band) == RT_OK);
+            CHECK(rt_set_launch_shape_tiles(fresh.g, t, r, band) == RT_OK);
+            CHECK(rt_launch_shape(fresh.g, &t1, &r1, &nb1, &band1) == RT_OK);
+            CHECK(t == t1 && r == r1 && nb == nb1 && band == band1);
+            kept.insert({t, r});
+        }
+    CHECK(kept.size() > 1);
+    sweep_ms = [](const LastSweep &) { return 1.f; };
+}
+
 int main(int argc, char **argv)
 {
     const std::string which = argc > 1 ? argv[1] : "";
@@ -512,6 +535,7 @@ int main(int argc, char **argv)
     else if (which == "mixed_calls") mixed_calls();
     else if (which == "short_memory") short_memory();
     else if (which == "default_shape_again") default_shape_again();
+    else if (which == "tuned_shape_again") tuned_shape_again();
     else return 2;
     if (g_fail == 0) std::printf("%s passed\n", which.c_str());
     return g_fail == 0 ? 0 : 1;

@@ -65,3 +65,9 @@ def test_short_memory_falls_back(fake):
 def test_default_shape_can_be_set_again(fake):
     """Also where a grid whose layers fit the LDS has band tiles for its default."""
     _case(fake, "default_shape_again")
+
+
+def test_tuned_shape_can_be_set_again(fake):
+    """Whichever shape the autotuner finds fastest, threads, rays and tile kind give it
+    back on another grid, its number of bundles included."""
+    _case(fake, "tuned_shape_again")
