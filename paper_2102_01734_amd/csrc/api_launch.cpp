@@ -167,6 +167,35 @@ static double shape_cost(const rt_grid *g, const Variant &v, int n_lambda, int n
     return std::max(longest, mean + 0.25 * longest) + 2.0 * slots / 1740.0;
 }
 
+// The shapes that calls of a precision and outputs choose among: each compiled shape
+// with up to eight bundle counts.  Found once per grid: a call of a new size then makes
+// no queries to the runtime (some 500, 5 to 25 us of the first call of a size).
+static const std::vector<Variant> &candidates(rt_grid *g, bool dbl, bool wj, bool wl)
+{
+    std::vector<Variant> &out = g->shapes[dbl][wj][wl];
+    if (g->shapes_known[dbl][wj][wl]) return out;
+    // Whole layers of a few thousand voxels flush in a few words a thread, which
+    // bands cannot better; larger ones let both kinds compete (65 x 65, 512
+    // directions: 2.8 ms on bands, 3.6 on layers).
+    const bool bands = g->band || (int64_t)g->geo.Nx * g->geo.Ny >= 2048;
+    const FsShape *sh = nullptr;
+    const int n = fs_box_shapes(&sh);
+    for (int i = 0; i < n; ++i) {
+        if (!sh[i].full && !(wj && !wl)) continue;
+        if (sh[i].band ? !bands : g->band) continue;
+        int tried = 0;
+        for (int nb = 1; nb <= std::min(32, g->geo.Nx * g->geo.Ny) && tried < 8; ++nb) {
+            if (sh[i].band && nb < 2) continue;
+            const Variant v = make_variant(g, dbl, wj, wl, sh[i].lb, sh[i].R, sh[i].occ, sh[i].band, false, nb);
+            if (v.nthr == 0) continue;  // the bundle does not fit the shape
+            ++tried;
+            if (v.ok) out.push_back(v);
+        }
+    }
+    g->shapes_known[dbl][wj][wl] = true;
+    return out;
+}
+
 static Variant estimate_variant(rt_grid *g, bool dbl, bool wj, bool wl, int n_lambda,
                                 const std::vector<int32_t> *subset)
 {
@@ -198,31 +227,15 @@ static Variant estimate_variant(rt_grid *g, bool dbl, bool wj, bool wl, int n_la
         v.n_wg -= v.n_wg % v.nb;
         return v.n_wg >= v.nb;
     };
-    // Whole layers of a few thousand voxels flush in a few words a thread, which
-    // bands cannot better; larger ones let both kinds compete (65 x 65, 512
-    // directions: 2.8 ms on bands, 3.6 on layers).
-    const bool bands = g->band || (int64_t)g->geo.Nx * g->geo.Ny >= 2048;
     Variant best = base;
     double best_cost = base.spill ? 1e300 : shape_cost(g, base, n_eff, n_dirs, sum_m, max_m);
-    const FsShape *sh = nullptr;
-    const int n = fs_box_shapes(&sh);
-    for (int i = 0; i < n; ++i) {
-        if (!sh[i].full && !(wj && !wl)) continue;
-        if (sh[i].band ? !bands : g->band) continue;
-        int first = 0, tried = 0;
-        for (int nb = 1; nb <= std::min(32, g->geo.Nx * g->geo.Ny) && tried < 8; ++nb) {
-            if (sh[i].band && nb < 2) continue;
-            Variant v = make_variant(g, dbl, wj, wl, sh[i].lb, sh[i].R, sh[i].occ, sh[i].band, false, nb);
-            if (v.nthr == 0) continue;  // the bundle does not fit the shape
-            if (!first) first = nb;
-            ++tried;
-            if (!v.ok || !trim(v)) continue;
-            const double cost = shape_cost(g, v, n_eff, n_dirs, sum_m, max_m);
-            // a few per cent are within the estimate's error: the earlier shape stays
-            if (cost < 0.97 * best_cost) {
-                best = v;
-                best_cost = cost;
-            }
+    for (Variant v : candidates(g, dbl, wj, wl)) {
+        if (!trim(v)) continue;
+        const double cost = shape_cost(g, v, n_eff, n_dirs, sum_m, max_m);
+        // a few per cent are within the estimate's error: the earlier shape stays
+        if (cost < 0.97 * best_cost) {
+            best = v;
+            best_cost = cost;
         }
     }
     g->picks.emplace(key, best);

@@ -188,6 +188,8 @@ struct rt_grid {
     bool fixed[2] = {false, false};
     Variant fixed_var[2];
     std::map<std::string, Variant> picks;
+    std::vector<Variant> shapes[2][2][2];  // the shapes chosen among, [dbl][wj][wl], once shapes_known
+    bool shapes_known[2][2][2] = {};
     // an allocation has failed: from then on the default shapes, with the fewest
     // slots, and no tables of the voxel-wise stencil kernel
     bool tight = false;

@@ -156,7 +156,7 @@ static LastSweep sweep;
 static std::function<float(const LastSweep &)> sweep_ms = [](const LastSweep &) { return 1.f; };
 static int updates = 0;                  // operator-splitting updates so far
 static std::function<double(int)> rel_of = [](int) { return 1.0; };
-static bool near_kernel = false;         // the last stencil build had the voxel-wise tables
+static int occupancy_queries = 0;
 
 static void check_lambdas(const int32_t *lam, int n)
 {
@@ -177,6 +177,7 @@ int fs_box_shapes(const FsShape **out)
 }
 int fs_box_occupancy(bool, bool, bool, bool, bool, int lb, int, int nthr, size_t lds)
 {
+    ++occupancy_queries;
     return std::max(1, std::min<int>(lb / nthr, (int)(160 * 1024 / std::max<size_t>(lds, 1))));
 }
 hipError_t fs_box_launch(const FsBoxArgs &a, bool dbl, bool wj, bool wl, bool, bool band, int lb, int R, int n_wg, int nthr,
@@ -276,7 +277,6 @@ hipError_t krylov_dots(const KDots &, int64_t, int n_lambda, double *, int, doub
 hipError_t krylov_vec(const KVec &, int, int64_t, int, bool, hipStream_t) { return dev::launch([] {}); }
 hipError_t lstar_stencil_accumulate(const StencilArgs &a, bool, bool, int, int n_batch, size_t, hipStream_t)
 {
-    near_kernel = a.near_visits != nullptr;
     return dev::launch([=] { check_lambdas(a.lambda_of, n_batch); });
 }
 hipError_t lstar_stencil_finish(const unsigned long long *, const int32_t *lambda_of, int64_t, int n_batch, const void *,
@@ -528,6 +528,25 @@ static void tuned_shape_again()
     sweep_ms = [](const LastSweep &) { return 1.f; };
 }
 
+// What the runtime says of a compiled shape does not depend on the call: batches and
+// shares of other sizes choose among the shapes of the first call without asking again.
+static void shapes_asked_once()
+{
+    for (rt_prec prec : {RT_FP64, RT_FP32}) {
+        Owner o(46, 45, 5, 4, 8, prec, 12);
+        std::vector<double> in(12 * (size_t)o.g->n_vox), out(in.size());
+        std::vector<int32_t> dirs;
+        for (int n = 1; n <= 12; ++n) {
+            occupancy_queries = 0;
+            dirs.push_back(n);
+            CHECK(rt_formal_solution(o.g, n, in.data(), in.data(), nullptr, out.data(), nullptr, nullptr) == RT_OK);
+            CHECK(rt_formal_solution_dirs(o.g, n, in.data(), in.data(), nullptr, n, dirs.data(), out.data(), nullptr,
+                                          nullptr) == RT_OK);
+            CHECK((occupancy_queries > 0) == (n == 1));
+        }
+    }
+}
+
 int main(int argc, char **argv)
 {
     const std::string which = argc > 1 ? argv[1] : "";
@@ -536,6 +555,7 @@ int main(int argc, char **argv)
     else if (which == "short_memory") short_memory();
     else if (which == "default_shape_again") default_shape_again();
     else if (which == "tuned_shape_again") tuned_shape_again();
+    else if (which == "shapes_asked_once") shapes_asked_once();
     else return 2;
     if (g_fail == 0) std::printf("%s passed\n", which.c_str());
     return g_fail == 0 ? 0 : 1;

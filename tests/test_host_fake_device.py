@@ -71,3 +71,8 @@ def test_tuned_shape_can_be_set_again(fake):
     """Whichever shape the autotuner finds fastest, threads, rays and tile kind give it
     back on another grid, its number of bundles included."""
     _case(fake, "tuned_shape_again")
+
+
+def test_shapes_are_asked_once(fake):
+    """A call of a new size costs no queries to the runtime beyond the grid's first."""
+    _case(fake, "shapes_asked_once")
