@@ -562,9 +562,10 @@ rt_status rt_profile_read(rt_grid_t grid, double *fs_ms, int32_t *fs_launches, i
  * partial sums -- lives in one fixed device array of RT_NOALLOC_SCRATCH_BYTES
  * that the library holds on each GPU it runs on until the process ends (set
  * up by rt_create_grid); the call itself allocates no device memory and
- * frees none.  When the partial sums of the grid's usual workgroup count do
- * not fit, fewer persistent workgroups are launched (results then differ
- * from rt_formal_solution's in the summation order only); a call whose
+ * frees none.  Results are rt_formal_solution's bit for bit where the partial
+ * sums of its launch shape fit the array; else another shape or fewer
+ * persistent workgroups are launched (results then differ in the summation
+ * order only); a call whose
  * padded input plus one workgroup's partial sums per ray bundle exceed the
  * array is refused with RT_E_INVALID before anything is enqueued.  All calls
  * on one GPU share the array: calls that overlap in time on one GPU (e.g.

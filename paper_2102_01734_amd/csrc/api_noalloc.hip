@@ -40,7 +40,7 @@ namespace {
 // kept in the grid so that the asynchronous upload always reads live memory)
 // and where its arrays sit in the scratch.
 struct NoAllocPass {
-    const Variant *v = nullptr;
+    Variant v;
     const Schedule *sc = nullptr;
     size_t off_wg = 0, off_items = 0, off_sb = 0, off_si = 0, off_lo = 0, off_part = 0, end = 0;
 };
@@ -51,20 +51,26 @@ size_t schedule_bytes(size_t n_wg, size_t n_items, size_t n_lambda, size_t n_slo
            align256(n_slots * 4) + align256(n_lambda * 4);
 }
 
-// Fewest-constraint plan: the largest workgroup count (at most the shape's
-// resident count, a multiple of its bundle count) whose partial sums fit the
-// scratch behind the padded input.
-rt_status plan_pass(rt_grid *g, const Variant &v, int n_lambda, size_t base, int nout, NoAllocPass &p)
+// Plan of a sweep behind the padded input: the shape of rt_formal_solution where its
+// partial sums fit the scratch, so that both give the same result; else the default
+// shape, which opens the fewest slots, with the largest workgroup count (a multiple of
+// its bundle count) that fits.
+rt_status plan_pass(rt_grid *g, bool wj, bool wl, int n_lambda, size_t base, NoAllocPass &p)
 {
+    const int nout = (wj ? 1 : 0) + (wl ? 1 : 0);
+    Variant v = pick_variant(g, g->dbl, wj, wl, n_lambda);
+    if (!v.ok) return fail(RT_E_UNSUPPORTED, "no kernel configuration fits this grid");
     const size_t esz = g->dbl ? 8 : 4;
     const size_t slot_bytes = (size_t)g->n_vox * esz * nout;
-    const size_t n_items_max = (size_t)n_lambda * g->n_dir * v.nb;
+    auto need = [&](int w) {
+        // the k workgroups of a bundle open at most k + n_lambda - 1 slots, none without an item
+        const size_t items = (size_t)n_lambda * g->n_dir * v.nb;
+        const size_t slots = std::min((size_t)w + (size_t)v.nb * (n_lambda - 1), items);
+        return base + schedule_bytes(w, items, n_lambda, slots) + slots * slot_bytes;
+    };
+    if (need(v.n_wg) > kNoAllocScratchBytes) v = base_variant(g, g->dbl, wj, wl);
     const int nb = v.nb;
     int n_wg = v.n_wg - v.n_wg % nb;
-    auto need = [&](int w) {
-        const size_t slots = (size_t)w + n_lambda;
-        return base + schedule_bytes(w, n_items_max, n_lambda, slots) + slots * slot_bytes;
-    };
     while (n_wg >= nb && need(n_wg) > kNoAllocScratchBytes) n_wg -= nb;
     if (n_wg < nb)
         return fail(RT_E_INVALID,
@@ -81,7 +87,7 @@ rt_status plan_pass(rt_grid *g, const Variant &v, int n_lambda, size_t base, int
         build_schedule(g->geo, lams, n_wg, *sc, nullptr, nb);
         it = g->na_sched.emplace(key, std::move(sc)).first;
     }
-    p.v = &v;
+    p.v = v;
     p.sc = it->second.get();
     const Schedule &s = *p.sc;
     p.off_wg = base;
@@ -130,9 +136,7 @@ extern "C" rt_status rt_formal_solution_noalloc(rt_grid_t g, int32_t n_lambda, c
     // validate every sweep before anything is enqueued
     std::vector<NoAllocPass> passes(outs.size());
     for (size_t i = 0; i < outs.size(); ++i) {
-        const Variant &v = base_variant(g, dbl, outs[i].wj, outs[i].wl);
-        if (!v.ok) return fail(RT_E_UNSUPPORTED, "no kernel configuration fits this grid");
-        rt_status rs = plan_pass(g, v, n_lambda, fld_bytes, (outs[i].wj ? 1 : 0) + (outs[i].wl ? 1 : 0), passes[i]);
+        rt_status rs = plan_pass(g, outs[i].wj, outs[i].wl, n_lambda, fld_bytes, passes[i]);
         if (rs != RT_OK) return rs;
     }
     const int Nx = g->lx, Ny = g->ly, Nz = g->lz;
@@ -142,7 +146,7 @@ extern "C" rt_status rt_formal_solution_noalloc(rt_grid_t g, int32_t n_lambda, c
         HIPCHK(pad_pair<float>((const float *)chi, (const float *)S, (float *)base, Nx, Ny, Nz, n_lambda, st));
     for (size_t i = 0; i < passes.size(); ++i) {
         const NoAllocPass &p = passes[i];
-        const Variant &v = *p.v;
+        const Variant &v = p.v;
         const Schedule &sc = *p.sc;
         // schedule into the scratch (host copies live in the grid until it is destroyed)
         HIPCHK(hipMemcpyAsync(base + p.off_wg, sc.wg_begin.data(), sc.wg_begin.size() * 4, hipMemcpyHostToDevice, st));

@@ -547,6 +547,26 @@ static void shapes_asked_once()
     }
 }
 
+// The slots that a schedule opens, which size the fixed scratch of the no-allocation
+// formal solution.
+static void slot_bound()
+{
+    for (int n_mu : {2, 4, 8})
+        for (int n_phi : {1, 3, 16}) {
+            BoxGeometry geo;
+            CHECK(build_box_geometry(9, 7, 5, n_mu, n_phi, geo).empty());
+            for (int nl : {1, 2, 3, 5, 11, 26})
+                for (int nb : {1, 2, 3, 5})
+                    for (int w = nb; w < 300; w += w < 20 ? nb : 7 * nb) {
+                        std::vector<int32_t> lams(nl);
+                        for (int i = 0; i < nl; ++i) lams[i] = i;
+                        Schedule s;
+                        build_schedule(geo, lams, w, s, nullptr, nb);
+                        CHECK(s.n_slots <= std::min(w + nb * (nl - 1), nl * n_mu * n_phi * nb));
+                    }
+        }
+}
+
 int main(int argc, char **argv)
 {
     const std::string which = argc > 1 ? argv[1] : "";
@@ -556,6 +576,7 @@ int main(int argc, char **argv)
     else if (which == "default_shape_again") default_shape_again();
     else if (which == "tuned_shape_again") tuned_shape_again();
     else if (which == "shapes_asked_once") shapes_asked_once();
+    else if (which == "slot_bound") slot_bound();
     else return 2;
     if (g_fail == 0) std::printf("%s passed\n", which.c_str());
     return g_fail == 0 ? 0 : 1;

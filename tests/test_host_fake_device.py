@@ -76,3 +76,8 @@ def test_tuned_shape_can_be_set_again(fake):
 def test_shapes_are_asked_once(fake):
     """A call of a new size costs no queries to the runtime beyond the grid's first."""
     _case(fake, "shapes_asked_once")
+
+
+def test_slots_of_a_schedule_are_bounded(fake):
+    """By its workgroups and wavelengths per bundle, and by its items."""
+    _case(fake, "slot_bound")
