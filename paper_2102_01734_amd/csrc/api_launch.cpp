@@ -208,9 +208,11 @@ static Variant estimate_variant(rt_grid *g, bool dbl, bool wj, bool wl, int n_la
         sum_m += m;
         max_m = std::max(max_m, m);
     }
-    // small batches run the shape of a single wavelength, so that they give its
-    // results bit for bit
-    const int n_item = n_lambda * n_dirs;
+    // small batches run the shape of a single wavelength: as long as every item has a
+    // slot of its own (n_item <= n_wg / nb, the workgroups of a bundle) they give its
+    // results bit for bit; beyond, directions share slots in another way and the sums
+    // are rounded in another order
+    const int64_t n_item = (int64_t)n_lambda * n_dirs;
     const int n_eff = n_item < 2 * g->n_cu ? 1 : n_lambda;
     char key[96];
     snprintf(key, sizeof key, "%d%d%d/%d/%d/%.0f/%.0f", dbl, wj, wl, n_eff, n_dirs, sum_m, max_m);
@@ -221,7 +223,7 @@ static Variant estimate_variant(rt_grid *g, bool dbl, bool wj, bool wl, int n_la
     // shape has only while they stay below a gigabyte
     const double slot_bytes = (double)g->n_vox * (dbl ? 8 : 4) * ((wj ? 1 : 0) + (wl ? 1 : 0));
     const int64_t most = std::max<int64_t>(base.n_wg, (int64_t)(1e9 / slot_bytes));
-    const int64_t items = std::max(n_item, 2 * g->n_cu);
+    const int64_t items = std::max<int64_t>(n_item, 2 * g->n_cu);
     auto trim = [&](Variant &v) {
         v.n_wg = (int)std::min<int64_t>(v.n_wg, std::min<int64_t>(most, items * v.nb));
         v.n_wg -= v.n_wg % v.nb;
