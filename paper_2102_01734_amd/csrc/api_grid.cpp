@@ -342,8 +342,8 @@ rt_status rt_sphere_tracks(const rt_grid_desc *desc, int32_t dir, double *h_out,
 }
 
 // Device bytes a box grid cannot do without for its geometry, the partial sums
-// of a formal solution with J and Lambda* of n_lambda_max wavelengths (a
-// schedule opens at most n_wg + n_lambda slots), both padded-input copies,
+// of a formal solution with J and Lambda* of n_lambda_max wavelengths (about
+// n_wg + n_lambda slots each), both padded-input copies,
 // the ALI state (Ng ring, double anchors and their sweep on FP32 grids) and
 // the nearest-neighbour stencil.  Shapes with more slots and the tables of the
 // voxel-wise stencil kernel come on top while there is room (make_room).

@@ -143,10 +143,12 @@ static double shape_cost(const rt_grid *g, const Variant &v, int n_lambda, int n
     // a wavelength's padded field beyond the 256 MB Infinity Cache: the HBM latency
     // shows where 30 rays and more share a SIMD lane's 512 registers, which then
     // hold few pairs in flight (257^3 x 512: 1024 x 8 180 ms, 768 x 11 179, 768 x 10
-    // 168; 768 x 8 156, 768 x 6 154, 1024 x 4 152)
+    // 168; 768 x 8 156, 768 x 6 154, 1024 x 4 152; of the last three, 3 % apart, the
+    // estimate takes the first)
     if (!v.dbl && v.R * v.lb >= 30 * 256 && 32.0 * (double)g->n_vox > 256e6) c *= 1.3;
-    // two outputs at eight rays and more on 1024 threads: their state and the
-    // point's temporaries pass the 128 registers (J and Lambda* in single, 129^3 x
+    // two outputs at eight rays and more on 1024 threads: eight words a ray of state and
+    // the point's temporaries pass the 128 registers that four waves a SIMD leave, as
+    // they do at no smaller workgroup (J and Lambda* in single, 129^3 x
     // 256 directions: 1024 x 8 12.2 ms, 768 x 6 11.2; x 2048 88.6 and 86.8;
     // 161 x 161 x 65 x 256 x 2 wavelengths 16.5 and 15.4; 768 x 11: 12.0, 78.3)
     if (!v.dbl && v.wj && v.wl && v.lb == 1024 && v.R >= 8) c *= 1.15;

@@ -152,14 +152,18 @@ fs_box_kernel(FsBoxArgs a)
     constexpr int kFree = kRegs > kUsed ? (kRegs - kUsed) / (2 * kWords) : 0;
     constexpr int PRE = !CARRY ? 0 : kFree < R ? kFree : R;
     constexpr bool TPRE = kUsed + 2 <= kRegs;
-    // Words of a layer flush per thread whose slot reads are issued together; a
-    // visit's temporaries are free by then.  Eighteen take the 98 rows of 129
-    // words of a 768-thread band in one go, where three groups of eight waited
-    // three times for memory at every layer.
+    // Words of a layer flush per thread whose slot reads are issued together: a
+    // flush waits for memory once per such group, so as many as find room in the
+    // registers that a visit's temporaries leave (eighteen beside eight rays and more
+    // from 160 registers up, else eight).  Larger bands take more groups; the 98 rows
+    // of 129 words of a 768-thread band take one, where groups of eight waited three
+    // times at every layer.
     constexpr int FLUSH = WIDE && R >= 8 && kRegs >= 160 ? 18 : 8;
-    // long visits of three waves a SIMD; neutral or slower elsewhere, and with two
-    // outputs the registers around the rays' blocks spill (768 x 11 on 129^3 x 2048
-    // directions, J and Lambda*: 88.8 ms with, 77.8 without)
+    // Wavefront priority by progress within a visit (see step): pays where a visit is
+    // long and few waves share a SIMD, ten to twelve rays a thread (64.6 -> 62.0 ms
+    // with the look-ahead at 768 x 11 on 129^3 x 2048 directions).  Neutral or slower
+    // for shorter and longer visits, and with two outputs the registers around the rays'
+    // blocks spill (the same, J and Lambda*: 88.8 ms with, 77.8 without).
     constexpr bool kPrio = R >= 10 && R <= 12 && !(WJ && WL);
 
     for (int i = tid; i < TW + nthr; i += nthr) {

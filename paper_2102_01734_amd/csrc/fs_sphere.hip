@@ -57,9 +57,12 @@ struct Rows {
 
 }  // namespace
 
-// Bound by instruction issue (77 vector instructions a visit, busy 84 % of the
+// Bound by instruction issue (79 vector instructions a visit, busy 84 % of the
 // time) with memory not far behind: 4 GB of contributions, geometry and field
-// lines a launch.  What a lane adds to the box sweep's point is the walk through
+// lines a launch.  Two of them refine the reciprocal of the weights, without which
+// thick steps lose their upwind weight (point_weights_pos): 2.24 -> 2.31 ms for the
+// 16 wavelengths below.  The exponential of a step is the single-precision
+// polynomial's, 2e-11 of itself.  What a lane adds to the box sweep's point is the walk through
 // the cache.  The wavefront's bundle is known to be uniform, so a
 // visit's row of the cache and of the outputs is a scalar base that advances by
 // scalar adds, each lane's place in it a constant 32-bit offset, and a field
@@ -68,7 +71,7 @@ struct Rows {
 // the reads ahead need no mask, only a scalar clamp; they run a group of four
 // visits ahead (two or one: 4 to 9 % slower at one wavelength, the same at 16).
 // Measured on 49 x 33 x 65 voxels x 128 directions (57 M visits): 16 wavelengths
-// in single 3.2 -> 2.35 ms; 25 x 17 x 34 x 32 directions, one wavelength, double,
+// in single 3.2 -> 2.4 ms; 25 x 17 x 34 x 32 directions, one wavelength, double,
 // J and Lambda*: 74 -> 35 us.  Keeping neighbouring bundles on one XCD (runs of
 // 8 to 128 blocks) changed nothing.
 template <typename T, typename TG, bool WJ, bool WL, bool PARA, bool SMALL>

@@ -99,8 +99,11 @@ __device__ __forceinline__ v8bf load8(const uint16_t *p, bool ok)
 // the next chunk's operands and the skip map are read ahead, the LDS copy is made
 // by rows whose addresses are scalar, tiles are found by a multiplication (before
 // that 2400 vector instructions a wavefront for 243 matrix ones: 97 and 190 us;
-// without reading ahead 116 and 285 us).  Tiles of other sizes (rows of 22 or
-// 33, two or four layers): 1 to 7 % slower; neighbouring blocks on one XCD, and
+// without reading ahead 116 and 285 us).  TXM is a bound: a row is cut into as few
+// pieces as it allows and evened out, so any width up to it occurs.  The bounds keep
+// a block's copy at 18 to 81 KB, so that two and more fit a CU's 160 KB, and its sums
+// in registers; other bounds (22 or 33, two or four layers) were 1 to 7 % slower at
+// 129^3; neighbouring blocks on one XCD, and
 // channels in separate planes against bank conflicts: no change.  Measured at
 // 129^3: 16 -> 16 channels 170 -> 61 us, 32 -> 16 with the skip 382 -> 119 us; the
 // network 1149 -> 550 us.
