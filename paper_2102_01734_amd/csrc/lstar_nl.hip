@@ -26,10 +26,13 @@
 // contributions arrive.  |sum| <= 1 per element, so 2^52 leaves ample
 // headroom below 2^63.
 //
-// The linear operator has a kernel that goes by voxels (below).
+// The linear operator has a kernel that goes by voxels (below), for templates
+// that step along one axis at a time.
 //
-// Row-window kernel (parabolic operator): a workgroup takes one wavelength, one direction and a
-// bundle of H consecutive ray rows (all Nx rays of each row), its rays in
+// Row-window kernel (the parabolic operator, and the linear one with many
+// characteristics where templates cross two faces at once, e.g. at 45 degrees,
+// n_phi = 4, 12, 20): a workgroup
+// takes one wavelength, one direction and a bundle of H consecutive ray rows (all Nx rays of each row), its rays in
 // lockstep.  At visit m every ray of bundle row yr adds to target row
 // yr + brow_m of the current layer (brow: the visit's row above the lowest
 // row the template reaches in that layer), so the live target rows form a
@@ -172,7 +175,7 @@ __global__ void __launch_bounds__(256) lstar_stencil_kernel(StencilArgs a)
 
 constexpr int kFlushWords = 4;
 
-template <typename G, int R>
+template <typename G, bool PARA, int R>
 __global__ void __launch_bounds__(1024) lstar_stencil_rows_kernel(StencilArgs a)
 {
     extern __shared__ unsigned long long tile[];  // [plane][H + 1 circular rows][Nx]
@@ -266,6 +269,7 @@ __global__ void __launch_bounds__(1024) lstar_stencil_rows_kernel(StencilArgs a)
         for (int r = 0; r < R; ++r) word[r] = slot[r] * Nx + x_cur[r];
 #pragma unroll
         for (int j = 0; j < 5; ++j) {
+            if (!PARA && j == 0) continue;  // no downwind weight in the linear operator
             const uint32_t c = (comps >> (6 * j)) & 63u;
             if (c == kNoComp) continue;
             const int p = plane_of[c];
@@ -360,14 +364,20 @@ __global__ void __launch_bounds__(1024) lstar_stencil_rows_kernel(StencilArgs a)
                 t_nxt[r] = half_seg(
                     (double)chi[(int64_t)k_nxt * NxNy + (int64_t)row(y0[r], w_nxt) * Nx + x_nxt[r]], sv[m + 1]);
             }
-            const double D = step_of(t_prev, t_cur[r]);
-            const double Dp = last ? 0.0 : step_of(t_cur[r], t_nxt[r]);
-            const PointW<double> pw = point_weights<double, sizeof(G) == 8>(D, Dp, last);
-            const double ex = pw.ex, wa = pw.a, wb = pw.b, wg = pw.g;
+            double ex, wa, wb, wg;
+            if constexpr (PARA) {
+                const double D = step_of(t_prev, t_cur[r]);
+                const double Dp = last ? 0.0 : step_of(t_cur[r], t_nxt[r]);
+                const PointW<double> pw = point_weights<double, sizeof(G) == 8>(D, Dp, last);
+                ex = pw.ex; wa = pw.a; wb = pw.b; wg = pw.g;
+            } else {
+                linear_weights<sizeof(G) == 8>(t_prev, t_cur[r], ex, wa, wb);
+                wg = 0.0;
+            }
             Gv[r][4] = ex * Gv[r][3];
             Gv[r][3] = ex * Gv[r][2];
-            Gv[r][2] = ex * Gv[r][1] + wa;
-            Gv[r][1] = ex * Gv[r][0] + wb;
+            Gv[r][2] = __builtin_fma(ex, Gv[r][1], wa);
+            Gv[r][1] = __builtin_fma(ex, Gv[r][0], wb);
             Gv[r][0] = wg;
         }
         add(wmu * sv[m], comp[m]);
@@ -610,13 +620,13 @@ static int stencil_rows(const StencilArgs &a, size_t max_lds)
     return (a.Ny + nb - 1) / nb;
 }
 
-template <typename G, int R>
+template <typename G, bool PARA, int R>
 static hipError_t launch_rows(const StencilArgs &a, int n_dir, int n_batch, hipStream_t st)
 {
     const int rays = a.rows * a.Nx;
     const int nthr = ((rays + R - 1) / R + 63) / 64 * 64;
     const size_t lds = (size_t)a.planes * (a.rows + 1) * a.Nx * 8;
-    auto k = lstar_stencil_rows_kernel<G, R>;
+    auto k = lstar_stencil_rows_kernel<G, PARA, R>;
     hipError_t e = hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     dim3 grid((unsigned)((a.Ny + a.rows - 1) / a.rows), (unsigned)n_dir, (unsigned)n_batch);
@@ -624,24 +634,31 @@ static hipError_t launch_rows(const StencilArgs &a, int n_dir, int n_batch, hipS
     return hipGetLastError();
 }
 
-template <typename G>
+template <typename G, bool PARA>
 static hipError_t launch_rows_r(const StencilArgs &a, int n_dir, int n_batch, hipStream_t st)
 {
-    if (a.rows * a.Nx <= 512) return launch_rows<G, 1>(a, n_dir, n_batch, st);
-    return launch_rows<G, 2>(a, n_dir, n_batch, st);
+    if (a.rows * a.Nx <= 512) return launch_rows<G, PARA, 1>(a, n_dir, n_batch, st);
+    return launch_rows<G, PARA, 2>(a, n_dir, n_batch, st);
 }
 
 hipError_t lstar_stencil_accumulate(const StencilArgs &a0, bool grid_double, bool parabolic, int n_dir, int n_batch,
                                     size_t max_lds, hipStream_t st)
 {
     if (n_dir <= 0 || n_batch <= 0) return hipSuccess;
-    if (a0.near_visits && !parabolic) return grid_double ? launch_near<double>(a0, n_batch, st) : launch_near<float>(a0, n_batch, st);
-    if (a0.dir_plane && a0.brow && parabolic) {
+    const StencilRoute route = stencil_route(a0, parabolic, n_dir, n_batch);
+    if (route == StencilRoute::voxels)
+        return grid_double ? launch_near<double>(a0, n_batch, st) : launch_near<float>(a0, n_batch, st);
+    if (route == StencilRoute::rows) {
         StencilArgs a = a0;
         a.rows = a.planes > 0 ? stencil_rows(a, max_lds) : 0;
         if (a.planes == 0) return hipSuccess;  // no component is ever added
-        if (a.rows > 0)
-            return grid_double ? launch_rows_r<double>(a, n_dir, n_batch, st) : launch_rows_r<float>(a, n_dir, n_batch, st);
+        if (a.rows > 0) {
+            if (grid_double)
+                return parabolic ? launch_rows_r<double, true>(a, n_dir, n_batch, st)
+                                 : launch_rows_r<double, false>(a, n_dir, n_batch, st);
+            return parabolic ? launch_rows_r<float, true>(a, n_dir, n_batch, st)
+                             : launch_rows_r<float, false>(a, n_dir, n_batch, st);
+        }
     }
     const StencilArgs &a = a0;
     const int NxNy = a.Nx * a.Ny;

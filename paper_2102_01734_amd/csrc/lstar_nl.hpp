@@ -55,6 +55,22 @@ struct StencilArgs {
 
 constexpr int kPlaneStride = 64;
 
+// The kernel that builds a box stencil: by voxels where the linear operator's tables
+// are made (templates that step along one axis at a time); else by windows of rows
+// where a template's rows move by at most one a visit; else by characteristics.  The
+// linear operator without tables also goes by characteristics while these are few: a
+// window of rows is one workgroup's, and leaves the chip idle.  By rows and by
+// characteristics, single: 33 x 33 x 33 x 32 directions (3.5e4 characteristics) 595 and
+// 194 us, 97 x 97 x 40 x 32 (3.0e5) 789 and 727, 129 x 129 x 40 x 32 (5.3e5) 936 and
+// 1234, 70 x 70 x 40 x 96 x 2 wavelengths (9.4e5) 2.2 and 3.3 ms; double alike.
+enum class StencilRoute { voxels, rows, characteristics };
+inline StencilRoute stencil_route(const StencilArgs &a, bool parabolic, int n_dir, int n_batch)
+{
+    if (a.near_visits && !parabolic) return StencilRoute::voxels;
+    const bool many = (int64_t)a.Nx * a.Ny * n_dir * n_batch >= 400000;
+    return a.dir_plane && a.brow && (parabolic || many) ? StencilRoute::rows : StencilRoute::characteristics;
+}
+
 // Nearest-neighbour Lambda* on a spherical grid, one chunk of the geometry
 // cache: one thread per characteristic and batch entry follows the
 // characteristic's visits (same recurrence as the box), and adds

@@ -157,6 +157,7 @@ static std::function<float(const LastSweep &)> sweep_ms = [](const LastSweep &) 
 static int updates = 0;                  // operator-splitting updates so far
 static std::function<double(int)> rel_of = [](int) { return 1.0; };
 static int occupancy_queries = 0;
+static StencilRoute route;               // of the last stencil build
 
 static void check_lambdas(const int32_t *lam, int n)
 {
@@ -275,8 +276,9 @@ hipError_t krylov_dots(const KDots &, int64_t, int n_lambda, double *, int, doub
     return dev::launch([=] { std::fill(out, out + 4 * n_lambda, 1.0); });
 }
 hipError_t krylov_vec(const KVec &, int, int64_t, int, bool, hipStream_t) { return dev::launch([] {}); }
-hipError_t lstar_stencil_accumulate(const StencilArgs &a, bool, bool, int, int n_batch, size_t, hipStream_t)
+hipError_t lstar_stencil_accumulate(const StencilArgs &a, bool, bool para, int n_dir, int n_batch, size_t, hipStream_t)
 {
+    route = stencil_route(a, para, n_dir, n_batch);
     return dev::launch([=] { check_lambdas(a.lambda_of, n_batch); });
 }
 hipError_t lstar_stencil_finish(const unsigned long long *, const int32_t *lambda_of, int64_t, int n_batch, const void *,
@@ -567,6 +569,27 @@ static void slot_bound()
         }
 }
 
+// Stencils of many characteristics go by voxels or by rows on every quadrature, those of
+// few by voxels or by characteristics.
+static void stencil_routes()
+{
+    int ties = 0;
+    for (uint32_t flags : {0u, RT_F_LSTAR_PARABOLIC})
+        for (int n_mu : {2, 4, 6, 10})
+            for (int n_phi = 1; n_phi <= 12; ++n_phi)
+                for (int nx : {10, 456}) {
+                    const bool many = nx * nx * n_mu * n_phi >= 400000;
+                    Owner o(nx, nx, 2, n_mu, n_phi, RT_FP32, 1, flags);
+                    std::vector<float> in(o.g->n_vox), st(27 * in.size());
+                    CHECK(rt_lstar_stencil(o.g, 1, in.data(), st.data(), nullptr) == RT_OK);
+                    const bool tie = o.g->nl_near <= 0;  // templates that cross two faces at once
+                    CHECK(flags ? route == StencilRoute::rows
+                                : route == (!tie ? StencilRoute::voxels : many ? StencilRoute::rows : StencilRoute::characteristics));
+                    ties += !flags && tie && many;
+                }
+    CHECK(ties > 0);
+}
+
 int main(int argc, char **argv)
 {
     const std::string which = argc > 1 ? argv[1] : "";
@@ -577,6 +600,7 @@ int main(int argc, char **argv)
     else if (which == "tuned_shape_again") tuned_shape_again();
     else if (which == "shapes_asked_once") shapes_asked_once();
     else if (which == "slot_bound") slot_bound();
+    else if (which == "stencil_routes") stencil_routes();
     else return 2;
     if (g_fail == 0) std::printf("%s passed\n", which.c_str());
     return g_fail == 0 ? 0 : 1;

@@ -81,3 +81,9 @@ def test_shapes_are_asked_once(fake):
 def test_slots_of_a_schedule_are_bounded(fake):
     """By its workgroups and wavelengths per bundle, and by its items."""
     _case(fake, "slot_bound")
+
+
+def test_routes_of_stencils(fake):
+    """Where the templates of a quadrature cross two faces at once (45 degrees), the
+    linear operator goes by rows as soon as the characteristics are many."""
+    _case(fake, "stencil_routes")
