@@ -292,7 +292,7 @@ rt_status get_schedule(rt_grid *g, int n_wg, const std::vector<int32_t> &lambdas
         for (int b = 0; b < nb; ++b) sc.slot_ids.push_back(b);
         ds->points = g->n_visits * nb;
     } else {
-        build_schedule(g->geo, lambdas, n_wg, sc, subset, nb);
+        build_schedule(g->geo, lambdas, n_wg, sc, subset, nb, g->n_cu);
         for (int w = 0; w < sc.n_wg; ++w) {
             const int64_t nr = bundle_ray_count(g, v, w % nb);
             for (int k = sc.wg_begin[w]; k < sc.wg_begin[w + 1]; ++k)

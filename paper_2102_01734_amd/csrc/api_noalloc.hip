@@ -84,7 +84,7 @@ rt_status plan_pass(rt_grid *g, bool wj, bool wl, int n_lambda, size_t base, NoA
         auto sc = std::make_unique<Schedule>();
         std::vector<int32_t> lams(n_lambda);
         for (int i = 0; i < n_lambda; ++i) lams[i] = i;
-        build_schedule(g->geo, lams, n_wg, *sc, nullptr, nb);
+        build_schedule(g->geo, lams, n_wg, *sc, nullptr, nb, g->n_cu);
         it = g->na_sched.emplace(key, std::move(sc)).first;
     }
     p.v = v;

@@ -107,9 +107,9 @@ struct Schedule {
 
 // Distributes (lambda, direction) items over n_wg persistent workgroups so
 // that their summed visit counts balance; see schedule.cpp.
-// subset: the directions to schedule (all when null).
+// subset: the directions to schedule (all when null); n_cu: compute units.
 void build_schedule(const BoxGeometry &g, const std::vector<int32_t> &lambdas, int n_wg, Schedule &out,
-                    const std::vector<int32_t> *subset = nullptr, int n_bundles = 1);
+                    const std::vector<int32_t> *subset = nullptr, int n_bundles = 1, int n_cu = 256);
 
 // Splits the directions into n_shards sets of nearly equal visit count
 // (longest first to the lightest shard); returns shard `shard` sorted.

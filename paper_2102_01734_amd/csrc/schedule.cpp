@@ -23,7 +23,11 @@
 //   opacity/source data in their L2.
 // * batch <= workgroups: every wavelength gets its own group of workgroups
 //   (sizes differ by at most one) and its directions are spread over them by
-//   longest-processing-time-first; one slot per workgroup.
+//   longest-processing-time-first; one slot per workgroup.  Workgroups go to the
+//   CUs in turn, n_cu to a row; the shares, heaviest first, are laid along the rows
+//   to and fro, so that a CU's workgroups add up to about the same load everywhere
+//   (laid wavelength by wavelength, with a multiple of n_cu workgroups each, the
+//   heaviest of every wavelength met on one CU).
 // * batch >  workgroups: items are laid out wavelength-major and cut into
 //   n_wg contiguous runs of equal cost; a workgroup opens a new slot whenever
 //   its run enters a new wavelength.
@@ -39,7 +43,8 @@ namespace rt3d {
 // One class of workgroups (those sweeping the same ray bundle) gets every
 // (wavelength, direction) item; `wgs` are the class's workgroup ids.
 static void schedule_class(const BoxGeometry &g, const std::vector<int32_t> &lambdas, const std::vector<int> &order,
-                           const std::vector<int> &wgs, std::vector<std::vector<WorkItem>> &per_wg,
+                           const std::vector<int> &wgs, int n_bundles, int n_cu,
+                           std::vector<std::vector<WorkItem>> &per_wg,
                            std::vector<std::vector<int32_t>> &slots_of_lambda, int &slot)
 {
     const int nl = (int)lambdas.size();
@@ -77,7 +82,7 @@ static void schedule_class(const BoxGeometry &g, const std::vector<int32_t> &lam
         std::vector<int> cnt(nl, n_wg / nl);
         for (int i = 0; i < n_wg % nl; ++i) cnt[i]++;
         for (int i = 0; i < nl; ++i) cnt[i] = std::max(1, std::min(cnt[i], nd));
-        int next = 0;  // next workgroup of the class
+        std::vector<std::pair<int64_t, std::vector<WorkItem>>> shares;  // load, items of a workgroup
         for (int li = 0; li < nl; ++li) {
             const int k = cnt[li];
             // LPT: longest direction to the least loaded workgroup of this wavelength
@@ -93,13 +98,23 @@ static void schedule_class(const BoxGeometry &g, const std::vector<int32_t> &lam
             }
             for (int w = 0; w < k; ++w) {
                 if (local[w].empty()) continue;
-                const int wg = wgs[(next++) % n_wg];
-                for (auto &it : local[w]) it.slot = slot;
+                int64_t load = 0;
+                for (auto &it : local[w]) {
+                    it.slot = slot;
+                    load += g.dirs[it.dir].M;
+                }
                 local[w][0].first = 1;
                 slots_of_lambda[li].push_back(slot);
                 ++slot;
-                for (auto &it : local[w]) per_wg[wg].push_back(it);
+                shares.emplace_back(load, std::move(local[w]));
             }
+        }
+        std::stable_sort(shares.begin(), shares.end(), [](const auto &a, const auto &b) { return a.first > b.first; });
+        const int row = std::max(1, n_cu / n_bundles), n_shares = (int)shares.size();
+        for (int r = 0; r < n_shares; ++r) {
+            const int r0 = r / row * row, len = std::min(row, n_wg - r0);
+            const int at = (r / row) % 2 ? r0 + len - 1 - (r - r0) : r;
+            per_wg[wgs[at]] = std::move(shares[r].second);
         }
     } else {
         // contiguous equal-cost runs over the wavelength-major item list
@@ -133,7 +148,7 @@ static void schedule_class(const BoxGeometry &g, const std::vector<int32_t> &lam
 }
 
 void build_schedule(const BoxGeometry &g, const std::vector<int32_t> &lambdas, int n_wg, Schedule &out,
-                    const std::vector<int32_t> *subset, int n_bundles)
+                    const std::vector<int32_t> *subset, int n_bundles, int n_cu)
 {
     out = Schedule();
     const int nl = (int)lambdas.size();
@@ -159,7 +174,7 @@ void build_schedule(const BoxGeometry &g, const std::vector<int32_t> &lambdas, i
     for (int b = 0; b < n_bundles; ++b) {
         std::vector<int> wgs;
         for (int w = b; w < n_wg; w += n_bundles) wgs.push_back(w);
-        schedule_class(g, lambdas, order, wgs, per_wg, slots_of_lambda, slot);
+        schedule_class(g, lambdas, order, wgs, n_bundles, n_cu, per_wg, slots_of_lambda, slot);
     }
     // slots are numbered by workgroup id in the XCD-rounds case and densely otherwise
     int n_slots = 0;

@@ -590,6 +590,33 @@ static void stencil_routes()
     CHECK(ties > 0);
 }
 
+// The workgroups that meet on one of 256 CUs (dealt in turn) add up to about the same
+// number of visits everywhere.
+static void balanced_cus()
+{
+    for (int nl : {2, 5, 8, 14})
+        for (int nb : {1, 2, 4})
+            for (int per_cu : {2, 4, 7}) {
+                BoxGeometry geo;
+                CHECK(build_box_geometry(20, 20, 30, 16, 24, geo).empty());
+                std::vector<int32_t> lams(nl);
+                for (int i = 0; i < nl; ++i) lams[i] = i;
+                Schedule s;
+                build_schedule(geo, lams, 256 * per_cu, s, nullptr, nb);
+                std::vector<double> cu(256, 0.0);
+                double sum = 0.0, longest = 0.0;
+                for (int w = 0; w < s.n_wg; ++w) {
+                    double load = 0.0;
+                    for (int k = s.wg_begin[w]; k < s.wg_begin[w + 1]; ++k) load += geo.dirs[s.items[k].dir].M;
+                    cu[w % 256] += load;
+                    sum += load;
+                    longest = std::max(longest, load);
+                }
+                // as far as whole workgroups allow: half of the heaviest one above the mean
+                CHECK(*std::max_element(cu.begin(), cu.end()) <= std::max(longest, sum / 256 + 0.5 * longest));
+            }
+}
+
 int main(int argc, char **argv)
 {
     const std::string which = argc > 1 ? argv[1] : "";
@@ -601,6 +628,7 @@ int main(int argc, char **argv)
     else if (which == "shapes_asked_once") shapes_asked_once();
     else if (which == "slot_bound") slot_bound();
     else if (which == "stencil_routes") stencil_routes();
+    else if (which == "balanced_cus") balanced_cus();
     else return 2;
     if (g_fail == 0) std::printf("%s passed\n", which.c_str());
     return g_fail == 0 ? 0 : 1;

@@ -87,3 +87,9 @@ def test_routes_of_stencils(fake):
     """Where the templates of a quadrature cross two faces at once (45 degrees), the
     linear operator goes by rows as soon as the characteristics are many."""
     _case(fake, "stencil_routes")
+
+
+def test_workgroups_of_a_cu_balance(fake):
+    """Batches on several workgroups a CU: the heaviest shares of the wavelengths must
+    not meet on one CU."""
+    _case(fake, "balanced_cus")
