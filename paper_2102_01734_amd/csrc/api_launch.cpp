@@ -122,24 +122,44 @@ void setup_variant(rt_grid *g, bool dbl, bool wj, bool wl)
     }
 }
 
-// Estimated time (cycles) of a launch of n_lambda x n_dirs items per bundle
-// whose directions have sum_m visits in all and max_m at most.  A visit costs a
-// workgroup a fixed part (barrier, visit set-up, the wave's own latency) plus
-// an issue part per ray-wave on its SIMD, which the workgroups of a CU share;
-// a layer end costs the memory latency of its flush, once per group of words
-// that a thread reads together, and an issue part per word.  Items are dealt
-// longest first, so a launch takes at least its longest item.  The constants
-// are fits to 33^3 .. 257^3 launches of 12 shapes each (one MI355X): single
-// precision 950 + 300 x, double 950 + 390 x (480 x for more than six rays a
-// thread, whose state does not stay in registers).
-static double shape_cost(const rt_grid *g, const Variant &v, int n_lambda, int n_dirs, double sum_m, double max_m)
+// Visits of the most loaded of k workgroups that share directions of M visits (longest
+// first, each to the least loaded): the bounds that such dealing meets closely.
+static double makespan(const std::vector<double> &M, double sum_m, int64_t k)
 {
-    const double waves = v.nthr / 64, nz = g->geo.Nz;
+    const int64_t n = (int64_t)M.size();
+    double most = std::max(M[0], sum_m / (double)k);
+    for (int64_t j = 1; j * k < n && j <= 4; ++j) {
+        double v = 0.0;
+        for (int64_t i = std::max<int64_t>(0, j * k - j); i <= j * k; ++i) v += M[i];
+        most = std::max(most, v);
+    }
+    return most;
+}
+
+// Estimated time (cycles) of a launch of n_lambda wavelengths over directions of M visits
+// (longest first).  A visit costs a workgroup a fixed part (barrier, visit set-up, the
+// wave's own latency) and an issue part per ray-wave on its fullest SIMD; workgroups that
+// share a CU hide each other's fixed part, but add up on the SIMDs, where waves that are
+// no multiple of four tend to meet on the same one.  A layer end costs the latency of its
+// flush, once per group of words that a thread reads together, and an issue part per
+// word.  The launch takes as long as the most loaded workgroup on its own or the chip's
+// throughput, whichever is more, a little of the other, and the slots' reduction.
+//
+// The constants are fits to 6000 timed launches (one MI355X): 153 calls of 5 to 257 voxels
+// a side, 4 to 2048 directions, 1 to 16 wavelengths, both precisions, each on all its
+// shapes.  Over these calls the shape taken is 4 % slower than the fastest in the mean
+// (with one visit cost for workgroups alone and together, and small batches costed as
+// one wavelength: 12 %, and up to 1.7 times slower than the widest workgroup).
+static double shape_cost(const rt_grid *g, const Variant &v, int n_lambda, const std::vector<double> &M, double sum_m)
+{
+    const double nz = g->geo.Nz, n_cu = g->n_cu, n_dirs = (double)M.size();
+    const double waves = v.nthr / 64, simd = std::ceil(waves / 4.0) * v.R;  // ray-waves of the fullest SIMD
     const double items = (double)n_lambda * n_dirs * v.nb;
-    const double per_cu = std::ceil(std::min((double)v.n_wg, items) / g->n_cu);
-    const double conc = std::min(items, std::min((double)v.n_wg, per_cu * g->n_cu));
-    const double x = std::max(std::ceil(waves / 4.0) * v.R, per_cu * waves * v.R / 4.0);
-    double c = v.dbl ? (v.R > 6 ? 450.0 : 370.0) : v.band ? 270.0 : 290.0;
+    const double per_cu = std::ceil(std::min((double)v.n_wg, items) / n_cu);
+    const double conc = std::min(items, std::min((double)v.n_wg, per_cu * n_cu));
+    const double even = per_cu * waves * v.R / 4.0, apart = waves >= 4.0 ? per_cu * simd : std::max(even, simd);
+    const double shared = std::max(simd, even + 0.93 * std::max(0.0, apart - even));
+    double c = v.dbl ? (v.R > 6 ? 446.0 : 408.0) : v.band ? 277.0 : 326.0;
     // a wavelength's padded field beyond the 256 MB Infinity Cache: the HBM latency
     // shows where 30 rays and more share a SIMD lane's 512 registers, which then
     // hold few pairs in flight (257^3 x 512: 1024 x 8 180 ms, 768 x 11 179, 768 x 10
@@ -150,23 +170,38 @@ static double shape_cost(const rt_grid *g, const Variant &v, int n_lambda, int n
     // the point's temporaries pass the 128 registers that four waves a SIMD leave, as
     // they do at no smaller workgroup (J and Lambda* in single, 129^3 x
     // 256 directions: 1024 x 8 12.2 ms, 768 x 6 11.2; x 2048 88.6 and 86.8;
-    // 161 x 161 x 65 x 256 x 2 wavelengths 16.5 and 15.4; 768 x 11: 12.0, 78.3)
-    if (!v.dbl && v.wj && v.wl && v.lb == 1024 && v.R >= 8) c *= 1.15;
-    if (v.wj && v.wl) c *= 1.25;
+    // 161 x 161 x 65 x 256 x 2 wavelengths 16.5 and 15.4; 768 x 11: 12.0, 78.3); one
+    // output keeps fewer pairs in flight there
+    if (!v.dbl && v.lb == 1024 && v.R >= 8) c *= v.wj && v.wl ? 1.15 * 1.03 : 1.03;
+    if (!v.dbl && v.lb == 512 && v.R >= 9) c *= 1.03;
+    if (v.wj && v.wl) c *= 1.09;
     else if (v.wl) c *= 0.8;
+    const double alone = 400.0 + c * simd, full = std::max(alone, 560.0 + c * shared);
     const bool wide = v.band && !v.dbl && !(v.wj && v.wl);
     const double words = (v.band ? v.tile_words / (wide ? 2.0 : 1.0) : (double)g->geo.Nx * g->geo.Ny) *
                          ((v.wj ? 1 : 0) + (v.wl ? 1 : 0));
-    const double group = !v.band ? 4.0 : !wide ? 4.0 : v.R >= 8 && v.lb <= 768 ? 18.0 : 8.0;
+    const double group = !wide ? 4.0 : v.R >= 8 && v.lb <= 768 ? 18.0 : 8.0;
     const double per_thr = std::ceil(words / v.nthr);
     const bool reads = items > conc;  // a slot's first item only stores
-    const double flush = 300.0 + (reads ? 2500.0 * std::ceil(per_thr / group) : 0.0) + 40.0 * per_thr;
-    const double visit = 950.0 + c * x;
-    const double longest = max_m * visit + nz * flush;
-    const double mean = (sum_m * visit + n_dirs * nz * flush) * n_lambda * v.nb / conc;
-    // partial sums: written and read once at about 4 TB/s (2.3 GHz cycles)
+    const double flush = 990.0 + (reads ? 470.0 * std::ceil(per_thr / group) : 0.0) + 107.0 * per_thr;
+    const double flush_full = std::max(flush, 990.0 + 107.0 * per_thr * std::max(1.0, even / simd));
+    // the most loaded workgroup: its visits and items
+    const int64_t k = v.n_wg / v.nb;
+    double visits, own;
+    if (n_lambda <= k) {
+        const int64_t share = std::max<int64_t>(1, std::min<int64_t>(k / n_lambda, (int64_t)M.size()));
+        visits = makespan(M, sum_m, share);
+        own = std::ceil(n_dirs / (double)share);
+    } else {
+        visits = sum_m * n_lambda / (double)k;
+        own = std::ceil(n_dirs * n_lambda / (double)k);
+    }
+    const double chain = visits * alone + nz * flush * own, chain_full = visits * full + nz * flush_full * own;
+    const double chip = (sum_m * full + n_dirs * nz * flush_full) * n_lambda * v.nb / conc;
+    const double sweep = std::max(std::max(chain, chip), 0.12 * chain_full + 0.88 * chain) + 0.037 * std::min(chain, chip);
+    // partial sums: written and read once at about 4.7 TB/s (2.3 GHz cycles)
     const double slots = conc * (double)g->n_vox * (v.dbl ? 8 : 4) * ((v.wj ? 1 : 0) + (v.wl ? 1 : 0));
-    return std::max(longest, mean + 0.25 * longest) + 2.0 * slots / 1740.0;
+    return sweep + 1.7 * slots / 1740.0 + 22700.0;  // and the call's launches
 }
 
 // The shapes that calls of a precision and outputs choose among: each compiled shape
@@ -210,19 +245,14 @@ static Variant estimate_variant(rt_grid *g, bool dbl, bool wj, bool wl, int n_la
         sum_m += m;
         max_m = std::max(max_m, m);
     }
-    // small batches run the shape of a single wavelength: as long as every item has a
-    // slot of its own (n_item <= n_wg / nb, the workgroups of a bundle) they give its
-    // results bit for bit; beyond, directions share slots in another way and the sums
-    // are rounded in another order
-    const int64_t n_item = (int64_t)n_lambda * n_dirs;
-    const int n_eff = n_item < 2 * g->n_cu ? 1 : n_lambda;
     char key[96];
-    snprintf(key, sizeof key, "%d%d%d/%d/%d/%.0f/%.0f", dbl, wj, wl, n_eff, n_dirs, sum_m, max_m);
+    snprintf(key, sizeof key, "%d%d%d/%d/%d/%.0f/%.0f", dbl, wj, wl, n_lambda, n_dirs, sum_m, max_m);
     auto it = g->picks.find(key);
     if (it != g->picks.end()) return it->second;
     if (g->picks.size() > 256) g->picks.clear();
     // no more workgroups than items, and more partial sums than the fewest-bundle
     // shape has only while they stay below a gigabyte
+    const int64_t n_item = (int64_t)n_lambda * n_dirs;
     const double slot_bytes = (double)g->n_vox * (dbl ? 8 : 4) * ((wj ? 1 : 0) + (wl ? 1 : 0));
     const int64_t most = std::max<int64_t>(base.n_wg, (int64_t)(1e9 / slot_bytes));
     const int64_t items = std::max<int64_t>(n_item, 2 * g->n_cu);
@@ -231,17 +261,37 @@ static Variant estimate_variant(rt_grid *g, bool dbl, bool wj, bool wl, int n_la
         v.n_wg -= v.n_wg % v.nb;
         return v.n_wg >= v.nb;
     };
+    // A small batch runs the shape of a single wavelength where every item then has a
+    // slot of its own (n_item <= n_wg / nb, the workgroups of a bundle), and gives its
+    // results bit for bit; beyond, directions share slots in another way and the sums
+    // are rounded in another order, so the batch has a shape of its own.
+    if (n_lambda > 1 && n_item < 2 * g->n_cu) {
+        const Variant single = estimate_variant(g, dbl, wj, wl, 1, subset);
+        if (single.n_wg / single.nb >= n_item) {
+            g->picks.emplace(key, single);
+            return single;
+        }
+    }
+    std::vector<double> M(n_dirs);
+    for (int i = 0; i < n_dirs; ++i) M[i] = g->geo.dirs[subset ? (*subset)[i] : i].M;
+    std::sort(M.begin(), M.end(), [](double x, double y) { return x > y; });
     Variant best = base;
-    double best_cost = base.spill ? 1e300 : shape_cost(g, base, n_eff, n_dirs, sum_m, max_m);
+    double best_cost = 1e300;
     for (Variant v : candidates(g, dbl, wj, wl)) {
         if (!trim(v)) continue;
-        const double cost = shape_cost(g, v, n_eff, n_dirs, sum_m, max_m);
-        // a few per cent are within the estimate's error: the earlier shape stays
-        if (cost < 0.97 * best_cost) {
+        const double cost = shape_cost(g, v, n_lambda, M, sum_m);
+        if (cost < best_cost) {
             best = v;
             best_cost = cost;
         }
     }
+    // The default shape, whose widest workgroups flush least, stays unless the estimate
+    // puts another well below it: ten per cent is about the estimate's error (without
+    // this one of the 153 calls above was 1.5 times slower than the default).  1024
+    // threads of eight rays and more in single are no such yardstick: they are often the
+    // slowest that fits.
+    const double margin = !dbl && base.lb == 1024 && base.R >= 8 ? 0.97 : 0.907;
+    if (!base.spill && !(best_cost < margin * shape_cost(g, base, n_lambda, M, sum_m))) best = base;
     g->picks.emplace(key, best);
     return best;
 }

@@ -1,7 +1,7 @@
-"""A small batch runs the launch shape of a single wavelength.  As long as the workgroups
-of a ray bundle are at least its wavelengths times directions, every direction has a
-partial sum of its own and the batch gives each wavelength's results bit for bit; beyond
-that, directions share partial sums in another order."""
+"""A small batch runs the launch shape of a single wavelength as long as that shape's
+workgroups of a ray bundle are at least its wavelengths times directions: every direction
+has a partial sum of its own and the batch gives each wavelength's results bit for bit.
+Beyond that, directions share partial sums in another order."""
 import numpy as np
 import pytest
 
@@ -22,8 +22,10 @@ def test_batch_against_its_wavelengths(nx, n_mu, n_phi, lam, own, prec):
     case = sy.random_box(nx, 45, 5, n_mu, n_phi, seed=nx, dtype=prec, n_lambda=lam)
     S = to_dev(sy.random_source(case.chi.shape, seed=3, dtype=prec), prec)
     chi, bc = to_dev(case.chi, prec), to_dev(case.I_bc, prec)
+    single = make_grid(case, n_lambda_max=1)
+    per_bundle = single.info()["n_workgroups"] // single.launch_shape()["bundles"]
+    single.close()
     g = make_grid(case)
-    per_bundle = g.info()["n_workgroups"] // g.launch_shape()["bundles"]
     fits = lam * n_mu * n_phi <= per_bundle
     print(nx, n_mu * n_phi, lam, prec, g.launch_shape(), "workgroups a bundle", per_bundle, fits, flush=True)
     assert own is None or fits == own
