@@ -169,17 +169,25 @@ template hipError_t pad_field<double, float>(const double *, const double *, flo
                                              hipStream_t);
 
 // ---------------------------------------------------------------------------
-// Sum of a voxel's partial slots (double accumulation).  The slots are split
-// over G wavefronts of the block, each adding a contiguous run of them in
-// order with eight loads in flight, and the G sums are added in order: a fixed
-// order for a given grid.  A thread per voxel (G = 1) fills the chip only
-// from about a quarter million voxels on; below that one wavefront walked 256
-// slots on its own, which took 36-43 us on 33^3 voxels (37 MB of slots).
-// G depends on the number of voxels alone, so a wavelength's sum does not
-// depend on the batch it is in.  With G > 1 the result is valid in the first
-// wavefront (threads 0-63), one voxel a lane.
+// Sum of a voxel's partial slots (double accumulation).  The slots are cut into
+// G contiguous runs, each added in order, and the G sums are added in order: a
+// fixed order for a given grid, as G depends on the number of voxels alone, so
+// that a wavelength's sum does not depend on the batch it is in.  The runs are
+// shared by W wavefronts of a block over the same 64 voxels, with eight loads in
+// flight each: a thread per voxel (W = 1) fills the chip only from about a
+// quarter million voxels of the batch on; below that one wavefront walked 256
+// slots on its own, which took 36-43 us on 33^3 voxels (37 MB of slots).  Beyond,
+// more wavefronts only leave idle ones beside what follows the sum (an update of
+// 58 x 101 x 9 voxels x 16 wavelengths of 16 slots in double: W = 16 164 us, 1
+// 61).  With W > 1 the result is valid in the first wavefront (threads 0-63), one
+// voxel a lane.
 // ---------------------------------------------------------------------------
 constexpr int slot_groups(int64_t n_vox) { return n_vox >= 262144 ? 1 : n_vox >= 65536 ? 4 : 16; }
+constexpr int slot_waves(int64_t n_vox, int n_batch)
+{
+    const int W = slot_groups(n_vox * n_batch), G = slot_groups(n_vox);
+    return W < G ? W : G;
+}
 
 template <typename TP>
 __device__ __forceinline__ double slot_run(const TP *__restrict__ part, const int32_t *__restrict__ slot_ids, int s,
@@ -198,40 +206,80 @@ __device__ __forceinline__ double slot_run(const TP *__restrict__ part, const in
     return acc;
 }
 
+// All G runs by one thread: the loads go on over the ends of the (short) runs.
 template <typename TP, int G>
+__device__ __forceinline__ double slot_runs(const TP *__restrict__ part, const int32_t *__restrict__ slot_ids, int s0,
+                                            int s1, int64_t n_vox, int64_t v)
+{
+    const int n = s1 - s0;
+    double sum = 0.0, acc = 0.0;
+    int g = 0, end = s0 + n / G;
+    constexpr int U = 8;
+    for (int s = s0; s < s1; s += U) {
+        TP x[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (s + u < s1) x[u] = part[(int64_t)slot_ids[s + u] * n_vox + v];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (s + u < s1) {
+                while (s + u == end) {  // run g ends here
+                    sum += acc;
+                    acc = 0.0;
+                    ++g;
+                    end = s0 + n * (g + 1) / G;
+                }
+                acc += (double)x[u];
+            }
+    }
+    return sum + acc;
+}
+
+template <typename TP, int G, int W>
 __device__ __forceinline__ double slot_sum(const TP *__restrict__ part, const int32_t *__restrict__ slot_begin,
                                            const int32_t *__restrict__ slot_ids, int b, int64_t n_vox, int64_t v)
 {
     const int s0 = slot_begin[b], s1 = slot_begin[b + 1];
-    if constexpr (G == 1) return v < n_vox ? slot_run(part, slot_ids, s0, s1, n_vox, v) : 0.0;
-    __shared__ double sums[G][64];
-    const int g = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), n = s1 - s0;
-    double acc = v < n_vox ? slot_run(part, slot_ids, s0 + n * g / G, s0 + n * (g + 1) / G, n_vox, v) : 0.0;
-    sums[g][threadIdx.x % 64] = acc;
-    __syncthreads();
-    if (g == 0)
-        for (int k = 1; k < G; ++k) acc += sums[k][threadIdx.x];
-    return acc;
+    if constexpr (G == 1) {
+        return v < n_vox ? slot_run(part, slot_ids, s0, s1, n_vox, v) : 0.0;
+    } else if constexpr (W == 1) {
+        return v < n_vox ? slot_runs<TP, G>(part, slot_ids, s0, s1, n_vox, v) : 0.0;
+    } else {
+        __shared__ double sums[G][64];
+        const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), n = s1 - s0;
+        constexpr int R = G / W;  // runs a wavefront
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int g = w * R + r;
+            sums[g][threadIdx.x % 64] =
+                v < n_vox ? slot_run(part, slot_ids, s0 + n * g / G, s0 + n * (g + 1) / G, n_vox, v) : 0.0;
+        }
+        __syncthreads();
+        double acc = 0.0;
+        if (w == 0)
+            for (int g = 0; g < G; ++g) acc += sums[g][threadIdx.x];
+        return acc;
+    }
 }
 
 // Voxel of this thread and whether it writes (blocks of 256 threads for
-// G = 1, of G wavefronts over 64 voxels otherwise).
-template <int G>
+// W = 1, of W wavefronts over 64 voxels otherwise).
+template <int W>
 __device__ __forceinline__ int64_t slot_voxel()
 {
-    return G == 1 ? (int64_t)blockIdx.x * 256 + threadIdx.x : (int64_t)blockIdx.x * 64 + threadIdx.x % 64;
+    return W == 1 ? (int64_t)blockIdx.x * 256 + threadIdx.x : (int64_t)blockIdx.x * 64 + threadIdx.x % 64;
 }
 
-template <int G>
+template <int W>
 static dim3 slot_grid(int64_t n_vox, int n_batch)
 {
-    const int64_t per = G == 1 ? 256 : 64;
+    const int64_t per = W == 1 ? 256 : 64;
     return dim3((unsigned)((n_vox + per - 1) / per), (unsigned)n_batch);
 }
 
 // out[lambda_of[b]][v] = sum of the slots of batch entry b (grid row z: J, Lambda*)
-template <typename TP, typename TO, int G>
-__global__ void __launch_bounds__(G == 1 ? 256 : 64 * G) reduce_kernel(const TP *__restrict__ part0,
+template <typename TP, typename TO, int G, int W>
+__global__ void __launch_bounds__(W == 1 ? 256 : 64 * W) reduce_kernel(const TP *__restrict__ part0,
                                                                        const TP *__restrict__ part1,
                                                                        const int32_t *__restrict__ slot_begin,
                                                                        const int32_t *__restrict__ slot_ids,
@@ -242,18 +290,18 @@ __global__ void __launch_bounds__(G == 1 ? 256 : 64 * G) reduce_kernel(const TP 
     const TP *__restrict__ part = blockIdx.z ? part1 : part0;
     TO *__restrict__ out = blockIdx.z ? out1 : out0;
     const int b = blockIdx.y;
-    const int64_t v = slot_voxel<G>();
-    const double acc = slot_sum<TP, G>(part, slot_begin, slot_ids, b, n_vox, v);
-    if (v < n_vox && (G == 1 || threadIdx.x < 64)) out[(int64_t)lambda_of[b] * n_vox + v] = (TO)acc;
+    const int64_t v = slot_voxel<W>();
+    const double acc = slot_sum<TP, G, W>(part, slot_begin, slot_ids, b, n_vox, v);
+    if (v < n_vox && (W == 1 || threadIdx.x < 64)) out[(int64_t)lambda_of[b] * n_vox + v] = (TO)acc;
 }
 
-template <typename TP, typename TO, int G>
+template <typename TP, typename TO, int G, int W>
 static hipError_t reduce_t(const TP *part, const TP *part2, const int32_t *slot_begin, const int32_t *slot_ids,
                            const int32_t *lambda_of, int n_batch, TO *out, TO *out2, int64_t n_vox, hipStream_t st)
 {
-    dim3 grid = slot_grid<G>(n_vox, n_batch);
+    dim3 grid = slot_grid<W>(n_vox, n_batch);
     grid.z = part2 ? 2 : 1;
-    hipLaunchKernelGGL((reduce_kernel<TP, TO, G>), grid, dim3(G == 1 ? 256 : 64 * G), 0, st, part, part2, slot_begin,
+    hipLaunchKernelGGL((reduce_kernel<TP, TO, G, W>), grid, dim3(W == 1 ? 256 : 64 * W), 0, st, part, part2, slot_begin,
                        slot_ids, lambda_of, out, out2, n_vox);
     return hipGetLastError();
 }
@@ -264,11 +312,18 @@ hipError_t reduce_partials(const TP *part, const int32_t *slot_begin, const int3
                            bool one_slot, const TP *part2, TO *out2)
 {
     if (n_batch == 0 || n_vox == 0) return hipSuccess;
-    switch (one_slot ? 1 : slot_groups(n_vox)) {
-    case 1: return reduce_t<TP, TO, 1>(part, part2, slot_begin, slot_ids, lambda_of, n_batch, out, out2, n_vox, st);
-    case 4: return reduce_t<TP, TO, 4>(part, part2, slot_begin, slot_ids, lambda_of, n_batch, out, out2, n_vox, st);
-    default: return reduce_t<TP, TO, 16>(part, part2, slot_begin, slot_ids, lambda_of, n_batch, out, out2, n_vox, st);
+    const int G = one_slot ? 1 : slot_groups(n_vox), W = slot_waves(n_vox, n_batch * (part2 ? 2 : 1));
+#define RT_REDUCE(GV, WV) \
+    return reduce_t<TP, TO, GV, WV>(part, part2, slot_begin, slot_ids, lambda_of, n_batch, out, out2, n_vox, st)
+    if (G == 1) RT_REDUCE(1, 1);
+    if (G == 4) {
+        if (W == 1) RT_REDUCE(4, 1);
+        RT_REDUCE(4, 4);
     }
+    if (W == 1) RT_REDUCE(16, 1);
+    if (W == 4) RT_REDUCE(16, 4);
+    RT_REDUCE(16, 16);
+#undef RT_REDUCE
 }
 
 template hipError_t reduce_partials<float, float>(const float *, const int32_t *, const int32_t *, const int32_t *, int,
@@ -401,17 +456,17 @@ template hipError_t source_update<float, double>(const double *, const float *, 
 // fused: J_fs = J_anchor + sum of partial slots; operator-splitting update;
 // S; next padded input; Ng history; per-wavelength max |dJ/J|
 // ---------------------------------------------------------------------------
-template <typename TP, typename G, typename TN, int NG>
-__global__ void __launch_bounds__(NG == 1 ? 256 : 64 * NG) ali_update_kernel(AliUpdateArgs a)
+template <typename TP, typename G, typename TN, int NG, int W>
+__global__ void __launch_bounds__(W == 1 ? 256 : 64 * W) ali_update_kernel(AliUpdateArgs a)
 {
-    constexpr int BS = NG == 1 ? 256 : 64 * NG;
+    constexpr int BS = W == 1 ? 256 : 64 * W;
     const int b = blockIdx.y;
     const int lam = a.lambda_of[b];
-    const int64_t v = slot_voxel<NG>();
-    const bool own = v < a.n_vox && (NG == 1 || threadIdx.x < 64);  // this thread's voxel is written by it
+    const int64_t v = slot_voxel<W>();
+    const bool own = v < a.n_vox && (W == 1 || threadIdx.x < 64);  // this thread's voxel is written by it
     double rel = 0.0, res = 0.0, sum = 0.0;
     if (a.part && !a.rfs_in)  // uniform over the launch
-        sum = slot_sum<TP, NG>(reinterpret_cast<const TP *>(a.part), a.slot_begin, a.slot_ids, b, a.n_vox, v);
+        sum = slot_sum<TP, NG, W>(reinterpret_cast<const TP *>(a.part), a.slot_begin, a.slot_ids, b, a.n_vox, v);
     if (a.rfs_out) {  // uniform over the launch: no thread reaches the block reductions
         if (own) {
             const int64_t i = (int64_t)lam * a.n_vox + v;
@@ -453,11 +508,11 @@ __global__ void __launch_bounds__(NG == 1 ? 256 : 64 * NG) ali_update_kernel(Ali
     }
 }
 
-template <typename TP, typename G, typename TN, int NG>
+template <typename TP, typename G, typename TN, int NG, int W>
 static hipError_t ali_update_g(const AliUpdateArgs &a, int n_batch, hipStream_t st)
 {
-    hipLaunchKernelGGL((ali_update_kernel<TP, G, TN, NG>), slot_grid<NG>(a.n_vox, n_batch),
-                       dim3(NG == 1 ? 256 : 64 * NG), 0, st, a);
+    hipLaunchKernelGGL((ali_update_kernel<TP, G, TN, NG, W>), slot_grid<W>(a.n_vox, n_batch),
+                       dim3(W == 1 ? 256 : 64 * W), 0, st, a);
     return hipGetLastError();
 }
 
@@ -465,11 +520,11 @@ template <typename TP, typename G, typename TN>
 static hipError_t ali_update_t(const AliUpdateArgs &a, int n_batch, hipStream_t st)
 {
     // launches that sum no slots, or one per voxel, need no groups
-    switch (a.part && !a.rfs_in && !a.one_slot ? slot_groups(a.n_vox) : 1) {
-    case 1: return ali_update_g<TP, G, TN, 1>(a, n_batch, st);
-    case 4: return ali_update_g<TP, G, TN, 4>(a, n_batch, st);
-    default: return ali_update_g<TP, G, TN, 16>(a, n_batch, st);
-    }
+    const int NG = a.part && !a.rfs_in && !a.one_slot ? slot_groups(a.n_vox) : 1, W = slot_waves(a.n_vox, n_batch);
+    if (NG == 1) return ali_update_g<TP, G, TN, 1, 1>(a, n_batch, st);
+    if (NG == 4) return W == 1 ? ali_update_g<TP, G, TN, 4, 1>(a, n_batch, st) : ali_update_g<TP, G, TN, 4, 4>(a, n_batch, st);
+    if (W == 1) return ali_update_g<TP, G, TN, 16, 1>(a, n_batch, st);
+    return W == 4 ? ali_update_g<TP, G, TN, 16, 4>(a, n_batch, st) : ali_update_g<TP, G, TN, 16, 16>(a, n_batch, st);
 }
 
 hipError_t ali_update(const AliUpdateArgs &a, bool part_double, bool grid_double, bool next_double, int n_batch,
